@@ -747,8 +747,13 @@ __device__ void final_tile(const StageArgs &a, int tile, double *smem, bool xwl)
     load_cell_in<K, FLUX>(I, c, a.BC[bp] + I.offC, a.BD[bp] + I.offD, ci);
     double sig[2][3] = {{0, 0, 0}, {0, 0, 0}};
     if (damp) {
-        reduce_instance<nthreads(T), NC>(a.part[(int)((a.ns * N - 1) & 1)], I.tile0, I.npart, false, red,
-                                         scratch);
+        if (a.red) {                         // folded (launch_fold_final_1d)
+            if (threadIdx.x < NSTAT) red[threadIdx.x] = a.red[(long long)tl.inst * NSTAT + threadIdx.x];
+            __syncthreads();
+        } else {
+            reduce_instance<nthreads(T), NC>(a.part[(int)((a.ns * N - 1) & 1)], I.tile0, I.npart, false, red,
+                                             scratch);
+        }
         finish_stats<NC>(I, red, sig);
     }
     damp_cell<K, FLUX>(I, c, ci, sig, tau, damp);
@@ -825,7 +830,13 @@ __global__ __launch_bounds__(nthreads(T), T == 64 && K <= 2 ? 3 : 1) void k_stag
 // One workgroup per instance: the partial columns of the state the next stage
 // reads (part[src]) reduced in the same fixed order as a stage kernel's own
 // reduction (same thread count, same tree), so batched instances keep the bits
-// of single-instance runs.  All NSTAT rows go to red[instance][row].
+// of single-instance runs.  All NSTAT rows go to red[instance][row].  src < 0:
+// the state that the final kernel damps (the output of the instance's last
+// executed stage).
+__device__ inline int fold_source(const StageArgs &a, int src, int inst) {
+    return src >= 0 ? src : (int)((a.ns * a.fin[inst].nexec - 1) & 1);
+}
+
 template <int NC, int T>
 __global__ __launch_bounds__(nthreads(T)) void k_fold(StageArgs a, int src) {
     __shared__ double red[NSTAT];
@@ -834,8 +845,44 @@ __global__ __launch_bounds__(nthreads(T)) void k_fold(StageArgs a, int src) {
     if (tid < NSTAT) red[tid] = 0.0;
     __syncthreads();
     const Inst1D I = a.ninst == 1 ? a.inst0 : a.inst[b];
-    reduce_instance<nthreads(T), NC>(a.part[src], I.tile0, I.npart, true, red, scratch);
+    reduce_instance<nthreads(T), NC>(a.part[fold_source(a, src, b)], I.tile0, I.npart, true, red, scratch);
     if (tid < NSTAT) a.red[(long long)b * NSTAT + tid] = red[tid];
+}
+
+// The same reduction with a workgroup per row (grid: instances x rows), for
+// instances of many tiles, where k_fold is bound by one workgroup's chain of
+// waits (81 rounds of 20 loads at 15626 tiles: 87 us, the other CUs idle).  A
+// workgroup per row with FOLD_AHEAD loads in flight per thread takes 22 us there.
+// Thread count, order and tree are k_fold's, so the bits are too.
+constexpr int FOLD_AHEAD = 8;
+
+template <int NC, int T>
+__global__ __launch_bounds__(nthreads(T)) void k_fold_rows(StageArgs a, int src) {
+    constexpr int NT = nthreads(T), NW = NT / WAVE;
+    __shared__ double scratch[NW];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid % WAVE;
+    const Inst1D I = a.ninst == 1 ? a.inst0 : a.inst[b];
+    const int row = stat_row<NC>(blockIdx.y), kind = stat_kind(row), n = I.npart;
+    const double *col = a.part[fold_source(a, src, b)] + (long long)I.tile0 * NSTAT + row;
+    double acc = stat_identity(kind);
+    for (int t0 = tid; t0 < n; t0 += FOLD_AHEAD * NT) {
+        double x[FOLD_AHEAD];
+#pragma unroll
+        for (int i = 0; i < FOLD_AHEAD; ++i) x[i] = col[(long long)min(t0 + i * NT, n - 1) * NSTAT];
+#pragma unroll
+        for (int i = 0; i < FOLD_AHEAD; ++i) {
+            const double y = stat_op(kind, acc, x[i]);
+            acc = t0 + i * NT < n ? y : acc;
+        }
+    }
+    acc = wave_reduce(kind, acc);
+    if (lane == WAVE - 1) scratch[tid / WAVE] = acc;
+    __syncthreads();
+    if (tid == 0) {
+        double v = scratch[0];
+        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, scratch[w]);
+        a.red[(long long)b * NSTAT + row] = v;
+    }
 }
 
 // Step records (both parities), final record of instance i, and with i = 0
@@ -1025,20 +1072,38 @@ hipError_t launch_stage_1d(const StageArgs &a, int kmax, int flux, int tile, hip
     return launch(pick<0>(kmax, flux, ti), b.tend - b.tbeg, tile, b, s);   // one workgroup per tile
 }
 
-hipError_t launch_fold_1d(const StageArgs &a, int flux, int tile, hipStream_t s) {
+// Instances of more tiles than this are folded with a workgroup per row: up to
+// it, k_fold's threads have all their tiles' rows in flight in one round of loads
+// (6.2 us for 512 instances of up to 129 tiles), beyond it they wait round by round.
+static int fold_rows(int tile) { return 2 * nthreads(tile); }
+
+static hipError_t launch_fold(const StageArgs &a, int src, int flux, int tile, int maxpart, hipStream_t s) {
     // the reduction uses nthreads(tile) threads, as a stage workgroup does
     // (an extra-wave launch's fifth wave takes no part in it either)
     if (!a.red || tile_index(tile) < 0) return hipErrorInvalidValue;
-    // the partials the stage (a.l, a.par) reads: those of the previous global stage
-    const int src = ((((a.ns & 1) ? a.par : 0) + a.l) & 1) ^ 1;
     void *fn = nullptr;
     const int nc = flux == 0 || flux == 1 ? 1 : 3;
-    if (nc == 1) fn = tile == 32 ? (void *)k_fold<1, 32> : (tile == 64 ? (void *)k_fold<1, 64> : (void *)k_fold<1, 128>);
-    else fn = tile == 32 ? (void *)k_fold<3, 32> : (tile == 64 ? (void *)k_fold<3, 64> : (void *)k_fold<3, 128>);
+    const bool rows = maxpart > fold_rows(tile);
+    if (rows) {
+        if (nc == 1) fn = tile == 32 ? (void *)k_fold_rows<1, 32> : (tile == 64 ? (void *)k_fold_rows<1, 64> : (void *)k_fold_rows<1, 128>);
+        else fn = tile == 32 ? (void *)k_fold_rows<3, 32> : (tile == 64 ? (void *)k_fold_rows<3, 64> : (void *)k_fold_rows<3, 128>);
+    } else {
+        if (nc == 1) fn = tile == 32 ? (void *)k_fold<1, 32> : (tile == 64 ? (void *)k_fold<1, 64> : (void *)k_fold<1, 128>);
+        else fn = tile == 32 ? (void *)k_fold<3, 32> : (tile == 64 ? (void *)k_fold<3, 64> : (void *)k_fold<3, 128>);
+    }
     StageArgs copy = a;
     int srcv = src;
     void *args[] = {&copy, &srcv};
-    return hipLaunchKernel(fn, dim3(a.ninst), dim3(nthreads(tile)), args, 0, s);
+    return hipLaunchKernel(fn, dim3(a.ninst, rows ? 6 * nc + 2 : 1), dim3(nthreads(tile)), args, 0, s);
+}
+
+hipError_t launch_fold_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s) {
+    // the partials the stage (a.l, a.par) reads: those of the previous global stage
+    return launch_fold(a, ((((a.ns & 1) ? a.par : 0) + a.l) & 1) ^ 1, flux, tile, maxpart, s);
+}
+
+hipError_t launch_fold_final_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s) {
+    return launch_fold(a, -1, flux, tile, maxpart, s);
 }
 
 hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s) {

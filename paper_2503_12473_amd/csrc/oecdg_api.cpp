@@ -36,6 +36,7 @@ struct oecdg_handle {
     int rk = 3;              // RK method of every instance (rk_stage)
     bool tailwave = false;   // some instance's last tile updates the extra dual cell (launches carry one more wave)
     int ncol = 0;            // partial-statistics columns (the tiles, plus one per tail)
+    int maxpart = 0;         // the most columns of one instance
     int tile = 64;
     int mode = OECDG_MODE_AUTO;
     int graph_steps = 64;
@@ -207,6 +208,7 @@ int build_tiles(oecdg_handle *h) {
     }
     const bool use_tail = h->nbatch == 1 && plain > ncu && merged <= ncu && merged < plain;
     int ncol = 0;
+    h->maxpart = 0;
     for (int k = 0; k <= MAXK; ++k) {
         const int tbeg = (int)h->tiles_h.size();
         for (int b = 0; b < h->nbatch; ++b) {
@@ -218,6 +220,7 @@ int build_tiles(oecdg_handle *h) {
             I.ntiles = I.tail ? I.np / T : (I.nd + T - 1) / T;
             I.npart = I.ntiles + (I.tail ? 1 : 0);
             ncol += I.npart;
+            h->maxpart = std::max(h->maxpart, I.npart);
             for (int t = 0; t < I.ntiles; ++t) h->tiles_h.push_back(Tile1D{b, t * T});
         }
         if ((int)h->tiles_h.size() > tbeg) h->groups.push_back({k, tbeg, (int)h->tiles_h.size()});
@@ -300,7 +303,7 @@ int check_errors(oecdg_handle *h) {
 // per-instance fold of the statistics when the stage kernels read it; one
 // workgroup per tile.
 int stage_all(oecdg_handle *h, const StageArgs &a) {
-    if (a.red) HIPCHK(h, launch_fold_1d(a, h->flux, h->tile, h->stream));
+    if (a.red) HIPCHK(h, launch_fold_1d(a, h->flux, h->tile, h->maxpart, h->stream));
     for (auto &g : h->groups) {
         StageArgs b = a;
         b.tbeg = g.tbeg;
@@ -324,9 +327,12 @@ int stats_all(oecdg_handle *h, const StageArgs &a) {
     return OECDG_OK;
 }
 
-// (a.fin_host: the first launch also copies the records to the host)
+// (a.fin_host: the first launch also copies the records to the host; a.red: the
+// statistics are folded once instead of in every workgroup, which at 15626
+// tiles took 2327 us of a final launch)
 int final_all(oecdg_handle *h, const StageArgs &a) {
     bool first = true;
+    if (a.red) HIPCHK(h, launch_fold_final_1d(a, h->flux, h->tile, h->maxpart, h->stream));
     for (const auto &g : h->groups) {
         StageArgs b = a;
         b.tbeg = g.tbeg;
@@ -1032,6 +1038,7 @@ int oecdg_stage(oecdg_handle *h, int32_t stage, double dt, double tau_max, const
     Final f{0.0, dt, (long long)stage + 1};
     HIPCHK(h, hipMemcpyAsync(h->fin, &f, sizeof(Final), hipMemcpyHostToDevice, h->stream));
     a.ns = 3;
+    a.red = fold_on(h) ? h->red : nullptr;
     a.dstC = uC_out;
     a.dstD = uD_out;
     int rcf = final_all(h, a);

@@ -157,7 +157,10 @@ int adj_waves();
 hipError_t launch_init_1d(const StageArgs &a, int ninst, hipStream_t s);
 hipError_t launch_stats_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s);
 hipError_t launch_stage_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s);   // one workgroup per tile
-hipError_t launch_fold_1d(const StageArgs &a, int flux, int tile, hipStream_t s);
+// Statistics into a.red: of the state the stage (a.l, a.par) reads, and of the
+// state the final kernel damps.  maxpart: the most partial columns of an instance.
+hipError_t launch_fold_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s);
+hipError_t launch_fold_final_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s);
 hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s);
 hipError_t launch_persistent_1d(const StageArgs &a, int kmax, int flux, int tile, int grid,
                                 long long nsteps, hipStream_t s);

@@ -476,3 +476,29 @@ def test_every_tile_count_mod_8(ntiles):
     rC, rD, rt, rn = ora.run1d(prob, uC, uD, nsteps=4, cfl=0.15)
     assert n == rn == 4 and t == pytest.approx(rt, rel=1e-14)
     assert _rel(gC, gD, rC, rD) <= RUN_TOL
+
+
+@pytest.mark.parametrize("tile,n", [(32, 32 * 256 - 1), (32, 32 * 257 - 1), (32, 32 * 1024), (64, 64 * 384 - 2),
+                                    (64, 64 * 385 - 1), (128, 128 * 641 - 1)])
+@pytest.mark.parametrize("euler", [True, False])
+def test_folded_rows_give_the_bits_of_the_in_kernel_reduction(tile, n, euler):
+    """The fold with a workgroup per row takes over beyond two tiles per thread
+    (256, 384, 640 tiles at tiles of 32, 64, 128): the same bits on both sides
+    of each line, in whole runs and (their final OE) in single stages."""
+    if euler:
+        prob, uC, uD = inputs.euler_riemann(n, 1, inputs.riemann_states(3))
+    else:
+        prob, uC, uD, _ = inputs.burgers_fourier(n, 2, seed=3)
+    outs = []
+    for fold in (1, 2):
+        print(f"[fold rows] tile={tile} n={n} euler={euler} fold={fold}", flush=True)
+        with OECDG(prob, 0.15) as s:
+            s.set_option(_lib.OPT_TILE, tile)
+            s.set_option(_lib.OPT_FOLD, fold)
+            a, b = to_device(uC), to_device(uD)
+            dt = s.dt(a, b)
+            one = s.stage(0, dt, dt, a, b)
+            t, ns = s.run(a, b, nsteps=5)
+            outs.append((a, b, one[0], one[1], t, ns))
+    for x, y in zip(*outs):
+        assert np.array_equal(x.cpu().numpy(), y.cpu().numpy()) if hasattr(x, "cpu") else x == y
