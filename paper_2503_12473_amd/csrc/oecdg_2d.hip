@@ -2,33 +2,25 @@
 // tensor-product Q^k Legendre modes or the total-degree P^k (k = 1, 2, 3),
 // linear advection or Euler.
 //
-// Per RK stage (eq:RKCDG) one tile kernel and one statistics kernel:
-//   k_reduce2d  one workgroup folds the per-tile partial statistics of the
-//               stage input into the global scalars: per mesh and component
-//               the domain average and sigma (Sec. 2.2), the largest x and y
-//               wave speeds, and at a step start tau and tau_max
-//               (tau_max = C_CFL / (beta_x/h_x + beta_y/h_y), Sec. 2.1);
+// Per RK stage (eq:RKCDG):
+//   k_reduce2d  folds the per-tile partial statistics of the stage input into
+//               the global scalars: per mesh and component the domain average
+//               and sigma (Sec. 2.2), the largest x and y wave speeds, and at a
+//               step start tau and tau_max (tau_max = C_CFL / (beta_x/h_x +
+//               beta_y/h_y), Sec. 2.1);
 //   k_stage2d   one workgroup per tile of TX x TY primal cells and the dual
-//               cells with the same indices.  It stages both meshes'
-//               pre-damping input with a one-cell halo in LDS, applies the
-//               OE step of the previous stage in place (OEstep2D solved
-//               exactly, delta_K^m from the edge integrals of Sec. 2.2),
-//               evaluates the operator of eq:2D_H on its cells, takes the
-//               RK combination (the c/d table of eq:RKCDG: SSP-RK3 by
-//               default, forward Euler, SSP-RK2 or classical RK4) and writes
-//               the undamped stage output;
-//   k_delta2d   the damping numerators and the tile's partial statistics of
-//               that output.
-// The same tile kernel, in other modes, damps a state without a stage (the
-// end of a run or of a single stage) or only computes statistics.
-//
-// Work split inside a tile: four lanes (a quad) per cell.  For the operator
-// lane t takes quadrant t (coupling and volume integrals against the one
-// overlapping cell of the other mesh) and edge t (half-edge flux integrals
-// on the other mesh's centre line); for the damping coefficients lane t takes
-// edge t.  The quad sums with order-fixed DPP exchanges.  Lanes run the same
-// instructions; what differs per lane (quadrant, edge direction) is chosen by
-// selects, so the quad never diverges.
+//               cells with the same indices, one thread per cell.  Its threads
+//               load the cells that the tile's operator reads, apply the OE
+//               step of the previous stage to them in registers (OEstep2D solved
+//               exactly, from the damping numerators of k_delta2d and sigma) and
+//               put them in LDS; each thread then evaluates the operator of
+//               eq:2D_H on its cell, takes the RK combination (the c/d table of
+//               eq:RKCDG: SSP-RK3 by default, forward Euler, SSP-RK2 or
+//               classical RK4) and writes the undamped stage output;
+//   k_delta2d   the damping numerators (the edge integrals of Sec. 2.2) and the
+//               tile's partial statistics of that output, one workgroup per
+//               tile and component.
+// k_damp2d damps a state without a stage (the end of a run or of a single stage).
 //
 // Layout (global): u[(((q*(k+1) + a)*(k+1) + b)*ny + iy)*nx + ix]; dual cell
 // (ix, iy) is centred on the lower-left vertex of primal cell (ix, iy), so
@@ -39,6 +31,7 @@
 #include "oecdg_tables.h"
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -46,6 +39,17 @@
 namespace oecdg {
 
 // ---------------------------------------------------------------- fluxes ---
+
+// 1/x from the hardware estimate and two Newton steps (within an ulp or so of
+// the correctly rounded quotient; the flux divisions do not need the full
+// IEEE division sequence).
+__device__ inline double rcp_nr(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    double e = fma(-x, r, 1.0);
+    r = fma(r, e, r);
+    e = fma(-x, r, 1.0);
+    return fma(r, e, r);
+}
 
 struct FPar2 {
     double a, b, gamma;      // advection velocity (a, b); ideal-gas gamma
@@ -55,8 +59,12 @@ template <int FLUX> struct Flux2D;
 
 template <> struct Flux2D<OECDG_FLUX_ADVECTION> {
     static constexpr int NC = 1;
-    // flux along direction dir (0 = x, 1 = y), selected per lane
-    __device__ static inline void f(int dir, const double *w, double *o, const FPar2 &p) {
+    __device__ static inline void both(const double *w, double *f1, double *f2, const FPar2 &p) {
+        f1[0] = p.a * w[0];
+        f2[0] = p.b * w[0];
+    }
+    // flux along direction dir (0 = x, 1 = y)
+    __device__ static inline void one(int dir, const double *w, double *o, const FPar2 &p) {
         o[0] = (dir ? p.b : p.a) * w[0];
     }
     __device__ static inline double speed(int dir, const double *, const FPar2 &p) { return fabs(dir ? p.b : p.a); }
@@ -65,11 +73,24 @@ template <> struct Flux2D<OECDG_FLUX_ADVECTION> {
 
 template <> struct Flux2D<OECDG_FLUX_EULER> {
     static constexpr int NC = 4;    // rho, rho u, rho v, E
-    __device__ static inline void f(int dir, const double *w, double *o, const FPar2 &p) {
-        const double ir = 1.0 / w[0];
+    __device__ static inline void both(const double *w, double *f1, double *f2, const FPar2 &p) {
+        const double ir = rcp_nr(w[0]);
         const double u = w[1] * ir, v = w[2] * ir;
         const double pr = (p.gamma - 1.0) * (w[3] - 0.5 * (w[1] * u + w[2] * v));
-        const double un = dir ? v : u;
+        const double H = w[3] + pr;
+        f1[0] = w[1];
+        f1[1] = w[1] * u + pr;
+        f1[2] = w[2] * u;
+        f1[3] = H * u;
+        f2[0] = w[2];
+        f2[1] = w[1] * v;
+        f2[2] = w[2] * v + pr;
+        f2[3] = H * v;
+    }
+    __device__ static inline void one(int dir, const double *w, double *o, const FPar2 &p) {
+        const double ir = rcp_nr(w[0]);
+        const double pr = (p.gamma - 1.0) * (w[3] - 0.5 * (w[1] * w[1] + w[2] * w[2]) * ir);
+        const double un = (dir ? w[2] : w[1]) * ir;
         o[0] = dir ? w[2] : w[1];
         o[1] = w[1] * un + (dir ? 0.0 : pr);
         o[2] = w[2] * un + (dir ? pr : 0.0);
@@ -100,6 +121,7 @@ struct Tab2 {
     double e0[K1][K1];            // [d][n]: P_n^(d)(0)
     double sp[NSP][K1];           // P_n at the sigma sample points (-1, half nodes, +1)
     double cdel[K1];              // (2m+1) / ((2K-1) m!)
+    double sh[2][K1][K1];         // [half][n][m]: P_n(x + 1) (half 0) or P_n(x - 1) (half 1) = sum_m sh P_m(x)
 };
 
 template <int K>
@@ -135,6 +157,16 @@ constexpr Tab2<K> make_tab2() {
         if (m > 1) fact *= m;
         t.cdel[m] = K > 0 ? (2.0 * m + 1.0) / ((2.0 * K - 1.0) * fact) : 0.0;
     }
+    for (int n = 0; n < K1; ++n) {
+        ct::Poly p = ct::shifted(ct::legpoly(n));                      // P_n(x - 1) in monomials
+        for (int m = n; m >= 0; --m) {                                 // highest power first: c_m / lead(P_m)
+            const ct::Poly l = ct::legpoly(m);
+            const ct::Rat c = ct::rmul(p.c[m], ct::rat(l.c[m].q, l.c[m].p));
+            for (int j = 0; j <= m; ++j) p.c[j] = ct::radd(p.c[j], ct::rmul(ct::rat(-c.p, c.q), l.c[j]));
+            t.sh[1][n][m] = (double)c.p / (double)c.q;
+            t.sh[0][n][m] = ((n + m) & 1) ? -t.sh[1][n][m] : t.sh[1][n][m];   // P_n(x+1) = (-1)^n P_n(-x-1)
+        }
+    }
     return t;
 }
 
@@ -143,6 +175,7 @@ constexpr Tab2<K> make_tab2() {
 // Global scalars of the current stage (written by k_reduce2d).
 struct Stats2 {
     double avg[2][4], sig[2][4];  // per mesh and component
+    double isig[2][4];            // 1 / sigma, 0 where sigma is 0 (the component takes no part in the damping)
     double bx, by;                // largest x / y wave speeds at cell averages (both meshes)
     double t;                     // start time of the current step
     double tau, tau_max;          // the current step
@@ -151,7 +184,7 @@ struct Stats2 {
     int done, pending, last, bad; // bad: no admissible time step
 };
 
-enum { M2_STAGE = 0, M2_FINAL = 1 };
+enum { M2_STAGE = 0, M2_ALWAYS = 1 };        // k_delta2d: skipped once the run is done, or not
 enum { R2_STEP = 0, R2_STAGE = 1, R2_FINAL = 2, R2_SINGLE = 3, R2_STATS = 4 };
 
 struct Stage2Args {
@@ -167,18 +200,9 @@ struct Stage2Args {
     double *AC, *AD;              // classical RK4: weighted sum of the damped inputs of stages 1 and 2
     const Stats2 *st;
     int *err;                     // [0] non-finite, [1] non-physical, [2] no admissible step
-    int l, mode, damp, write_u;
+    int l, mode, damp, write_u;   // mode: k_delta2d
     RKStage rs;                   // c/d coefficients of stage l of the RK method (eq:RKCDG)
 };
-
-// Stage output of eq:RKCDG from the damped input s0, its rate Lv and (l > 0)
-// the damped u^n un and the accumulated earlier stages acc (classical RK4):
-//   c_{l0} u^n [+ acc] + c_{ll} s0 + tau d_{ll} L(s0)
-__device__ inline double rk_out(const RKStage &rs, int l, double s0, double Lv, double tau, double un, double acc) {
-    const double v = fma(tau * rs.d, Lv, rs.cw * s0);
-    if (l == 0) return v;
-    return (rs.acc_read ? rs.cn * un + acc : rs.cn * un) + v;
-}
 
 struct Red2Args {
     const double *part;
@@ -195,28 +219,26 @@ __host__ __device__ constexpr int row2(int nc, int mesh, int q, int kind) { retu
 
 // ------------------------------------------------------------ helpers ---
 
-// Sum over the four lanes of a quad; every lane gets ((l0 + l1) + (l2 + l3)).
-__device__ inline double quad_sum(double v) {
-    v += dpp_all<0xB1>(v);          // quad_perm [1,0,3,2]
-    v += dpp_all<0x4E>(v);          // quad_perm [2,3,0,1]
-    return v;
+// Tile of a workgroup; a band of consecutive tiles per XCD (xcd_tile).
+__device__ inline int tile_of_block(int nt) { return xcd_tile(blockIdx.x, nt); }
+
+// sqrt(x), x >= 0, from the hardware estimate of 1/sqrt (relative error below
+// 2^-22), one Goldschmidt step and one correction by the residual x - g^2:
+// within an ulp of the correctly rounded root for x in [1e-290, 1e300]; below
+// that range the result is at most 1e-140 off, 0 gives 0.  The IEEE sequence
+// (range scaling, three steps, class checks) was 40 % of k_delta2d.
+__device__ inline double sqrt_nr(double x) {
+    const double r = __builtin_amdgcn_rsq(max_d(x, 1e-300));
+    const double h = 0.5 * r;
+    double g = x * r;
+    g = fma(g, fma(-h, g, 0.5), g);
+    return fma(fma(-g, g, x), h, g);
 }
 
-__device__ inline double quad_max(double v) {
-    v = fmax(v, dpp_all<0xB1>(v));
-    v = fmax(v, dpp_all<0x4E>(v));
-    return v;
-}
-
-// 1/x from the hardware estimate and two Newton steps (within an ulp or so of
-// the correctly rounded quotient; the flux divisions do not need the full
-// IEEE division sequence).
-__device__ inline double rcp_nr(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+// x with its sign bit flipped by mask (0 or 0x80000000).
+__device__ inline double flip_sign(double x, unsigned mask) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    return __builtin_bit_cast(double, b ^ ((unsigned long long)mask << 32));
 }
 
 __device__ inline int wrap_idx(int i, int n, bool small) {
@@ -224,425 +246,182 @@ __device__ inline int wrap_idx(int i, int n, bool small) {
     return i < 0 ? i + n : (i >= n ? i - n : i);
 }
 
-// (-1)^(n+d) P_n^(d)(1) = P_n^(d)(-1)
-__device__ inline double edge_val(double v1, int n, int d, int side) { return (side || !((n + d) & 1)) ? v1 : -v1; }
+// PK: the total-degree space P^K.  Modes with a + b > K are zero in every
+// state, so the unrolled loops skip them at compile time.
+template <int K, bool PK>
+__host__ __device__ constexpr bool kept(int a, int b) { return !PK || a + b <= K; }
+// Modes per component that are kept, and the place of mode (a, b) among them.
+template <int K, bool PK>
+__host__ __device__ constexpr int kept_modes() { return PK ? (K + 1) * (K + 2) / 2 : (K + 1) * (K + 1); }
+template <int K, bool PK>
+__host__ __device__ constexpr int kept_index(int a, int b) {
+    int n = 0;
+    for (int i = 0; i < a; ++i)
+        for (int j = 0; j <= K; ++j) n += kept<K, PK>(i, j);
+    for (int j = 0; j < b; ++j) n += kept<K, PK>(a, j);
+    return n;
+}
 
-// ---------------------------------------------------------- tile kernels ---
-
-// Tile of primal cells [i0, i0+TX) x [j0, j0+TY) and the dual cells with the
-// same indices; a band of consecutive tiles per XCD (xcd_tile).
-__device__ inline int tile_of_block(int nt) { return xcd_tile(blockIdx.x, nt); }
-
-// Both meshes' state of a tile with a one-cell halo into LDS:
-// tile[(mesh*NE + entry)*NCELL + ly*W + lx], global cell (i0-1+lx, j0-1+ly).
-// A thread keeps one cell of the tile (its wrapped global index computed
-// once) and walks the rows (mesh, entry) in steps of NT / NCELL, so that each
-// load costs a pointer select and one multiply-add.
-template <int NE, int TX, int TY, int NT>
-__device__ inline void stage_tile2d(double *tile, const double *inC, const double *inD, int i0, int j0, int nx,
-                                    int ny, long long plane) {
-    constexpr int W = TX + 2, H = TY + 2, NCELL = W * H, NROW = 2 * NE;
-    constexpr int RPT = NT / NCELL, NIT = (NROW + RPT - 1) / RPT;    // rows per pass, passes
-    static_assert(RPT >= 1, "one pass covers every cell of the tile");
-    const int tid = threadIdx.x;
-    if (tid >= RPT * NCELL) return;
-    const int cell = tid % NCELL, r0 = tid / NCELL;
-    const bool small = nx < W || ny < H;
-    const int gx = wrap_idx(i0 - 1 + cell % W, nx, small);
-    const int gy = wrap_idx(j0 - 1 + cell / W, ny, small);
-    const long long g = (long long)gy * nx + gx;
-    double v[NIT];
+// Damping factors exp(-tau sum_{m<=j} delta^m), j = 1..K, of global cell g of a
+// mesh, delta^m = max_q N^m_q / sigma_q (isig: 1 / sigma_q, 0 where sigma_q is 0).
+template <int K, int NC>
+__device__ inline void damp_factors(const double *__restrict__ N, long long plane, long long g,
+                                    const double *__restrict__ isig, double tau, double (&f)[K]) {
+    double nv[K + 1][NC];
 #pragma unroll
-    for (int i = 0; i < NIT; ++i) {
-        const int r = min(r0 + i * RPT, NROW - 1);                   // past the last row: a valid duplicate
-        v[i] = (r < NE ? inC + r * plane : inD + (r - NE) * plane)[g];
-    }
+    for (int m = 0; m <= K; ++m)
 #pragma unroll
-    for (int i = 0; i < NIT; ++i) {
-        const int r = r0 + i * RPT;
-        if (r < NROW) tile[r * NCELL + cell] = v[i];
+        for (int q = 0; q < NC; ++q) nv[m][q] = N[(m * NC + q) * plane + g];
+    double S = 0.0;
+#pragma unroll
+    for (int m = 0; m <= K; ++m) {
+        double dm = nv[m][0] * isig[0];
+#pragma unroll
+        for (int q = 1; q < NC; ++q) dm = max_d(dm, nv[m][q] * isig[q]);
+        S += dm;
+        if (m >= 1) f[m - 1] = exp(-tau * S);
     }
 }
 
-// Stage kernel: OE step of the previous stage on the staged input (from the
-// damping numerators of k_delta2d and sigma), then the operator of eq:2D_H
-// and the RK combination on the owned cells (stage mode), or only the
-// damped owned cells (final mode).
-// PK: the total-degree space P^K.  Modes with a + b > K are zero in every
-// state, so the unrolled loops skip them at compile time (kept()).
-template <int K, bool PK>
-__device__ constexpr bool kept(int a, int b) { return !PK || a + b <= K; }
+// ----------------------------------------------------------- stage kernel ---
 
-template <int K, int FLUX, int TX, int TY, bool PK>
-__global__ __launch_bounds__(8 * TX * TY) void k_stage2d(Stage2Args a) {
-    using F = Flux2D<FLUX>;
-    constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NE = NC * K1 * K1;
-    constexpr int W = TX + 2, H = TY + 2, NCELL = W * H, NT = 8 * TX * TY;
-    constexpr int ND1 = (TX + 1) * (TY + 1), NDAMP = 2 * ND1;
+// Cells of a tile that its operator reads, per mesh: (TX+1) x (TY+1), primal
+// i0-1 .. i0+TX-1, dual i0 .. i0+TX (rows likewise).  In these indices an owned
+// cell of either mesh at (s, r) overlaps the other mesh's cells s..s+1, r..r+1.
+template <int TX, int TY>
+struct Halo2 {
+    static constexpr int W = TX + 1, H = TY + 1, N = W * H;
+};
+
+// Table entries of Gauss node p of the upper half, for a loop over the nodes.
+template <int K>
+struct NodeTab {
+    double w, nb[K + 1], p[K + 1], dp[K + 1];    // weight; P_n of the overlapping cell; P_n and P_n' of the own cell
+};
+template <int K>
+struct NodeTabs {
+    NodeTab<K> t[K + 1];
+};
+template <int K>
+constexpr NodeTabs<K> make_node_tabs() {
     constexpr Tab2<K> tb = make_tab2<K>();
-    static_assert(NT % WAVE == 0 && NT <= 1024 && NDAMP <= NT, "one damped cell per thread");
-    __shared__ double tile[2 * NE * NCELL];      // [mesh][entry][cell]
-    __shared__ double fac[2 * K * NCELL];        // [mesh][j-1][cell]: exp(-tau sum_{m<=j} delta^m)
-
-    const int tid = threadIdx.x, lane4 = tid & 3;
-    const int nt = a.ntx * a.nty, tileid = tile_of_block(nt);
-    const int i0 = (tileid % a.ntx) * TX, j0 = (tileid / a.ntx) * TY;
-    const Stats2 *st = a.st;
-    if (a.mode == M2_STAGE && st->done) return;
-
-    // damping factors of the damped set (owned cells and one ring): one
-    // thread per cell, delta^m = max_q N^m_q / sigma_q
-    double fj[K];
-    int fcell = -1, fmesh = 0;
-    if (a.damp && tid < NDAMP) {
-        fmesh = tid / ND1;
-        const int rr = tid % ND1;
-        const int lx = rr % (TX + 1) + fmesh, ly = rr / (TX + 1) + fmesh;
-        fcell = ly * W + lx;
-        const bool small = a.nx < W || a.ny < H;
-        const int gx = wrap_idx(i0 - 1 + lx, a.nx, small), gy = wrap_idx(j0 - 1 + ly, a.ny, small);
-        const double *N = fmesh == 0 ? a.numC : a.numD;
-        const long long g = (long long)gy * a.nx + gx;
-        double nv[K1][NC];
-#pragma unroll
-        for (int m = 0; m < K1; ++m)
-#pragma unroll
-            for (int q = 0; q < NC; ++q) nv[m][q] = N[(m * NC + q) * a.plane + g];
-        const double tau = st->tau_damp;
-        double S = 0.0;
-#pragma unroll
-        for (int m = 0; m < K1; ++m) {
-            double dm = 0.0;
-#pragma unroll
-            for (int q = 0; q < NC; ++q) {
-                const double sg = st->sig[fmesh][q];
-                dm = fmax(dm, sg != 0.0 ? nv[m][q] / sg : 0.0);
-            }
-            S += dm;
-            if (m >= 1) fj[m - 1] = exp(-tau * S);
+    NodeTabs<K> r{};
+    for (int p = 0; p <= K; ++p) {
+        r.t[p].w = tb.w[p];
+        for (int n = 0; n <= K; ++n) {
+            r.t[p].nb[n] = tb.nb[0][1][p][n];
+            r.t[p].p[n] = tb.own[0][1][p][n];
+            r.t[p].dp[n] = tb.own[1][1][p][n];
         }
     }
-    stage_tile2d<NE, TX, TY, NT>(tile, a.inC, a.inD, i0, j0, a.nx, a.ny, a.plane);
-    if (a.damp) {
-        if (fcell >= 0) {
-#pragma unroll
-            for (int j = 0; j < K; ++j) fac[(fmesh * K + j) * NCELL + fcell] = fj[j];
-        }
-        __syncthreads();
-        // mode (a, b) != (0, 0) takes the factor of total degree min(a + b, K);
-        // a thread keeps one damped cell and walks its entries
-        constexpr int RD = NT / NDAMP, NID = (NE + RD - 1) / RD;
-        static_assert(RD >= 1, "one pass covers every damped cell");
-        if (tid < RD * NDAMP) {
-            const int cs = tid % NDAMP, e0 = tid / NDAMP;
-            const int mesh = cs / ND1, rr = cs % ND1;
-            const int cell = (rr / (TX + 1) + mesh) * W + rr % (TX + 1) + mesh;
-            double f[K];
-#pragma unroll
-            for (int j = 0; j < K; ++j) f[j] = fac[(mesh * K + j) * NCELL + cell];
-#pragma unroll
-            for (int i = 0; i < NID; ++i) {
-                const int ent = e0 + i * RD;
-                const int ab = ent % (K1 * K1), deg = ab / K1 + ab % K1;
-                if (ent < NE && deg > 0) tile[(mesh * NE + ent) * NCELL + cell] *= f[(deg < K ? deg : K) - 1];
-            }
-        }
-    }
-    __syncthreads();
+    return r;
+}
+template <int K>
+__constant__ constexpr NodeTabs<K> node_tabs = make_node_tabs<K>();
+template <int K>
+__device__ inline NodeTab<K> node_tab(int p) { return node_tabs<K>.t[p]; }
 
-    // ---- owned cells: quad lanes per cell
-    const int cs = tid >> 2;
-    const int mesh = cs / (TX * TY), rr = cs % (TX * TY);
-    const int lx = rr % TX + 1, ly = rr / TX + 1;
-    const int cell = ly * W + lx;
-    const int gx = i0 + lx - 1, gy = j0 + ly - 1;
-    const bool valid = gx < a.nx && gy < a.ny;
-    const long long gofs = (long long)gy * a.nx + gx;
-    const double *town = tile + mesh * NE * NCELL;
-
-    if (a.mode == M2_FINAL) {
-        double *dst = mesh == 0 ? a.outC : a.outD;
-        if (valid)
-            for (int e = lane4; e < NE; e += 4) dst[e * a.plane + gofs] = town[e * NCELL + cell];
-        return;
-    }
-    if (a.write_u && valid) {
-        double *UM = mesh == 0 ? a.UC : a.UD;
-        for (int e = lane4; e < NE; e += 4) UM[e * a.plane + gofs] = town[e * NCELL + cell];
-    }
-    const double *toth = tile + (1 - mesh) * NE * NCELL;
-    const double tau = st->tau, itm = 1.0 / st->tau_max;
-    const double hx = a.hx, hy = a.hy;
-    const double *UM = mesh == 0 ? a.UC : a.UD;
-    double *OM = mesh == 0 ? a.outC : a.outD;
-    double *AM = mesh == 0 ? a.AC : a.AD;
-    bool finite = true;
-    if constexpr (NC == 4) {
-        // lane q accumulates component q over all quadrants and edges; the
-        // quad shares the point values of w so every lane can form its flux
-        const int q = lane4;
-        double Rq[K1][K1];
-#pragma unroll
-        for (int i = 0; i < K1; ++i)
-#pragma unroll
-            for (int j = 0; j < K1; ++j) Rq[i][j] = 0.0;
-        const double gm1 = a.fp.gamma - 1.0;
-        // coupling and volume, quadrant (sx, sy)
+// Quadrant loop and edges of eq:2D_H for one owned cell: R[q][a][b] = the
+// integral of the rate against P_a P_b (own-cell part of the coupling left to
+// the caller), from the damped cells of the other mesh in LDS (oth, [entry][cell]).
 //
-        // Quadrant (sx, sy) is evaluated in its mirror image on the upper
-        // right quadrant: with P_n(-x) = (-1)^n P_n(x) and the symmetric Gauss
-        // rule, mirroring a direction flips the sign of the odd modes of the
-        // overlapping cell and of the odd test functions (the even ones for a
-        // derivative, and the flux along that direction), so every quadrant
-        // uses the same compile-time tables.
-#pragma unroll 1
-        for (int qd = 0; qd < 4; ++qd) {
-            const int sx = qd & 1, sy = qd >> 1;
-            const double sgx = sx ? 1.0 : -1.0, sgy = sy ? 1.0 : -1.0;
-            const int oc = (ly + sy - mesh) * W + (lx + sx - mesh);
-            double d[K1][K1];
+// A quadrant (sx, sy) is evaluated in its mirror image on the upper right one.
+// With P_n(-x) = (-1)^n P_n(x) and the symmetric Gauss rule, mirroring x turns a
+// mode a into (-1)^a times itself and the x momentum into its negative, and the
+// mirrored state obeys the same equations; so all quadrants use the same
+// compile-time tables, and only signs of the loaded modes (flip_sign) and, where
+// the quadrant loop crosses an axis, of the sums R change.
+template <int K, int FLUX, int TX, int TY, bool PK>
+__device__ inline void operator2d(const Stage2Args &a, const double *oth, int s, int r, double itm,
+                                  double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
+    using F = Flux2D<FLUX>;
+    constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NM = kept_modes<K, PK>();
+    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N;
+    constexpr Tab2<K> tb = make_tab2<K>();
+    const double hx = a.hx, hy = a.hy;
+    const double sxx = 2.0 / hx, syy = 2.0 / hy, area = hx * hy / 16.0;
 #pragma unroll
-            for (int c = 0; c < K1; ++c)
-#pragma unroll
-                for (int e = 0; e < K1; ++e) {
-                    if (!kept<K, PK>(c, e)) {
-                        d[c][e] = 0.0;
-                        continue;
-                    }
-                    const double x = toth[((q * K1 + c) * K1 + e) * NCELL + oc];
-                    const double xs = (c & 1) ? sgx * x : x;
-                    d[c][e] = (e & 1) ? sgy * xs : xs;
-                }
-#pragma unroll
-            for (int p = 0; p < Q; ++p) {
-                double cx[K1];
-#pragma unroll
-                for (int e = 0; e < K1; ++e) {
-                    double t = 0.0;
-#pragma unroll
-                    for (int c = 0; c < K1; ++c)
-                        if (kept<K, PK>(c, e)) t += d[c][e] * tb.nb[0][1][p][c];
-                    cx[e] = t;
-                }
-                double A[K1], B[K1];
-#pragma unroll
-                for (int j = 0; j < K1; ++j) A[j] = B[j] = 0.0;
-#pragma unroll
-                for (int g = 0; g < Q; ++g) {
-                    double wq = 0.0;
-#pragma unroll
-                    for (int e = 0; e < K1; ++e) wq += cx[e] * tb.nb[0][1][g][e];
-                    const double w0 = dpp_all<0x00>(wq), w1 = dpp_all<0x55>(wq);
-                    const double w2 = dpp_all<0xAA>(wq), w3 = dpp_all<0xFF>(wq);
-                    const double ir = rcp_nr(w0), u = w1 * ir, v = w2 * ir;
-                    const double pr = gm1 * (w3 - 0.5 * (w1 * u + w2 * v));
-                    const double base = q == 3 ? w3 + pr : wq;
-                    const double f1 = base * u + (q == 1 ? pr : 0.0);
-                    const double f2 = sgy * (base * v + (q == 2 ? pr : 0.0));
-#pragma unroll
-                    for (int j = 0; j < K1; ++j) {
-                        A[j] += tb.w[g] * (wq * itm * tb.own[0][1][g][j] + (2.0 / hy) * f2 * tb.own[1][1][g][j]);
-                        B[j] += tb.w[g] * f1 * tb.own[0][1][g][j];
-                    }
-                }
-                double Ax[K1], Bx[K1];
-#pragma unroll
-                for (int j = 0; j < K1; ++j) {
-                    if (j & 1) A[j] *= sgy, B[j] *= sgy;
-                    Ax[j] = sgx * A[j];
-                    Bx[j] = sgx * B[j];
-                }
-                const double wp = hx * hy / 16.0 * tb.w[p];
-#pragma unroll
-                for (int i = 0; i < K1; ++i)
-#pragma unroll
-                    for (int j = 0; j < K1; ++j)
-                        if (kept<K, PK>(i, j))
-                            Rq[i][j] += wp * (tb.own[0][1][p][i] * ((i & 1) ? Ax[j] : A[j]) +
-                                              (2.0 / hx) * tb.own[1][1][p][i] * ((i & 1) ? B[j] : Bx[j]));
-            }
-        }
-        // edges: (dir, side) = W, E (f_1 on vertical centre lines), S, N (f_2)
-#pragma unroll 1
-        for (int ed = 0; ed < 4; ++ed) {
-            const int dir = ed >> 1, side = ed & 1;
-            const double ht = dir ? hx : hy, sgn = side ? 1.0 : -1.0;
-            double Y[K1];
-#pragma unroll
-            for (int t = 0; t < K1; ++t) Y[t] = 0.0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int ox = (dir ? lx + h : lx + side) - mesh, oy = (dir ? ly + side : ly + h) - mesh;
-                const int oc = oy * W + ox;
-                double r[K1];
-#pragma unroll
-                for (int t = 0; t < K1; ++t) {
-                    double sum = 0.0;
-#pragma unroll
-                    for (int n = 0; n < K1; ++n) {
-                        if (!kept<K, PK>(t, n)) continue;
-                        const int ent = dir ? (q * K1 + t) * K1 + n : (q * K1 + n) * K1 + t;
-                        sum += toth[ent * NCELL + oc] * tb.e0[0][n];
-                    }
-                    r[t] = sum;
-                }
-#pragma unroll
-                for (int g = 0; g < Q; ++g) {
-                    double wq = 0.0;
-#pragma unroll
-                    for (int t = 0; t < K1; ++t) wq += r[t] * tb.nb[0][h][g][t];
-                    const double w0 = dpp_all<0x00>(wq), w1 = dpp_all<0x55>(wq);
-                    const double w2 = dpp_all<0xAA>(wq), w3 = dpp_all<0xFF>(wq);
-                    const double ir = rcp_nr(w0), un = (dir ? w2 : w1) * ir;
-                    const double pr = gm1 * (w3 - 0.5 * (w1 * w1 + w2 * w2) * ir);
-                    const double base = q == 3 ? w3 + pr : wq;
-                    const double fn = base * un + (q == 1 + dir ? pr : 0.0);
-#pragma unroll
-                    for (int t = 0; t < K1; ++t) Y[t] += tb.w[g] * fn * tb.own[0][h][g][t];
-                }
-            }
-#pragma unroll
-            for (int n = 0; n < K1; ++n)
-#pragma unroll
-                for (int t = 0; t < K1; ++t) {
-                    if (!kept<K, PK>(n, t)) continue;
-                    const double x = sgn * 0.25 * ht * edge_val(1.0, n, 0, side) * Y[t];
-                    if (dir) Rq[t][n] -= x;
-                    else Rq[n][t] -= x;
-                }
-        }
-        // own part of the coupling, mass inverse, RK combination
+    for (int q = 0; q < NC; ++q)
 #pragma unroll
         for (int i = 0; i < K1; ++i)
 #pragma unroll
-            for (int j = 0; j < K1; ++j) {
-                const int e = (q * K1 + i) * K1 + j;
-                const double mass = hx * hy / ((2.0 * i + 1.0) * (2.0 * j + 1.0));
-                const double s0 = town[e * NCELL + cell];
-                const double Lv = (Rq[i][j] - mass * itm * s0) / mass;
-                const double un = (a.l > 0 && valid) ? UM[e * a.plane + gofs] : 0.0;
-                const double ac = (a.rs.acc_read && valid) ? AM[e * a.plane + gofs] : 0.0;
-                double o = rk_out(a.rs, a.l, s0, Lv, tau, un, ac);
-                if (!kept<K, PK>(i, j)) o = 0.0;
-                finite = finite && isfinite(o);
-                if (valid) {
-                    OM[e * a.plane + gofs] = o;
-                    if (a.rs.ca != 0.0) {     // classical RK4: this stage's damped input joins the sum
-                        double *p = AM + e * a.plane + gofs;
-                        *p = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, *p);
-                    }
-                }
-            }
-    } else {
-        // one component: lane t takes quadrant t and edge t, the quad sums
-        double R[NC][K1][K1];
+            for (int j = 0; j < K1; ++j) R[q][i][j] = 0.0;
+
+    // component q of a mirrored state changes sign along x (y) if it is the x (y) momentum
+    constexpr auto vecx = [](int q) { return NC == 4 && q == 1; };
+    constexpr auto vecy = [](int q) { return NC == 4 && q == 2; };
+    // quadrants (0,0), (1,0), (1,1), (0,1): one axis is crossed each time
+#pragma unroll 1
+    for (int qd = 0; qd < 4; ++qd) {
+        const int sy = qd >> 1, sx = (qd ^ sy) & 1;
+        const unsigned mx = sx ? 0u : 0x80000000u, my = sy ? 0u : 0x80000000u;
+        const unsigned cx = (qd & 1) ? 0x80000000u : 0u, cy = qd == 2 ? 0x80000000u : 0u;
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
             for (int i = 0; i < K1; ++i)
 #pragma unroll
-                for (int j = 0; j < K1; ++j) R[q][i][j] = 0.0;
-        {
-            const int sx = lane4 & 1, sy = lane4 >> 1;
-            const int oc = (ly + sy - mesh) * W + (lx + sx - mesh);
-#pragma unroll
-            for (int p = 0; p < Q; ++p) {
-                double cx[NC][K1];
-#pragma unroll
-                for (int q = 0; q < NC; ++q)
-#pragma unroll
-                    for (int d = 0; d < K1; ++d) {
-                        double sum = 0.0;
-#pragma unroll
-                        for (int c = 0; c < K1; ++c)
-                            if (kept<K, PK>(c, d))
-                                sum += toth[((q * K1 + c) * K1 + d) * NCELL + oc] *
-                                       (sx ? tb.nb[0][1][p][c] : tb.nb[0][0][p][c]);
-                        cx[q][d] = sum;
-                    }
-                double A[NC][K1], B[NC][K1];
-#pragma unroll
-                for (int q = 0; q < NC; ++q)
-#pragma unroll
-                    for (int j = 0; j < K1; ++j) A[q][j] = B[q][j] = 0.0;
-#pragma unroll
-                for (int g = 0; g < Q; ++g) {
-                    double w[NC], f1[NC], f2[NC];
-#pragma unroll
-                    for (int q = 0; q < NC; ++q) {
-                        double sum = 0.0;
-#pragma unroll
-                        for (int d = 0; d < K1; ++d) sum += cx[q][d] * (sy ? tb.nb[0][1][g][d] : tb.nb[0][0][g][d]);
-                        w[q] = sum;
-                    }
-                    F::f(0, w, f1, a.fp);
-                    F::f(1, w, f2, a.fp);
-#pragma unroll
-                    for (int q = 0; q < NC; ++q)
-#pragma unroll
-                        for (int j = 0; j < K1; ++j) {
-                            const double pb = sy ? tb.own[0][1][g][j] : tb.own[0][0][g][j];
-                            const double dpb = sy ? tb.own[1][1][g][j] : tb.own[1][0][g][j];
-                            A[q][j] += tb.w[g] * (w[q] * itm * pb + (2.0 / hy) * f2[q] * dpb);
-                            B[q][j] += tb.w[g] * f1[q] * pb;
-                        }
+                for (int j = 0; j < K1; ++j) {
+                    if (!kept<K, PK>(i, j)) continue;
+                    const bool ox = (i & 1) != (int)vecx(q), oy = (j & 1) != (int)vecy(q);
+                    if (ox || oy) R[q][i][j] = flip_sign(R[q][i][j], (ox ? cx : 0u) ^ (oy ? cy : 0u));
                 }
-                const double wp = hx * hy / 16.0 * tb.w[p];
-#pragma unroll
-                for (int i = 0; i < K1; ++i) {
-                    const double pa = sx ? tb.own[0][1][p][i] : tb.own[0][0][p][i];
-                    const double dpa = sx ? tb.own[1][1][p][i] : tb.own[1][0][p][i];
-#pragma unroll
-                    for (int q = 0; q < NC; ++q)
-#pragma unroll
-                        for (int j = 0; j < K1; ++j)
-                            if (kept<K, PK>(i, j)) R[q][i][j] += wp * (pa * A[q][j] + (2.0 / hx) * dpa * B[q][j]);
-                }
-            }
+        const double *o = oth + (r + sy) * W + s + sx;
+        FPar2 fp = a.fp;
+        if constexpr (NC == 1) {                 // advection: the mirrored velocity
+            fp.a = flip_sign(fp.a, mx);
+            fp.b = flip_sign(fp.b, my);
         }
-        {
-            const int dir = lane4 >> 1, side = lane4 & 1;
-            const double ht = dir ? hx : hy, sgn = side ? 1.0 : -1.0;
-            double Y[NC][K1];
+        // One node in x at a time, a loop at run time (its table entries are
+        // uniform loads): the modes are read from LDS again for each node, as
+        // keeping them beside R, A and B passes 256 registers.
+#pragma unroll 1
+        for (int p = 0; p < Q; ++p) {
+            const NodeTab<K> nt = node_tab<K>(p);
+            double cxv[NC][K1];                  // the line x = node p, modes in y
 #pragma unroll
             for (int q = 0; q < NC; ++q)
 #pragma unroll
-                for (int t = 0; t < K1; ++t) Y[q][t] = 0.0;
+                for (int e = 0; e < K1; ++e) {
+                    double t = 0.0;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int ox = (dir ? lx + h : lx + side) - mesh, oy = (dir ? ly + side : ly + h) - mesh;
-                const int oc = oy * W + ox;
-                double r[NC][K1];
+                    for (int c = 0; c < K1; ++c) {
+                        if (!kept<K, PK>(c, e)) continue;
+                        const double x = o[(q * NM + kept_index<K, PK>(c, e)) * NCELL];
+                        const bool ox = (c & 1) != (int)vecx(q);
+                        if (c == 0) t = ox ? flip_sign(x, mx) : x;
+                        else t = fma(x, flip_sign(nt.nb[c], ox ? mx : 0u), t);
+                    }
+                    cxv[q][e] = (e & 1) != (int)vecy(q) ? flip_sign(t, my) : t;
+                }
+            // A_j: coupling and y flux against P_j(y), P_j'(y); B_j: x flux against P_j(y)
+            double A[NC][K1], B[NC][K1];
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+#pragma unroll
+                for (int j = 0; j < K1; ++j) A[q][j] = B[q][j] = 0.0;
+#pragma unroll
+            for (int g = 0; g < Q; ++g) {
+                double w[NC], f1[NC], f2[NC];
+#pragma unroll
+                for (int q = 0; q < NC; ++q) {
+                    double t = cxv[q][0];
+#pragma unroll
+                    for (int e = 1; e < K1; ++e) t = fma(cxv[q][e], tb.nb[0][1][g][e], t);
+                    w[q] = t;
+                }
+                F::both(w, f1, f2, fp);
+                const double wc = tb.w[g] * itm, wd = tb.w[g] * syy;
 #pragma unroll
                 for (int q = 0; q < NC; ++q)
 #pragma unroll
-                    for (int t = 0; t < K1; ++t) {
-                        double sum = 0.0;
-#pragma unroll
-                        for (int n = 0; n < K1; ++n) {
-                            if (!kept<K, PK>(t, n)) continue;
-                            const int ent = dir ? (q * K1 + t) * K1 + n : (q * K1 + n) * K1 + t;
-                            sum += toth[ent * NCELL + oc] * tb.e0[0][n];
-                        }
-                        r[q][t] = sum;
+                    for (int j = 0; j < K1; ++j) {
+                        A[q][j] = fma(wc * tb.own[0][1][g][j], w[q], A[q][j]);
+                        if (j > 0) A[q][j] = fma(wd * tb.own[1][1][g][j], f2[q], A[q][j]);
+                        B[q][j] = fma(tb.w[g] * tb.own[0][1][g][j], f1[q], B[q][j]);
                     }
-#pragma unroll
-                for (int g = 0; g < Q; ++g) {
-                    double w[NC], fn[NC];
-#pragma unroll
-                    for (int q = 0; q < NC; ++q) {
-                        double sum = 0.0;
-#pragma unroll
-                        for (int t = 0; t < K1; ++t) sum += r[q][t] * tb.nb[0][h][g][t];
-                        w[q] = sum;
-                    }
-                    F::f(dir, w, fn, a.fp);
-#pragma unroll
-                    for (int q = 0; q < NC; ++q)
-#pragma unroll
-                        for (int t = 0; t < K1; ++t) Y[q][t] += tb.w[g] * fn[q] * tb.own[0][h][g][t];
-                }
             }
+            const double wp = area * nt.w, wpx = wp * sxx;
 #pragma unroll
             for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -650,246 +429,484 @@ __global__ __launch_bounds__(8 * TX * TY) void k_stage2d(Stage2Args a) {
 #pragma unroll
                     for (int j = 0; j < K1; ++j) {
                         if (!kept<K, PK>(i, j)) continue;
-                        const double x_ij = sgn * 0.25 * ht * edge_val(1.0, i, 0, side) * Y[q][j];
-                        const double x_ji = sgn * 0.25 * ht * edge_val(1.0, j, 0, side) * Y[q][i];
-                        R[q][i][j] -= dir ? x_ji : x_ij;
+                        R[q][i][j] = fma(wp * nt.p[i], A[q][j], R[q][i][j]);
+                        if (i > 0) R[q][i][j] = fma(wpx * nt.dp[i], B[q][j], R[q][i][j]);
                     }
         }
+    }
+    // the loop ends in the frame of quadrant (0, 1): back across x
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j)
+                if (kept<K, PK>(i, j) && (i & 1) != (int)vecx(q)) R[q][i][j] = -R[q][i][j];
+
+    // edges of direction dir: f_dir of the other mesh on its centre line along each
+    // half-edge, mirrored onto the upper half of the E (N) edge as above
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+        constexpr auto vecn = [](int dr, int q) { return NC == 4 && q == 1 + dr; };   // momentum normal to the edge
+        constexpr auto vect = [](int dr, int q) { return NC == 4 && q == 2 - dr; };   // and along it
+        const double ht = -0.25 * (dir ? hx : hy);
+#pragma unroll 1
+        for (int side = 0; side < 2; ++side) {
+            const unsigned fn = side ? 0u : 0x80000000u;
+            double Y[NC][K1];
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+#pragma unroll
+                for (int t = 0; t < K1; ++t) Y[q][t] = 0.0;
+#pragma unroll 1
+            for (int h = 0; h < 2; ++h) {
+                const unsigned ft = h ? 0u : 0x80000000u;
+                const double *o = oth + (dir ? (r + side) * W + s + h : (r + h) * W + s + side);
+                // into the frame of this half: the odd Y_t (and of the momentum along the edge the even ones)
+                const unsigned cross = h ? 0x80000000u : 0u;
+                double l[NC][K1];
+#pragma unroll
+                for (int q = 0; q < NC; ++q)
+#pragma unroll
+                    for (int t = 0; t < K1; ++t) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int n = 0; n < K1; n += 2) {             // P_n(0) = 0 for odd n
+                            if (!kept<K, PK>(t, n)) continue;
+                            const int m = dir ? kept_index<K, PK>(t, n) : kept_index<K, PK>(n, t);
+                            const double x = o[(q * NM + m) * NCELL];
+                            sum = n == 0 ? x : fma(x, tb.e0[0][n], sum);
+                        }
+                        const bool on = vecn(dir, q), ot = (t & 1) != (int)vect(dir, q);
+                        l[q][t] = (on || ot) ? flip_sign(sum, (on ? fn : 0u) ^ (ot ? ft : 0u)) : sum;
+                        if (ot) Y[q][t] = flip_sign(Y[q][t], cross);
+                    }
+                FPar2 fp = a.fp;
+                if constexpr (NC == 1) {
+                    fp.a = flip_sign(fp.a, fn);
+                    fp.b = flip_sign(fp.b, fn);
+                }
+#pragma unroll
+                for (int g = 0; g < Q; ++g) {
+                    double w[NC], f[NC];
+#pragma unroll
+                    for (int q = 0; q < NC; ++q) {
+                        double t = l[q][0];
+#pragma unroll
+                        for (int e = 1; e < K1; ++e) t = fma(l[q][e], tb.nb[0][1][g][e], t);
+                        w[q] = t;
+                    }
+                    F::one(dir, w, f, fp);
+#pragma unroll
+                    for (int q = 0; q < NC; ++q)
+#pragma unroll
+                        for (int t = 0; t < K1; ++t)
+                            Y[q][t] = fma(tb.w[g] * tb.own[0][1][g][t], f[q], Y[q][t]);
+                }
+            }
+            // P_n(1) = 1; out of the frame of the side
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+#pragma unroll
+                for (int t = 0; t < K1; ++t) {
+                    const double y = ht * Y[q][t], z = flip_sign(y, fn);
+#pragma unroll
+                    for (int n = 0; n < K1; ++n) {
+                        if (!kept<K, PK>(n, t)) continue;
+                        const double x = (n & 1) != (int)vecn(dir, q) ? z : y;
+                        if (dir) R[q][t][n] += x;
+                        else R[q][n][t] += x;
+                    }
+                }
+        }
+    }
+}
+
+// One RK stage (see the top of the file).
+template <int K, int FLUX, int TX, int TY, bool PK>
+__global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
+    using F = Flux2D<FLUX>;
+    constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>(), NE = NC * NM;
+    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, NT = 2 * TX * TY;
+    static_assert((TX * TY) % WAVE == 0, "a wave holds cells of one mesh");
+    __shared__ double tile[2 * NE * NCELL];      // [mesh][entry][cell], damped
+
+    const int tid = threadIdx.x;
+    const int tileid = tile_of_block(a.ntx * a.nty);
+    const int i0 = (tileid % a.ntx) * TX, j0 = (tileid / a.ntx) * TY;
+    const Stats2 *st = a.st;
+    if (st->done) return;
+
+    // the tile's cells into LDS, damped on the way; a thread takes a cell of
+    // either mesh with all its entries
+    const bool small = a.nx <= TX || a.ny <= TY;
+#pragma unroll 1
+    for (int c = tid; c < 2 * NCELL; c += NT) {
+        const int mesh = c >= NCELL, cell = c - mesh * NCELL;
+        const int gx = wrap_idx(i0 - 1 + mesh + cell % W, a.nx, small);
+        const int gy = wrap_idx(j0 - 1 + mesh + cell / W, a.ny, small);
+        const long long g = (long long)gy * a.nx + gx;
+        const double *in = (mesh ? a.inD : a.inC) + g;
+        double v[NE];
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j)
+                    if (kept<K, PK>(i, j))
+                        v[q * NM + kept_index<K, PK>(i, j)] = in[((q * K1 + i) * K1 + j) * a.plane];
+        if (a.damp) {
+            double f[K];
+            damp_factors<K, NC>(mesh ? a.numD : a.numC, a.plane, g, st->isig[mesh], st->tau_damp, f);
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+#pragma unroll
+                for (int i = 0; i < K1; ++i)
+#pragma unroll
+                    for (int j = 0; j < K1; ++j)
+                        if (kept<K, PK>(i, j) && i + j > 0)
+                            v[q * NM + kept_index<K, PK>(i, j)] *= f[(i + j < K ? i + j : K) - 1];
+        }
+        double *o = tile + mesh * NE * NCELL + cell;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) o[e * NCELL] = v[e];
+    }
+    __syncthreads();
+
+    // owned cells: the first half of the threads primal, the second dual
+    const int mesh = tid >= TX * TY, rr = tid - mesh * TX * TY;
+    const int s = rr % TX, r = rr / TX;
+    const int gx = i0 + s, gy = j0 + r;
+    const bool valid = gx < a.nx && gy < a.ny;
+    const long long gofs = valid ? (long long)gy * a.nx + gx : 0;
+    const double *own = tile + mesh * NE * NCELL + (r + 1 - mesh) * W + s + 1 - mesh;
+    const double itm = 1.0 / st->tau_max, tau = st->tau;
+    double R[NC][K1][K1];
+    operator2d<K, FLUX, TX, TY, PK>(a, tile + (1 - mesh) * NE * NCELL, s, r, itm, R);
+
+    // own part of the coupling, mass inverse, RK combination
+    double *UM = (mesh ? a.UD : a.UC) + gofs, *OM = (mesh ? a.outD : a.outC) + gofs, *AM = (mesh ? a.AD : a.AC) + gofs;
+    if (!valid) return;
+    double base[NC][K1][K1];                     // c_{l0} u^n [+ the accumulated earlier stages]
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j) base[q][i][j] = 0.0;
+    if (a.l > 0) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j)
+                    if (kept<K, PK>(i, j)) base[q][i][j] = a.rs.cn * UM[(long long)((q * K1 + i) * K1 + j) * a.plane];
+    }
+    if (a.rs.acc_read) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j)
+                    if (kept<K, PK>(i, j)) base[q][i][j] += AM[(long long)((q * K1 + i) * K1 + j) * a.plane];
+    }
+    const double im = 1.0 / (a.hx * a.hy), td = tau * a.rs.d;
+    double bad = 0.0;                            // 0 times every output: 0, or NaN if one is not finite
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j) {
+                const long long e = (long long)((q * K1 + i) * K1 + j) * a.plane;
+                if (!kept<K, PK>(i, j)) {
+                    OM[e] = 0.0;
+                    continue;
+                }
+                const double s0 = own[(q * NM + kept_index<K, PK>(i, j)) * NCELL];
+                const double Lv = fma(R[q][i][j], (2.0 * i + 1.0) * (2.0 * j + 1.0) * im, -itm * s0);
+                const double o = base[q][i][j] + fma(td, Lv, a.rs.cw * s0);
+                bad = fma(o, 0.0, bad);
+                OM[e] = o;
+            }
+    if (!(bad == 0.0)) a.err[0] = 1;
+    // damped input: u^n of the step, and classical RK4's sum of the stages that its last one needs
+    if (a.write_u || a.rs.ca != 0.0) {
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
             for (int i = 0; i < K1; ++i)
 #pragma unroll
                 for (int j = 0; j < K1; ++j) {
-                    const int e = (q * K1 + i) * K1 + j;
-                    if (!kept<K, PK>(i, j)) {
-                        if ((e & 3) == lane4 && valid) OM[e * a.plane + gofs] = 0.0;
-                        continue;
-                    }
-                    const double mass = hx * hy / ((2.0 * i + 1.0) * (2.0 * j + 1.0));
-                    const double s0 = town[e * NCELL + cell];
-                    const double Lv = (quad_sum(R[q][i][j]) - mass * itm * s0) / mass;
-                    if ((e & 3) == lane4) {
-                        const double un = (a.l > 0 && valid) ? UM[e * a.plane + gofs] : 0.0;
-                        const double ac = (a.rs.acc_read && valid) ? AM[e * a.plane + gofs] : 0.0;
-                        const double o = rk_out(a.rs, a.l, s0, Lv, tau, un, ac);
-                        finite = finite && isfinite(o);
-                        if (valid) {
-                            OM[e * a.plane + gofs] = o;
-                            if (a.rs.ca != 0.0) {
-                                double *p = AM + e * a.plane + gofs;
-                                *p = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, *p);
-                            }
-                        }
-                    }
+                    const long long e = (long long)((q * K1 + i) * K1 + j) * a.plane;
+                    const double s0 = kept<K, PK>(i, j) ? own[(q * NM + kept_index<K, PK>(i, j)) * NCELL] : 0.0;
+                    if (a.write_u) UM[e] = s0;
+                    else AM[e] = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, AM[e]);
                 }
     }
-    if (valid && !finite) a.err[0] = 1;
 }
 
-// Damping numerators and statistics of a state (the undamped output of a
-// stage, or initial data): per owned cell and component q
-//   N^m_q = sum_{e in {W,E,S,N}} beta_{e,K} (2m+1) h_e^(m-1) / ((2k-1) m!)
-//           (1/|e|) int_e ( sum_{alpha1+alpha2=m} (d^alpha (u_K - w)_q)^2 )^(1/2) ds
-// (delta^m_K = max_q N^m_q / sigma_q once sigma is known, Sec. 2.2), with one
-// lane per edge; then the tile's partial statistics (sums of averages, sample
-// max / min per component, largest wave speeds) with one lane per component.
-template <int K, int FLUX, int TX, int TY, bool PK>
-// Two workgroups per CU (4 waves per SIMD; the LDS tile allows no more): the
-// register cap spills a few values to scratch, which costs less than running
-// one workgroup per CU (6.86 -> 6.32 ms per step on the 1024^2 workload).  At
-// k = 3 the LDS tile allows 2 waves per SIMD only, so no register cap.
-__global__ __launch_bounds__(8 * TX * TY, K == 3 ? 2 : 4) void k_delta2d(Stage2Args a) {
-    using F = Flux2D<FLUX>;
-    constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NE = NC * K1 * K1, NSP = 2 * K + 4;
-    constexpr int W = TX + 2, NCELL = W * (TY + 2), NT = 8 * TX * TY, NW = NT / WAVE;
-    constexpr int NR = nrow2<NC>();
-    constexpr Tab2<K> tb = make_tab2<K>();
-    __shared__ double tile[2 * NE * NCELL];
-    __shared__ double red[NW * NR];
-
-    const int tid = threadIdx.x, lane4 = tid & 3;
-    const int nt = a.ntx * a.nty, tileid = tile_of_block(nt);
-    const int i0 = (tileid % a.ntx) * TX, j0 = (tileid / a.ntx) * TY;
-    if (a.mode == M2_STAGE && a.st->done) return;
-    stage_tile2d<NE, TX, TY, NT>(tile, a.inC, a.inD, i0, j0, a.nx, a.ny, a.plane);
-    __syncthreads();
-
-    const int cs = tid >> 2;
-    const int mesh = cs / (TX * TY), rr = cs % (TX * TY);
-    const int lx = rr % TX + 1, ly = rr / TX + 1;
-    const int cell = ly * W + lx;
-    const int gx = i0 + lx - 1, gy = j0 + ly - 1;
-    const bool valid = gx < a.nx && gy < a.ny;
-    const long long gofs = (long long)gy * a.nx + gx;
-    const double *own = tile + mesh * NE * NCELL, *oth = tile + (1 - mesh) * NE * NCELL;
-    double ubar[NC];
+// A state damped without a stage (damp off: copied), one thread per cell; grid.y is the mesh.
+template <int K, int FLUX, bool PK>
+__global__ __launch_bounds__(256) void k_damp2d(Stage2Args a) {
+    constexpr int NC = Flux2D<FLUX>::NC, K1 = K + 1;
+    const long long g = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int mesh = blockIdx.y;
+    if (g >= a.plane) return;
+    double f[K];
 #pragma unroll
-    for (int q = 0; q < NC; ++q) ubar[q] = own[(q * K1 * K1) * NCELL + cell];
-
-    if (a.numC) {
-        const int dir = lane4 >> 1, side = lane4 & 1;
-        const double hn = dir ? a.hy : a.hx, ht = dir ? a.hx : a.hy;
-        const double beta = F::speed(dir, ubar, a.fp);
-        int oc[2];
+    for (int j = 0; j < K; ++j) f[j] = 1.0;
+    if (a.damp) damp_factors<K, NC>(mesh ? a.numD : a.numC, a.plane, g, a.st->isig[mesh], a.st->tau_damp, f);
+    const double *in = (mesh ? a.inD : a.inC) + g;
+    double *out = (mesh ? a.outD : a.outC) + g;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int ox = (dir ? lx + h : lx + side) - mesh, oy = (dir ? ly + side : ly + h) - mesh;
-            oc[h] = oy * W + ox;
-        }
-        double* N = mesh == 0 ? a.numC : a.numD;
-#pragma unroll 1
-        for (int q = 0; q < NC; ++q) {
-            // traces restricted to the edge, by normal derivative order: own at
-            // the edge (normal coordinate +-1); the other mesh at its centre
-            // line (0), one half-edge at a time (each mean[m] still sums the
-            // half-edges in order)
-            double ro[K1][K1];
-#pragma unroll
-            for (int dn = 0; dn < K1; ++dn)
-#pragma unroll
-                for (int t = 0; t < K1; ++t) {
-                    double so = 0.0;
-#pragma unroll
-                    for (int n = 0; n < K1; ++n) {
-                        if (!kept<K, PK>(t, n)) continue;
-                        const int ent = dir ? (q * K1 + t) * K1 + n : (q * K1 + n) * K1 + t;
-                        so += own[ent * NCELL + cell] * edge_val(tb.e1[dn][n], n, dn, side);
-                    }
-                    ro[dn][t] = so;
-                }
-            double mean[K1];
-#pragma unroll
-            for (int m = 0; m < K1; ++m) mean[m] = 0.0;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                double rt[K1][K1];
-#pragma unroll
-                for (int dn = 0; dn < K1; ++dn)
-#pragma unroll
-                    for (int t = 0; t < K1; ++t) {
-                        double sh = 0.0;
-#pragma unroll
-                        for (int n = 0; n < K1; ++n) {
-                            if (!kept<K, PK>(t, n)) continue;
-                            const int ent = dir ? (q * K1 + t) * K1 + n : (q * K1 + n) * K1 + t;
-                            sh += oth[ent * NCELL + oc[h]] * tb.e0[dn][n];
-                        }
-                        rt[dn][t] = sh;
-                    }
-#pragma unroll
-                for (int m = 0; m < K1; ++m)
-#pragma unroll
-                    for (int g = 0; g < Q; ++g) {
-                        double ss = 0.0;
-                        double scn = 1.0;
-#pragma unroll
-                        for (int dn = 0; dn <= m; ++dn) {
-                            const int dt = m - dn;
-                            double sct = scn;
-#pragma unroll
-                            for (int j = 0; j < dt; ++j) sct *= 2.0 / ht;
-                            double vo = 0.0, vt = 0.0;
-#pragma unroll
-                            for (int t = 0; t < K1; ++t) {
-                                vo += ro[dn][t] * tb.own[dt][h][g][t];
-                                vt += rt[dn][t] * tb.nb[dt][h][g][t];
-                            }
-                            const double d = sct * (vo - vt);
-                            ss = m == 0 ? fabs(d) : ss + d * d;
-                            scn *= 2.0 / hn;
-                        }
-                        mean[m] += 0.25 * tb.w[g] * (m == 0 ? ss : sqrt(ss));   // |d| = (d^2)^(1/2) for m = 0
-                    }
-            }
-#pragma unroll
-            for (int m = 0; m < K1; ++m) {
-                double hm = 1.0;                          // h_e^(m-1)
-                if (m == 0) hm = 1.0 / hn;
-#pragma unroll
-                for (int j = 1; j < m; ++j) hm *= hn;
-                const double num = quad_sum(beta * tb.cdel[m] * hm * mean[m]);
-                if (valid && lane4 == (m & 3)) N[(m * NC + q) * a.plane + gofs] = num;
-            }
-        }
-    }
-
-    // ---- partial statistics: component cq of this cell, all sample rows for
-    // a component lane (Euler), rows i = lane (mod 4) for one component
-    // (a wave holds cells of one mesh only, so a thread keeps the rows of its
-    // own mesh, (sum, max, min) per component, and the two wave-speed rows)
-    constexpr bool LANE_COMP = NC == 4;
-    constexpr int NM = 3 * NC;
-    const int cq = LANE_COMP ? lane4 : 0;
-    double vals[NM + 2];
-#pragma unroll
-    for (int j = 0; j < NM + 2; ++j) vals[j] = j < NM ? stat_identity(j % 3) : -INFINITY;
-    if (valid) {
-        double cst[K1][K1];
+    for (int q = 0; q < NC; ++q)
 #pragma unroll
         for (int i = 0; i < K1; ++i)
 #pragma unroll
-            for (int j = 0; j < K1; ++j) cst[i][j] = kept<K, PK>(i, j) ? own[((cq * K1 + i) * K1 + j) * NCELL + cell] : 0.0;
-        double mx = -INFINITY, mn = INFINITY;
-#pragma unroll
-        for (int i = 0; i < NSP; ++i) {
-            if (!LANE_COMP && (i & 3) != lane4) continue;
-            double rb[K1];
-#pragma unroll
             for (int j = 0; j < K1; ++j) {
-                double sum = 0.0;
+                const long long e = (long long)((q * K1 + i) * K1 + j) * a.plane;
+                if (!kept<K, PK>(i, j)) out[e] = 0.0;
+                else out[e] = i + j == 0 ? in[e] : in[e] * f[(i + j < K ? i + j : K) - 1];
+            }
+}
+
+// ----------------------------------------------------------- delta kernel ---
+
+// Damping numerators and statistics of a state (the undamped output of a
+// stage, or initial data): per cell and component q
+//   N^m_q = sum_{e in {W,E,S,N}} beta_{e,K} (2m+1) h_e^(m-1) / ((2k-1) m!)
+//           (1/|e|) int_e ( sum_{alpha1+alpha2=m} (d^alpha (u_K - w)_q)^2 )^(1/2) ds
+// (delta^m_K = max_q N^m_q / sigma_q once sigma is known, Sec. 2.2).
+//
+// The two edges of a direction share beta, so N^m_q = beta_x X^m_q + beta_y Y^m_q
+// with X, Y formed from component q alone: a workgroup takes one component of
+// one tile, and its threads one cell of each mesh in turn.  Along a half-edge
+// the traces of both meshes are polynomials in the edge coordinate; the other
+// mesh's is brought to the cell's own coordinate (tb.sh), and the derivatives of
+// the difference are evaluated from its coefficients.
+
+// sqrt terms of one direction: acc[m] = sum over both edges, both halves and the
+// Gauss nodes of w_g (sum_alpha (d^alpha (u_K - w))^2)^(1/2).  u[n][t]: the own
+// cell's modes, normal to the edge and along it; oth: the other mesh's, of which
+// cell oc0 + side sn + half st (strides sn, st) overlaps each half-edge, mode
+// (n, t) at n mn + t mt.
+// Each half-edge is evaluated as its mirror image on the upper half of the E (N)
+// edge: the odd modes of a mirrored direction change sign in both cells, the
+// derivatives at most their sign, so one loop body with compile-time tables
+// serves all four.
+template <int K, bool PK, bool DIRY, int NCELL>
+__device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double *oth, int sn, int st, double hn,
+                                  double ht, double (&acc)[K + 1]) {
+    constexpr int K1 = K + 1, Q = K + 1;
+    constexpr Tab2<K> tb = make_tab2<K>();
+    double scn[K1], sct[K1];                     // (2/h_n)^d, (2/h_t)^d
+    scn[0] = sct[0] = 1.0;
 #pragma unroll
-                for (int c = 0; c < K1; ++c)
-                    if (kept<K, PK>(c, j)) sum += cst[c][j] * tb.sp[i][c];
-                rb[j] = sum;
+    for (int d = 1; d < K1; ++d) {
+        scn[d] = scn[d - 1] * (2.0 / hn);
+        sct[d] = sct[d - 1] * (2.0 / ht);
+    }
+#pragma unroll
+    for (int m = 0; m < K1; ++m) acc[m] = 0.0;
+#pragma unroll 1
+    for (int e = 0; e < 4; ++e) {
+        const int side = e >> 1, half = e & 1;
+        const unsigned fn = side ? 0u : 0x80000000u, ft = half ? 0u : 0x80000000u;
+        const double *o = oth + side * sn + half * st;
+        double D[K1][K1];                        // [normal derivative][mode along the edge], own coordinate
+#pragma unroll
+        for (int dn = 0; dn < K1; ++dn) {
+            double r[K1];                        // derivative dn of the other trace at its centre line
+#pragma unroll
+            for (int t = 0; t < K1; ++t) {
+                r[t] = 0.0;
+#pragma unroll
+                for (int n = dn; n < K1; n += 2)
+                    if (kept<K, PK>(n, t)) {
+                        const double w = o[(DIRY ? kept_index<K, PK>(t, n) : kept_index<K, PK>(n, t)) * NCELL];
+                        r[t] = n == 0 ? w : fma(w, tb.e0[dn][n], r[t]);
+                    }
+                // (the modes n of one derivative have one parity)
+                if ((dn & 1) || (t & 1)) r[t] = flip_sign(r[t], ((dn & 1) ? fn : 0u) ^ ((t & 1) ? ft : 0u));
             }
 #pragma unroll
-            for (int jj = 0; jj < NSP; ++jj) {
-                double v = 0.0;
+            for (int t = 0; t < K1; ++t) {
+                double x = 0.0;                  // own trace at the edge
 #pragma unroll
-                for (int j = 0; j < K1; ++j) v += rb[j] * tb.sp[jj][j];
-                mx = fmax(mx, v);
-                mn = fmin(mn, v);
+                for (int n = dn; n < K1; ++n) {
+                    if (!kept<K, PK>(n, t)) continue;
+                    const bool fl = (n & 1) || (t & 1);
+                    const double v = fl ? flip_sign(u[n][t], ((n & 1) ? fn : 0u) ^ ((t & 1) ? ft : 0u)) : u[n][t];
+                    x = n == 0 ? v : fma(v, tb.e1[dn][n], x);
+                }
+#pragma unroll
+                for (int j = t; j < K1; ++j) x = j == t ? x - r[j] : fma(r[j], -tb.sh[1][j][t], x);
+                D[dn][t] = dn == 0 ? x : x * scn[dn];
             }
         }
 #pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            if (q != cq) continue;
-            vals[3 * q] = (LANE_COMP || lane4 == 0) ? cst[0][0] : 0.0;
-            vals[3 * q + 1] = mx;
-            vals[3 * q + 2] = mn;
-        }
-        if (lane4 == 0) {
-            double ub[NC];                // the cell averages again from LDS: not kept live across the numerators
+        for (int g = 0; g < Q; ++g)
 #pragma unroll
-            for (int q = 0; q < NC; ++q) ub[q] = own[(q * K1 * K1) * NCELL + cell];
-            vals[NM] = F::speed(0, ub, a.fp);
-            vals[NM + 1] = F::speed(1, ub, a.fp);
-            if (!F::physical(ub, a.fp)) a.err[1] = 1;
+            for (int m = 0; m < K1; ++m) {
+                double ss = 0.0;
+#pragma unroll
+                for (int dn = 0; dn <= m; ++dn) {
+                    const int dt = m - dn;
+                    double v = 0.0;
+#pragma unroll
+                    for (int t = dt; t < K1; ++t)
+                        if (tb.own[dt][1][g][t] != 0.0)
+                            v = tb.own[dt][1][g][t] == 1.0 ? v + D[dn][t] : fma(D[dn][t], tb.own[dt][1][g][t], v);
+                    if (dt > 0) v *= sct[dt];
+                    ss = m == 0 ? fabs(v) : (dn == 0 ? v * v : fma(v, v, ss));
+                }
+                acc[m] = fma(tb.w[g], m == 0 ? ss : sqrt_nr(ss), acc[m]);   // |d| = (d^2)^(1/2) for m = 0
+            }
+    }
+}
+
+// Largest and smallest value of one component over S x S, S = {+-1, +-nodes}:
+// in each direction the even and the odd part at +x give the values at +x and
+// -x, whose larger and smaller are even +- |odd|.
+template <int K, bool PK>
+__device__ inline void sample_extrema(const double (&u)[K + 1][K + 1], double &mx, double &mn) {
+    constexpr int K1 = K + 1, NSP = 2 * K + 4;
+    constexpr Tab2<K> tb = make_tab2<K>();
+    mx = -INFINITY;
+    mn = INFINITY;
+#pragma unroll
+    for (int i = K + 2; i < NSP; ++i) {          // the sample points x > 0
+        double rp[K1], rm[K1];
+#pragma unroll
+        for (int j = 0; j < K1; ++j) {
+            double ev = 0.0, od = 0.0;
+#pragma unroll
+            for (int c = 0; c < K1; ++c) {
+                if (!kept<K, PK>(c, j)) continue;
+                if (c & 1) od = fma(u[c][j], tb.sp[i][c], od);
+                else ev = c == 0 ? u[c][j] : fma(u[c][j], tb.sp[i][c], ev);
+            }
+            rp[j] = ev + od;
+            rm[j] = ev - od;
+        }
+#pragma unroll
+        for (int y = K + 2; y < NSP; ++y)
+#pragma unroll
+            for (int sg = 0; sg < 2; ++sg) {
+                const double *b = sg ? rm : rp;
+                double ev = b[0], od = 0.0;
+#pragma unroll
+                for (int j = 1; j < K1; ++j) {
+                    if (j & 1) od = fma(b[j], tb.sp[y][j], od);
+                    else ev = fma(b[j], tb.sp[y][j], ev);
+                }
+                mx = max_d(mx, ev + fabs(od));
+                mn = min_d(mn, ev - fabs(od));
+            }
+    }
+}
+
+template <int K, int FLUX, int TX, int TY, bool PK>
+__global__ __launch_bounds__(TX * TY) void k_delta2d(Stage2Args a) {
+    using F = Flux2D<FLUX>;
+    constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>();
+    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, NT = TX * TY, NW = NT / WAVE;
+    constexpr Tab2<K> tb = make_tab2<K>();
+    __shared__ double tile[2 * NM * NCELL];      // [mesh][mode][cell] of component q
+    __shared__ double red[NW * 8];
+
+    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
+    const int nt = a.ntx * a.nty, tileid = tile_of_block(nt), q = blockIdx.y;
+    const int i0 = (tileid % a.ntx) * TX, j0 = (tileid / a.ntx) * TY;
+    if (a.mode == M2_STAGE && a.st->done) return;
+    const bool small = a.nx <= TX || a.ny <= TY;
+#pragma unroll
+    for (int c0 = 0; c0 < 2 * NCELL; c0 += NT) {
+        const int c = c0 + tid;
+        if (c < 2 * NCELL) {
+            const int mesh = c >= NCELL, cell = c - mesh * NCELL;
+            const int gx = wrap_idx(i0 - 1 + mesh + cell % W, a.nx, small);
+            const int gy = wrap_idx(j0 - 1 + mesh + cell / W, a.ny, small);
+            const double *in = (mesh ? a.inD : a.inC) + (long long)q * K1 * K1 * a.plane + (long long)gy * a.nx + gx;
+            double *o = tile + mesh * NM * NCELL + cell;
+#pragma unroll
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j)
+                    if (kept<K, PK>(i, j)) o[kept_index<K, PK>(i, j) * NCELL] = in[(i * K1 + j) * a.plane];
         }
     }
-    {
-        // the wave's own mesh rows and the wave speeds are reduced; the other
-        // mesh's rows are the identity in this wave
-        static_assert((4 * TX * TY) % WAVE == 0, "waves do not straddle the meshes");
-        const int lane = tid % WAVE, wave = tid / WAVE, wmesh = wave / (4 * TX * TY / WAVE);
+    const int s = tid % TX, r = tid / TX, gx = i0 + s, gy = j0 + r;
+    const bool valid = gx < a.nx && gy < a.ny;
+    const long long gofs = valid ? (long long)gy * a.nx + gx : 0;
+    __syncthreads();
+
+    double sx = -INFINITY, sy = -INFINITY;       // the wave speeds of both cells
+#pragma unroll 1
+    for (int mesh = 0; mesh < 2; ++mesh) {
+        const double *own = tile + mesh * NM * NCELL + (r + 1 - mesh) * W + s + 1 - mesh;
+        const double *oth = tile + (1 - mesh) * NM * NCELL + r * W + s;
+        const double *bar = (mesh ? a.inD : a.inC) + gofs;
+        double ub[NC];                           // the cell averages of every component
 #pragma unroll
-        for (int j = 0; j < NM + 2; ++j) {
-            const int kind = j < NM ? j % 3 : 1;
-            const double v = wave_reduce(kind, vals[j]);
-            if (lane == WAVE - 1) red[wave * NR + (j < NM ? row2(NC, wmesh, j / 3, j % 3) : 2 * NM + (j - NM))] = v;
-        }
+        for (int c = 0; c < NC; ++c) ub[c] = bar[(long long)c * K1 * K1 * a.plane];
+        double u[K1][K1];
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j) u[i][j] = kept<K, PK>(i, j) ? own[kept_index<K, PK>(i, j) * NCELL] : 0.0;
+        double mx, mn;
+        sample_extrema<K, PK>(u, mx, mn);
+        const double v0 = wave_reduce(0, valid ? u[0][0] : 0.0);
+        const double v1 = wave_reduce(1, valid ? mx : -INFINITY);
+        const double v2 = wave_reduce(2, valid ? mn : INFINITY);
         if (lane == WAVE - 1) {
+            red[wave * 8 + 3 * mesh] = v0;
+            red[wave * 8 + 3 * mesh + 1] = v1;
+            red[wave * 8 + 3 * mesh + 2] = v2;
+        }
+        const double bx = F::speed(0, ub, a.fp), by = F::speed(1, ub, a.fp);
+        if (q == 0 && valid) {
+            sx = max_d(sx, bx);
+            sy = max_d(sy, by);
+            if (!F::physical(ub, a.fp)) a.err[1] = 1;
+        }
+        if (a.numC) {
+            double X[K1], Y[K1], ut[K1][K1];
+            edge_norms<K, PK, false, NCELL>(u, oth, 1, W, a.hx, a.hy, X);
 #pragma unroll
-            for (int j = 0; j < NM; ++j) red[wave * NR + row2(NC, 1 - wmesh, j / 3, j % 3)] = stat_identity(j % 3);
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j) ut[i][j] = u[j][i];
+            edge_norms<K, PK, true, NCELL>(ut, oth, W, 1, a.hy, a.hx, Y);
+            double *N = (mesh ? a.numD : a.numC) + gofs;
+            double hxm = 1.0 / a.hx, hym = 1.0 / a.hy;         // h_e^(m-1)
+#pragma unroll
+            for (int m = 0; m < K1; ++m) {
+                if (valid) N[(long long)(m * NC + q) * a.plane] = 0.25 * tb.cdel[m] * (bx * hxm * X[m] + by * hym * Y[m]);
+                hxm = m == 0 ? 1.0 : hxm * a.hx;
+                hym = m == 0 ? 1.0 : hym * a.hy;
+            }
         }
-        __syncthreads();
-        if (tid < NR) {
-            const int kind = tid < 2 * NC * 3 ? tid % 3 : 1;
-            double v = red[tid];
-            for (int w2 = 1; w2 < NW; ++w2) v = stat_op(kind, v, red[w2 * NR + tid]);
-            a.part[(long long)tid * nt + tileid] = v;
-        }
+    }
+    // the tile's partials of component q (q = 0: the wave speeds too)
+    sx = wave_reduce(1, sx);
+    sy = wave_reduce(1, sy);
+    if (lane == WAVE - 1) {
+        red[wave * 8 + 6] = sx;
+        red[wave * 8 + 7] = sy;
+    }
+    __syncthreads();
+    if (tid < 6 || (tid < 8 && q == 0)) {
+        const int kind = tid < 6 ? tid % 3 : 1;
+        double v = red[tid];
+        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, red[w * 8 + tid]);
+        const int row = tid < 6 ? row2(NC, tid / 3, q, tid % 3) : 2 * NC * 3 + tid - 6;
+        a.part[(long long)row * nt + tileid] = v;
     }
 }
 
@@ -959,7 +976,9 @@ __global__ __launch_bounds__(RED2_NT) void k_reduce2d(Red2Args r) {
         for (int q = 0; q < NC; ++q) {
             const double avg = tot[row2(NC, mesh, q, 0)] / (double)r.ncell;
             st->avg[mesh][q] = avg;
-            st->sig[mesh][q] = fmax(tot[row2(NC, mesh, q, 1)] - avg, avg - tot[row2(NC, mesh, q, 2)]);
+            const double sig = fmax(tot[row2(NC, mesh, q, 1)] - avg, avg - tot[row2(NC, mesh, q, 2)]);
+            st->sig[mesh][q] = sig;
+            st->isig[mesh][q] = sig != 0.0 ? fmin(1.0 / sig, DBL_MAX) : 0.0;
         }
     st->bx = tot[2 * NC * 3];
     st->by = tot[2 * NC * 3 + 1];
@@ -1012,39 +1031,50 @@ __global__ __launch_bounds__(RED2_NT) void k_reduce2d(Red2Args r) {
 
 namespace {
 
-// Tiles of 8 x 8 primal cells for k = 1, 2; 4 x 4 for k = 3, whose 64
-// coefficients per cell would make an 8 x 8 tile with its halo overflow LDS.
-template <int K> struct Tile2 {
-    static constexpr int TX = K == 3 ? 4 : 8, TY = K == 3 ? 4 : 8;
+// Tiles in primal cells.  k_stage2d: 16 x 4 (full 128-byte lines of a row, 49 KB
+// of LDS for Euler at k = 2: three workgroups per CU), 8 x 8 would read 64-byte
+// pieces; one thread per cell.  k_delta2d: 16 x 16 of one component.
+template <int K, int FLUX> struct Tile2 {
+    static constexpr int TX = 16, TY = 4, DX = 16, DY = 16;
 };
-constexpr int tile2(int k) { return k == 3 ? 4 : 8; }
 
+// which: 0 stage, 1 delta, 2 damp
 template <int K, int FLUX, bool PK>
-void *stage2d_fn(bool delta) {
-    constexpr int TX = Tile2<K>::TX, TY = Tile2<K>::TY;
-    return delta ? (void *)k_delta2d<K, FLUX, TX, TY, PK> : (void *)k_stage2d<K, FLUX, TX, TY, PK>;
+void *kernel2d_fn(int which) {
+    using T = Tile2<K, FLUX>;
+    if (which == 1) return (void *)k_delta2d<K, FLUX, T::DX, T::DY, PK>;
+    if (which == 2) return (void *)k_damp2d<K, FLUX, PK>;
+    return (void *)k_stage2d<K, FLUX, T::TX, T::TY, PK>;
 }
 
 template <int K>
-void *pick2_k(int flux, bool pk, bool delta) {
-    if (flux == OECDG_FLUX_EULER) return pk ? stage2d_fn<K, OECDG_FLUX_EULER, true>(delta) : stage2d_fn<K, OECDG_FLUX_EULER, false>(delta);
-    return pk ? stage2d_fn<K, OECDG_FLUX_ADVECTION, true>(delta) : stage2d_fn<K, OECDG_FLUX_ADVECTION, false>(delta);
+void *pick2_k(int flux, bool pk, int which) {
+    if (flux == OECDG_FLUX_EULER)
+        return pk ? kernel2d_fn<K, OECDG_FLUX_EULER, true>(which) : kernel2d_fn<K, OECDG_FLUX_EULER, false>(which);
+    return pk ? kernel2d_fn<K, OECDG_FLUX_ADVECTION, true>(which) : kernel2d_fn<K, OECDG_FLUX_ADVECTION, false>(which);
 }
 
-void *pick2(int k, int flux, bool pk, bool delta) {
+void *pick2(int k, int flux, bool pk, int which) {
     switch (k) {
-    case 1: return pick2_k<1>(flux, pk, delta);
-    case 2: return pick2_k<2>(flux, pk, delta);
-    default: return pick2_k<3>(flux, pk, delta);
+    case 1: return pick2_k<1>(flux, pk, which);
+    case 2: return pick2_k<2>(flux, pk, which);
+    default: return pick2_k<3>(flux, pk, which);
     }
 }
+
+struct Tiles2 {
+    int tx, ty, dx, dy;
+};
+Tiles2 tiles2(int, int) { return {16, 4, 16, 16}; }
 
 struct Ext2D {
     int k, nc, flux, oe;
     int pk;                      // total-degree space P^k
-    int tx, ty;                  // primal cells per tile and direction
+    Tiles2 t;                    // primal cells per tile and direction
     int rk, ns;                  // RK method (rk_stage) and its stages per step
-    int nx, ny, ntx, nty, ntiles;
+    int nx, ny;
+    int ntx, nty;                // k_stage2d's tiles
+    int dtx, dty, ntiles;        // k_delta2d's tiles (columns of the partial statistics)
     double hx, hy, cfl;
     FPar2 fp;
     long long S1;                // doubles of one mesh
@@ -1069,18 +1099,26 @@ Ext2D *ext(oecdg_handle *h) { return static_cast<Ext2D *>(handle_ext2d(h)); }
         if (e_ != hipSuccess) return handle_fail((h), OECDG_EHIP, hipGetErrorString(e_));                     \
     } while (0)
 
-hipError_t launch_tile(void *fn, const Ext2D &x, const Stage2Args &a, hipStream_t s) {
-    Stage2Args copy = a;
-    void *args[] = {&copy};
-    return hipLaunchKernel(fn, dim3(x.ntiles), dim3(8 * x.tx * x.ty), args, 0, s);
-}
-
 hipError_t launch_stage2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
-    return launch_tile(pick2(x.k, x.flux, x.pk, false), x, a, s);
+    Stage2Args copy = a;
+    copy.ntx = x.ntx;
+    copy.nty = x.nty;
+    void *args[] = {&copy};
+    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 0), dim3(x.ntx * x.nty), dim3(2 * x.t.tx * x.t.ty), args, 0, s);
 }
 
 hipError_t launch_delta2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
-    return launch_tile(pick2(x.k, x.flux, x.pk, true), x, a, s);
+    Stage2Args copy = a;
+    copy.ntx = x.dtx;
+    copy.nty = x.dty;
+    void *args[] = {&copy};
+    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 1), dim3(x.ntiles, x.nc), dim3(x.t.dx * x.t.dy), args, 0, s);
+}
+
+hipError_t launch_damp2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
+    Stage2Args copy = a;
+    void *args[] = {&copy};
+    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 2), dim3((unsigned)((a.plane + 255) / 256), 2), dim3(256), args, 0, s);
 }
 
 // Fold r.part (per-tile partials) into the global scalars: first level into
@@ -1106,8 +1144,6 @@ Stage2Args stage_args(const Ext2D &x) {
     memset(&a, 0, sizeof(a));
     a.nx = x.nx;
     a.ny = x.ny;
-    a.ntx = x.ntx;
-    a.nty = x.nty;
     a.plane = (long long)x.nx * x.ny;
     a.hx = x.hx;
     a.hy = x.hy;
@@ -1184,12 +1220,14 @@ int create_2d(oecdg_handle *h, const oecdg_desc *d) {
     x->pk = d->space == 1;
     x->nx = (int)d->nx;
     x->ny = (int)d->ny;
-    x->tx = x->ty = tile2(x->k);
+    x->t = tiles2(x->k, x->flux);
     x->rk = d->rk == 0 ? 3 : d->rk;
     x->ns = rk_stages(x->rk);
-    x->ntx = (x->nx + x->tx - 1) / x->tx;
-    x->nty = (x->ny + x->ty - 1) / x->ty;
-    x->ntiles = x->ntx * x->nty;
+    x->ntx = (x->nx + x->t.tx - 1) / x->t.tx;
+    x->nty = (x->ny + x->t.ty - 1) / x->t.ty;
+    x->dtx = (x->nx + x->t.dx - 1) / x->t.dx;
+    x->dty = (x->ny + x->t.dy - 1) / x->t.dy;
+    x->ntiles = x->dtx * x->dty;
     x->hx = (d->xhi - d->xlo) / d->nx;
     x->hy = (d->yhi - d->ylo) / d->ny;
     x->cfl = d->cfl;
@@ -1240,7 +1278,7 @@ int dt_2d(oecdg_handle *h, const double *uC, const double *uD, double *dt_out) {
     hipStream_t s = handle_stream(h);
     int rc = reset2d(h, x);
     if (rc != OECDG_OK) return rc;
-    HIPCHK2(h, delta_of(x, uC, uD, 0, M2_FINAL, s));
+    HIPCHK2(h, delta_of(x, uC, uD, 0, M2_ALWAYS, s));
     HIPCHK2(h, launch_reduce2d(x, red_args(x, x.part[0], R2_STATS), s));
     HIPCHK2(h, hipMemcpyAsync(x.st_h, x.st, sizeof(Stats2), hipMemcpyDeviceToHost, s));
     HIPCHK2(h, hipStreamSynchronize(s));
@@ -1275,10 +1313,9 @@ int stage_2d(oecdg_handle *h, int stage, double dt, double tau_max, const double
     a.outC = x.B[0];
     a.outD = x.B[0] + x.S1;
     HIPCHK2(h, launch_stage2d(x, a, s));
-    HIPCHK2(h, delta_of(x, x.B[0], x.B[0] + x.S1, 0, M2_FINAL, s));
+    HIPCHK2(h, delta_of(x, x.B[0], x.B[0] + x.S1, 0, M2_ALWAYS, s));
     HIPCHK2(h, launch_reduce2d(x, red_args(x, x.part[0], R2_STAGE), s));
     Stage2Args f = stage_args(x);
-    f.mode = M2_FINAL;
     f.damp = x.oe && x.k > 0;
     f.inC = x.B[0];
     f.inD = x.B[0] + x.S1;
@@ -1286,7 +1323,7 @@ int stage_2d(oecdg_handle *h, int stage, double dt, double tau_max, const double
     f.numD = x.num[0] + x.SN;
     f.outC = uCo;
     f.outD = uDo;
-    HIPCHK2(h, launch_stage2d(x, f, s));
+    HIPCHK2(h, launch_damp2d(x, f, s));
     return check2d(h, x);
 }
 
@@ -1310,7 +1347,7 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
                                                       0, sizeof(double) * plane, s));
     }
     // statistics of the initial data (wave speeds for the first step) into part[0]
-    HIPCHK2(h, delta_of(x, x.B[0], x.B[0] + x.S1, 0, M2_FINAL, s));
+    HIPCHK2(h, delta_of(x, x.B[0], x.B[0] + x.S1, 0, M2_ALWAYS, s));
     const int chunk = 16;
     long long n = 0;
     while (nsteps < 0 || n < nsteps) {
@@ -1351,7 +1388,6 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
     r.t_end = t_end;
     HIPCHK2(h, launch_reduce2d(x, r, s));
     Stage2Args f = stage_args(x);
-    f.mode = M2_FINAL;
     f.damp = x.oe && x.k > 0 && N > 0;
     f.inC = x.B[fb];
     f.inD = x.B[fb] + x.S1;
@@ -1359,7 +1395,7 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
     f.numD = x.num[fb] + x.SN;
     f.outC = uC;
     f.outD = uD;
-    HIPCHK2(h, launch_stage2d(x, f, s));
+    HIPCHK2(h, launch_damp2d(x, f, s));
     HIPCHK2(h, hipMemcpyAsync(x.st_h, x.st, sizeof(Stats2), hipMemcpyDeviceToHost, s));
     rc = check2d(h, x);
     if (t_out) *t_out = x.st_h->t;

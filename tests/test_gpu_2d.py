@@ -178,3 +178,27 @@ def test_nonfinite_input_is_reported():
     with pytest.raises(_lib.OECDGError) as e:
         _gpu_run(prob, uC, uD, 0.3, nsteps=3)
     assert e.value.code == _lib.ENONFINITE
+
+
+@pytest.mark.parametrize("flux,k,space", [(FLUX_EULER, 1, 0), (FLUX_EULER, 2, 0), (FLUX_EULER, 2, 1), (FLUX_EULER, 3, 1),
+                                          (FLUX_ADVECTION, 2, 0), (FLUX_ADVECTION, 3, 1)])
+@pytest.mark.parametrize("nx,ny", [(16, 4), (17, 5), (15, 3), (2, 33), (33, 2), (31, 18)])
+def test_mesh_sizes_at_the_edges_of_the_tiles(nx, ny, flux, k, space):
+    """Meshes of one tile (16 x 4 of the stage kernel, 16 x 16 of the damping
+    numerators), one cell more and less, and thinner than a tile with its
+    halo, against the oracle."""
+    nc = 4 if flux == FLUX_EULER else 1
+    prob = Problem2D(k=k, nc=nc, flux=flux, nx=nx, ny=ny, xlo=0.0, xhi=1.2, ylo=0.0, yhi=0.7, a=1.0, b=-0.6, space=space)
+
+    def f(X, Y):
+        w = np.sin(2 * math.pi * X / 1.2) * np.cos(2 * math.pi * Y / 0.7)
+        rho = 1.0 + 0.3 * w + 0.1 * (np.mod(X, 1.2) > 0.5)
+        if nc == 1:
+            return rho[None]
+        u, v, p = 0.3 - 0.2 * w, 0.1 + 0.3 * w, 1.0 + 0.2 * (np.mod(Y, 0.7) > 0.3)
+        return np.stack([rho, rho * u, rho * v, p / 0.4 + 0.5 * rho * (u * u + v * v)])
+
+    uC, uD = inputs.project_2d(f, prob)
+    g, _, _ = _gpu_run(prob, uC, uD, 0.2, nsteps=3)
+    rC, rD, _, _ = ora.run2d(prob, uC, uD, nsteps=3, cfl=0.2)
+    assert _rel(g, (rC, rD)) <= TOL
