@@ -67,7 +67,10 @@ template <> struct Flux2D<OECDG_FLUX_ADVECTION> {
     __device__ static inline void one(int dir, const double *w, double *o, const FPar2 &p) {
         o[0] = (dir ? p.b : p.a) * w[0];
     }
-    __device__ static inline double speed(int dir, const double *, const FPar2 &p) { return fabs(dir ? p.b : p.a); }
+    __device__ static inline void speeds(const double *, double &x, double &y, const FPar2 &p) {
+        x = fabs(p.a);
+        y = fabs(p.b);
+    }
     __device__ static inline bool physical(const double *, const FPar2 &) { return true; }
 };
 
@@ -96,11 +99,14 @@ template <> struct Flux2D<OECDG_FLUX_EULER> {
         o[2] = w[2] * un + (dir ? pr : 0.0);
         o[3] = (w[3] + pr) * un;
     }
-    __device__ static inline double speed(int dir, const double *w, const FPar2 &p) {
+    // spectral radii of f_1' and f_2'
+    __device__ static inline void speeds(const double *w, double &x, double &y, const FPar2 &p) {
         const double ir = 1.0 / w[0];
         const double u = w[1] * ir, v = w[2] * ir;
         const double pr = (p.gamma - 1.0) * (w[3] - 0.5 * (w[1] * u + w[2] * v));
-        return fabs(dir ? v : u) + sqrt(p.gamma * pr * ir);
+        const double c = sqrt(p.gamma * pr * ir);
+        x = fabs(u) + c;
+        y = fabs(v) + c;
     }
     __device__ static inline bool physical(const double *w, const FPar2 &p) {
         if (!(w[0] > 0.0)) return false;
@@ -222,18 +228,23 @@ __host__ __device__ constexpr int row2(int nc, int mesh, int q, int kind) { retu
 // Tile of a workgroup; a band of consecutive tiles per XCD (xcd_tile).
 __device__ inline int tile_of_block(int nt) { return xcd_tile(blockIdx.x, nt); }
 
-// sqrt(x), x >= 0, from the hardware estimate of 1/sqrt (relative error below
-// 2^-22), one Goldschmidt step and one correction by the residual x - g^2:
-// within an ulp of the correctly rounded root for x in [1e-290, 1e300]; below
-// that range the result is at most 1e-140 off, 0 gives 0.  The IEEE sequence
-// (range scaling, three steps, class checks) was 40 % of k_delta2d.
+// sqrt(x) for x >= SQRT_TINY from the hardware estimate of 1/sqrt (relative
+// error below 2^-22), one Goldschmidt step and one correction by the residual
+// x - g^2: within an ulp of the correctly rounded root up to 1e300.  The IEEE
+// sequence (range scaling, three steps, class checks) was 40 % of k_delta2d.
+constexpr double SQRT_TINY = 1e-300;
 __device__ inline double sqrt_nr(double x) {
-    const double r = __builtin_amdgcn_rsq(max_d(x, 1e-300));
+    const double r = __builtin_amdgcn_rsq(x);
     const double h = 0.5 * r;
     double g = x * r;
     g = fma(g, fma(-h, g, 0.5), g);
     return fma(fma(-g, g, x), h, g);
 }
+
+// c x + y and c x for a constant c: no multiplication by 1 (the compiler may not
+// drop an addition of 0 or a product that it has to round).
+__device__ inline double mad_c(double c, double x, double y) { return c == 1.0 ? x + y : fma(c, x, y); }
+__device__ inline double mul_c(double c, double x) { return c == 1.0 ? x : c * x; }
 
 // x with its sign bit flipped by mask (0 or 0x80000000).
 __device__ inline double flip_sign(double x, unsigned mask) {
@@ -703,11 +714,14 @@ __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double 
                                   double ht, double (&acc)[K + 1]) {
     constexpr int K1 = K + 1, Q = K + 1;
     constexpr Tab2<K> tb = make_tab2<K>();
-    double scn[K1], sct[K1];                     // (2/h_n)^d, (2/h_t)^d
-    scn[0] = sct[0] = 1.0;
+    // Derivatives scaled by the tangential (2/h_t)^m of their order m: the factor
+    // leaves the root and is applied to the sum at the end, and a normal derivative
+    // brings (h_t/h_n) each.
+    double kap[K1], sct[K1];
+    kap[0] = sct[0] = 1.0;
 #pragma unroll
     for (int d = 1; d < K1; ++d) {
-        scn[d] = scn[d - 1] * (2.0 / hn);
+        kap[d] = kap[d - 1] * (ht / hn);
         sct[d] = sct[d - 1] * (2.0 / ht);
     }
 #pragma unroll
@@ -724,49 +738,58 @@ __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double 
 #pragma unroll
             for (int t = 0; t < K1; ++t) {
                 r[t] = 0.0;
+                if (!kept<K, PK>(dn, t)) continue;
 #pragma unroll
                 for (int n = dn; n < K1; n += 2)
                     if (kept<K, PK>(n, t)) {
                         const double w = o[(DIRY ? kept_index<K, PK>(t, n) : kept_index<K, PK>(n, t)) * NCELL];
-                        r[t] = n == 0 ? w : fma(w, tb.e0[dn][n], r[t]);
+                        r[t] = n == dn ? mul_c(tb.e0[dn][n], w) : mad_c(tb.e0[dn][n], w, r[t]);
                     }
                 // (the modes n of one derivative have one parity)
                 if ((dn & 1) || (t & 1)) r[t] = flip_sign(r[t], ((dn & 1) ? fn : 0u) ^ ((t & 1) ? ft : 0u));
             }
 #pragma unroll
             for (int t = 0; t < K1; ++t) {
+                D[dn][t] = 0.0;
+                if (!kept<K, PK>(dn, t)) continue;
                 double x = 0.0;                  // own trace at the edge
 #pragma unroll
                 for (int n = dn; n < K1; ++n) {
                     if (!kept<K, PK>(n, t)) continue;
                     const bool fl = (n & 1) || (t & 1);
                     const double v = fl ? flip_sign(u[n][t], ((n & 1) ? fn : 0u) ^ ((t & 1) ? ft : 0u)) : u[n][t];
-                    x = n == 0 ? v : fma(v, tb.e1[dn][n], x);
+                    x = n == dn ? mul_c(tb.e1[dn][n], v) : mad_c(tb.e1[dn][n], v, x);
                 }
 #pragma unroll
-                for (int j = t; j < K1; ++j) x = j == t ? x - r[j] : fma(r[j], -tb.sh[1][j][t], x);
-                D[dn][t] = dn == 0 ? x : x * scn[dn];
+                for (int j = t; j < K1; ++j)
+                    if (kept<K, PK>(dn, j)) x = j == t ? x - r[j] : fma(r[j], -tb.sh[1][j][t], x);
+                D[dn][t] = dn == 0 ? x : x * kap[dn];
             }
         }
 #pragma unroll
         for (int g = 0; g < Q; ++g)
 #pragma unroll
             for (int m = 0; m < K1; ++m) {
-                double ss = 0.0;
+                double ss = SQRT_TINY;
 #pragma unroll
                 for (int dn = 0; dn <= m; ++dn) {
                     const int dt = m - dn;
                     double v = 0.0;
+                    bool first = true;
 #pragma unroll
                     for (int t = dt; t < K1; ++t)
-                        if (tb.own[dt][1][g][t] != 0.0)
-                            v = tb.own[dt][1][g][t] == 1.0 ? v + D[dn][t] : fma(D[dn][t], tb.own[dt][1][g][t], v);
-                    if (dt > 0) v *= sct[dt];
-                    ss = m == 0 ? fabs(v) : (dn == 0 ? v * v : fma(v, v, ss));
+                        if (kept<K, PK>(dn, t) && tb.own[dt][1][g][t] != 0.0) {
+                            const double c = tb.own[dt][1][g][t];
+                            v = first ? mul_c(c, D[dn][t]) : mad_c(c, D[dn][t], v);
+                            first = false;
+                        }
+                    ss = m == 0 ? fabs(v) : fma(v, v, ss);
                 }
                 acc[m] = fma(tb.w[g], m == 0 ? ss : sqrt_nr(ss), acc[m]);   // |d| = (d^2)^(1/2) for m = 0
             }
     }
+#pragma unroll
+    for (int m = 1; m < K1; ++m) acc[m] *= sct[m];
 }
 
 // Largest and smallest value of one component over S x S, S = {+-1, +-nodes}:
@@ -869,7 +892,8 @@ __global__ __launch_bounds__(TX * TY) void k_delta2d(Stage2Args a) {
             red[wave * 8 + 3 * mesh + 1] = v1;
             red[wave * 8 + 3 * mesh + 2] = v2;
         }
-        const double bx = F::speed(0, ub, a.fp), by = F::speed(1, ub, a.fp);
+        double bx, by;
+        F::speeds(ub, bx, by, a.fp);
         if (q == 0 && valid) {
             sx = max_d(sx, bx);
             sy = max_d(sy, by);
