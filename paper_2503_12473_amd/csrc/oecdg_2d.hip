@@ -187,10 +187,11 @@ struct Stats2 {
     double tau, tau_max;          // the current step
     double tau_damp;              // tau of the OE step applied to the next tile kernel's input
     long long nexec;              // completed steps
-    int done, pending, last, bad; // bad: no admissible time step
+    int pending, last, bad;       // bad: no admissible time step
+    int done[2];                  // the run has ended, by the parity of the stage index: the reduction for the
+                                  // next stage writes its entry while k_delta2d of this one reads the other
 };
 
-enum { M2_STAGE = 0, M2_ALWAYS = 1 };        // k_delta2d: skipped once the run is done, or not
 enum { R2_STEP = 0, R2_STAGE = 1, R2_FINAL = 2, R2_SINGLE = 3, R2_STATS = 4 };
 
 struct Stage2Args {
@@ -201,27 +202,38 @@ struct Stage2Args {
     const double *inC, *inD;      // tile input (pre-damping, or damped when damp == 0)
     double *outC, *outD;          // stage output (undamped) or damped state (final mode)
     double *UC, *UD;              // damped u^n: written at stage 0 (write_u), read at stages 1, 2
-    double *part;                 // [row][tile] partial statistics (k_delta2d)
+    double *part;                 // partial statistics, one record (Rec2) per tile
     double *numC, *numD;          // damping numerators [m*NC + q][ny][nx]: written by k_delta2d, read by k_stage2d
     double *AC, *AD;              // classical RK4: weighted sum of the damped inputs of stages 1 and 2
     const Stats2 *st;
     int *err;                     // [0] non-finite, [1] non-physical, [2] no admissible step
-    int l, mode, damp, write_u;   // mode: k_delta2d
+    int l, gpar, damp, write_u;   // stage, parity of the stage index (st->done)
+    int nred;                     // k_delta2d: leading workgroups that reduce the statistics (reduce2d)
     RKStage rs;                   // c/d coefficients of stage l of the RK method (eq:RKCDG)
 };
 
+// Reduction of the partial records into the global scalars.
 struct Red2Args {
     const double *part;
-    int ntiles, mode;
+    int nrec, per, nb, mode;      // records, records per workgroup, workgroups
+    int gpar;                     // parity of the stage index that the result is for
     long long ncell;
     double t_end, dt_fixed, cfl, hx, hy;
     double tau_o, taumax_o;       // single-stage call
+    double *fold;                 // [nb][Rec2::N]
+    unsigned *count;              // workgroups that have written their record (0 between launches)
     Stats2 *st;
     int *err;
 };
 
-template <int NC> __host__ __device__ constexpr int nrow2() { return 2 * NC * 3 + 2; }
-__host__ __device__ constexpr int row2(int nc, int mesh, int q, int kind) { return (mesh * nc + q) * 3 + kind; }
+// A partial record: per mesh (sum of averages, max, min of the samples) of each
+// component, then the largest x and y wave speeds.
+template <int NC> struct Rec2 {
+    static constexpr int NM = 3 * NC + 2, N = 2 * NM;
+    static constexpr int G = NC == 4 ? 32 : 16;   // threads of a record (the first N of them hold a value)
+    static_assert(N <= G, "a thread per value");
+    __device__ static inline int kind(int j) { return j % NM < 3 * NC ? j % NM % 3 : 1; }
+};
 
 // ------------------------------------------------------------ helpers ---
 
@@ -295,6 +307,76 @@ __device__ inline void damp_factors(const double *__restrict__ N, long long plan
 }
 
 // ----------------------------------------------------------- stage kernel ---
+
+// Largest and smallest value of one component over S x S, S = {+-1, +-nodes}:
+// in each direction the even and the odd part at +x give the values at +x and
+// -x, whose larger and smaller are even +- |odd|.
+template <int K, bool PK>
+__device__ inline void sample_extrema(const double (&u)[K + 1][K + 1], double &mx, double &mn) {
+    constexpr int K1 = K + 1, NSP = 2 * K + 4;
+    constexpr Tab2<K> tb = make_tab2<K>();
+    mx = -INFINITY;
+    mn = INFINITY;
+#pragma unroll
+    for (int i = K + 2; i < NSP; ++i) {          // the sample points x > 0
+        double rp[K1], rm[K1];
+#pragma unroll
+        for (int j = 0; j < K1; ++j) {
+            double ev = 0.0, od = 0.0;
+#pragma unroll
+            for (int c = 0; c < K1; ++c) {
+                if (!kept<K, PK>(c, j)) continue;
+                if (c & 1) od = fma(u[c][j], tb.sp[i][c], od);
+                else ev = c == 0 ? u[c][j] : fma(u[c][j], tb.sp[i][c], ev);
+            }
+            rp[j] = ev + od;
+            rm[j] = ev - od;
+        }
+#pragma unroll
+        for (int y = K + 2; y < NSP; ++y)
+#pragma unroll
+            for (int sg = 0; sg < 2; ++sg) {
+                const double *b = sg ? rm : rp;
+                double ev = b[0], od = 0.0;
+#pragma unroll
+                for (int j = 1; j < K1; ++j) {
+                    if (j & 1) od = fma(b[j], tb.sp[y][j], od);
+                    else ev = fma(b[j], tb.sp[y][j], ev);
+                }
+                mx = max_d(mx, ev + fabs(od));
+                mn = min_d(mn, ev - fabs(od));
+            }
+    }
+}
+
+// Partial record of a wave's cells of mesh `mesh` (valid: this lane holds one)
+// from its first lane's view: u(q) gives the modes of component q, ub the cell
+// averages.  Lane 63 writes the mesh's half of the record.  Every lane takes part.
+template <int K, int FLUX, bool PK, class U>
+__device__ inline void wave_record(const Stage2Args &a, int mesh, bool valid, U &&u, double *rec) {
+    using F = Flux2D<FLUX>;
+    constexpr int NC = F::NC, K1 = K + 1, NM = Rec2<NC>::NM;
+    double v[NM], ub[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+        double m[K1][K1], mx, mn;
+        u(q, m);
+        sample_extrema<K, PK>(m, mx, mn);
+        ub[q] = valid ? m[0][0] : 1.0;
+        v[3 * q] = wave_reduce(0, valid ? m[0][0] : 0.0);
+        v[3 * q + 1] = wave_reduce(1, valid ? mx : -INFINITY);
+        v[3 * q + 2] = wave_reduce(2, valid ? mn : INFINITY);
+    }
+    double bx, by;
+    F::speeds(ub, bx, by, a.fp);
+    v[3 * NC] = wave_reduce(1, valid ? bx : -INFINITY);
+    v[3 * NC + 1] = wave_reduce(1, valid ? by : -INFINITY);
+    if (valid && !F::physical(ub, a.fp)) a.err[1] = 1;
+    if (threadIdx.x % WAVE == WAVE - 1) {
+#pragma unroll
+        for (int j = 0; j < NM; ++j) rec[mesh * NM + j] = v[j];
+    }
+}
 
 // Cells of a tile that its operator reads, per mesh: (TX+1) x (TY+1), primal
 // i0-1 .. i0+TX-1, dual i0 .. i0+TX (rows likewise).  In these indices an owned
@@ -546,7 +628,7 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
     const int tileid = tile_of_block(a.ntx * a.nty);
     const int i0 = (tileid % a.ntx) * TX, j0 = (tileid / a.ntx) * TY;
     const Stats2 *st = a.st;
-    if (st->done) return;
+    if (st->done[a.gpar]) return;
 
     // the tile's cells into LDS, damped on the way; a thread takes a cell of
     // either mesh with all its entries
@@ -598,7 +680,6 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
 
     // own part of the coupling, mass inverse, RK combination
     double *UM = (mesh ? a.UD : a.UC) + gofs, *OM = (mesh ? a.outD : a.outC) + gofs, *AM = (mesh ? a.AD : a.AC) + gofs;
-    if (!valid) return;
     double base[NC][K1][K1];                     // c_{l0} u^n [+ the accumulated earlier stages]
 #pragma unroll
     for (int q = 0; q < NC; ++q)
@@ -606,57 +687,87 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
         for (int i = 0; i < K1; ++i)
 #pragma unroll
             for (int j = 0; j < K1; ++j) base[q][i][j] = 0.0;
-    if (a.l > 0) {
+    if (a.l > 0) {                               // (lanes without a cell read cell 0)
+        const double *p = UM;
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
             for (int i = 0; i < K1; ++i)
 #pragma unroll
-                for (int j = 0; j < K1; ++j)
-                    if (kept<K, PK>(i, j)) base[q][i][j] = a.rs.cn * UM[(long long)((q * K1 + i) * K1 + j) * a.plane];
+                for (int j = 0; j < K1; ++j, p += a.plane)
+                    if (kept<K, PK>(i, j)) base[q][i][j] = a.rs.cn * *p;
     }
     if (a.rs.acc_read) {
+        const double *p = AM;
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
             for (int i = 0; i < K1; ++i)
 #pragma unroll
-                for (int j = 0; j < K1; ++j)
-                    if (kept<K, PK>(i, j)) base[q][i][j] += AM[(long long)((q * K1 + i) * K1 + j) * a.plane];
+                for (int j = 0; j < K1; ++j, p += a.plane)
+                    if (kept<K, PK>(i, j)) base[q][i][j] += *p;
     }
     const double im = 1.0 / (a.hx * a.hy), td = tau * a.rs.d;
     double bad = 0.0;                            // 0 times every output: 0, or NaN if one is not finite
+    double *po = OM;
 #pragma unroll
     for (int q = 0; q < NC; ++q)
 #pragma unroll
         for (int i = 0; i < K1; ++i)
 #pragma unroll
-            for (int j = 0; j < K1; ++j) {
-                const long long e = (long long)((q * K1 + i) * K1 + j) * a.plane;
+            for (int j = 0; j < K1; ++j, po += a.plane) {
                 if (!kept<K, PK>(i, j)) {
-                    OM[e] = 0.0;
+                    if (valid) *po = 0.0;
                     continue;
                 }
                 const double s0 = own[(q * NM + kept_index<K, PK>(i, j)) * NCELL];
                 const double Lv = fma(R[q][i][j], (2.0 * i + 1.0) * (2.0 * j + 1.0) * im, -itm * s0);
                 const double o = base[q][i][j] + fma(td, Lv, a.rs.cw * s0);
                 bad = fma(o, 0.0, bad);
-                OM[e] = o;
+                if (valid) *po = o;
+                R[q][i][j] = o;
             }
-    if (!(bad == 0.0)) a.err[0] = 1;
+    if (valid && !(bad == 0.0)) a.err[0] = 1;
     // damped input: u^n of the step, and classical RK4's sum of the stages that its last one needs
-    if (a.write_u || a.rs.ca != 0.0) {
+    if (valid && (a.write_u || a.rs.ca != 0.0)) {
+        double *p = a.write_u ? UM : AM;
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
             for (int i = 0; i < K1; ++i)
 #pragma unroll
-                for (int j = 0; j < K1; ++j) {
-                    const long long e = (long long)((q * K1 + i) * K1 + j) * a.plane;
+                for (int j = 0; j < K1; ++j, p += a.plane) {
                     const double s0 = kept<K, PK>(i, j) ? own[(q * NM + kept_index<K, PK>(i, j)) * NCELL] : 0.0;
-                    if (a.write_u) UM[e] = s0;
-                    else AM[e] = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, AM[e]);
+                    if (a.write_u) *p = s0;
+                    else *p = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, *p);
                 }
+    }
+    // Statistics of the output, from registers: this kernel waits on memory
+    // where k_delta2d, which had them, is bound by VALU issue.
+    wave_record<K, FLUX, PK>(a, mesh, valid, [&](int q, double (&m)[K1][K1]) {
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j) m[i][j] = R[q][i][j];
+    }, a.part + (long long)tileid * Rec2<NC>::N);
+}
+
+// Statistics of given data (a run's initial data, oecdg_dt): a record per 64 cells.
+template <int K, int FLUX, bool PK>
+__global__ __launch_bounds__(256) void k_stats2d(Stage2Args a) {
+    constexpr int NC = Flux2D<FLUX>::NC, K1 = K + 1;
+    const long long g = (long long)blockIdx.x * 256 + threadIdx.x;
+    const bool valid = g < a.plane;
+    if (g - threadIdx.x % WAVE >= a.plane) return;           // the whole wave
+#pragma unroll 1
+    for (int mesh = 0; mesh < 2; ++mesh) {
+        const double *in = (mesh ? a.inD : a.inC) + (valid ? g : 0);
+        wave_record<K, FLUX, PK>(a, mesh, valid, [&](int q, double (&m)[K1][K1]) {
+#pragma unroll
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j) m[i][j] = kept<K, PK>(i, j) ? in[((q * K1 + i) * K1 + j) * a.plane] : 0.0;
+        }, a.part + g / WAVE * Rec2<NC>::N);
     }
 }
 
@@ -685,10 +796,135 @@ __global__ __launch_bounds__(256) void k_damp2d(Stage2Args a) {
             }
 }
 
+// ---------------------------------------------------------- reduction ---
+
+constexpr int RED2_NT = 256;
+constexpr int RED2_LDS = RED2_NT + 2;
+constexpr int RED2_MAXB = 64;
+constexpr int RED2_AHEAD = 8;                    // records in flight per thread
+
+// Workgroup blk of r.nb folds its range of records into r.fold; the last one to
+// arrive folds those and updates the step scalars.  Both in a fixed order, so the
+// result does not depend on which one is last.  lds: RED2_LDS doubles.
+template <int NC>
+__device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
+    using RC = Rec2<NC>;
+    constexpr int G = RC::G, N = RC::N, NM = RC::NM, SUB = RED2_NT / G;
+    const int tid = threadIdx.x, row = tid % G, sub = tid / G;
+    const int j = row < N ? row : 0, kind = RC::kind(j);
+    Stats2 *st = r.st;
+    auto op = [kind](double x, double y) { return kind == 0 ? x + y : (kind == 1 ? max_d(x, y) : min_d(x, y)); };
+    auto combine = [&](double v) {               // over the subs in order: thread row < N gets row's value
+        lds[tid] = v;
+        __syncthreads();
+        double t = lds[row];
+        for (int k = 1; k < SUB; ++k) t = op(t, lds[k * G + row]);
+        __syncthreads();
+        return t;
+    };
+    if (r.mode == R2_SINGLE) {
+        if (tid == 0) {
+            st->tau = r.tau_o;
+            st->tau_max = r.taumax_o;
+            st->tau_damp = r.tau_o;
+            st->done[0] = st->done[1] = 0;
+        }
+        return;
+    }
+    const int t0 = blk * r.per, t1 = min(r.nrec, t0 + r.per);
+    double acc = stat_identity(kind);
+    for (int t = t0 + sub; t < t1; t += SUB * RED2_AHEAD) {
+        double x[RED2_AHEAD];
+#pragma unroll
+        for (int i = 0; i < RED2_AHEAD; ++i) x[i] = r.part[(long long)min(t + i * SUB, t1 - 1) * N + j];
+#pragma unroll
+        for (int i = 0; i < RED2_AHEAD; ++i) {
+            const double y = op(acc, x[i]);
+            acc = t + i * SUB < t1 ? y : acc;
+        }
+    }
+    double tot = combine(acc);
+    if (r.nb > 1) {
+        if (sub == 0 && row < N)
+            __hip_atomic_store(&r.fold[blk * N + row], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();                     // every store of the workgroup has been issued and waited for
+        unsigned *flag = (unsigned *)(lds + RED2_NT);
+        if (tid == 0) {
+            const unsigned n = __hip_atomic_fetch_add(r.count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            *flag = n == (unsigned)r.nb - 1;
+        }
+        __syncthreads();
+        if (!*flag) return;                  // uniform over the workgroup
+        if (tid == 0) __hip_atomic_store(r.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        acc = stat_identity(kind);
+        for (int b = sub; b < r.nb; b += SUB)
+            acc = op(acc, __hip_atomic_load(&r.fold[b * N + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        tot = combine(acc);
+    }
+    lds[tid] = tot;
+    __syncthreads();
+    if (r.mode == R2_STAGE && st->done[r.gpar ^ 1]) {            // the run has ended: nothing changes but the entry of this parity
+        if (tid == 0) st->done[r.gpar] = 1;
+        return;
+    }
+    if (tid < 2 * NC) {
+        const int mesh = tid / NC, q = tid % NC;
+        const double *t = lds + mesh * NM + 3 * q;
+        const double avg = t[0] / (double)r.ncell;
+        const double sig = fmax(t[1] - avg, avg - t[2]);
+        st->avg[mesh][q] = avg;
+        st->sig[mesh][q] = sig;
+        st->isig[mesh][q] = sig != 0.0 ? fmin(1.0 / sig, DBL_MAX) : 0.0;
+    }
+    if (tid != 0) return;
+    const double bx = max_d(lds[3 * NC], lds[NM + 3 * NC]), by = max_d(lds[3 * NC + 1], lds[NM + 3 * NC + 1]);
+    st->bx = bx;
+    st->by = by;
+    if (r.mode == R2_STEP || r.mode == R2_FINAL) {
+        if (st->pending) {                       // complete the previous step
+            st->t = st->last ? r.t_end : st->t + st->tau;
+            st->nexec += 1;
+            st->pending = 0;
+        }
+        st->tau_damp = st->tau;
+    }
+    if (r.mode == R2_STEP) {
+        if (!(st->t < r.t_end)) {
+            st->done[r.gpar] = 1;
+            return;
+        }
+        double tm = r.dt_fixed;
+        if (!(tm > 0.0)) {
+            const double rate = bx / r.hx + by / r.hy;
+            if (!(rate > 0.0) || !isfinite(rate)) {
+                st->done[r.gpar] = 1;
+                st->bad = 1;
+                r.err[2] = 1;
+                return;
+            }
+            tm = r.cfl / rate;
+        }
+        double tau = tm;
+        int last = 0;
+        if (st->t + tau >= r.t_end) {
+            tau = r.t_end - st->t;
+            last = 1;
+        }
+        st->tau = tau;
+        st->tau_max = tm;
+        st->last = last;
+        st->done[r.gpar] = 0;
+        st->pending = 1;
+    } else if (r.mode == R2_STAGE) {
+        st->tau_damp = st->tau;
+        st->done[r.gpar] = 0;
+    }
+}
+
 // ----------------------------------------------------------- delta kernel ---
 
-// Damping numerators and statistics of a state (the undamped output of a
-// stage, or initial data): per cell and component q
+// Damping numerators of a state (the undamped output of a stage): per cell and
+// component q
 //   N^m_q = sum_{e in {W,E,S,N}} beta_{e,K} (2m+1) h_e^(m-1) / ((2k-1) m!)
 //           (1/|e|) int_e ( sum_{alpha1+alpha2=m} (d^alpha (u_K - w)_q)^2 )^(1/2) ds
 // (delta^m_K = max_q N^m_q / sigma_q once sigma is known, Sec. 2.2).
@@ -792,60 +1028,26 @@ __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double 
     for (int m = 1; m < K1; ++m) acc[m] *= sct[m];
 }
 
-// Largest and smallest value of one component over S x S, S = {+-1, +-nodes}:
-// in each direction the even and the odd part at +x give the values at +x and
-// -x, whose larger and smaller are even +- |odd|.
-template <int K, bool PK>
-__device__ inline void sample_extrema(const double (&u)[K + 1][K + 1], double &mx, double &mn) {
-    constexpr int K1 = K + 1, NSP = 2 * K + 4;
-    constexpr Tab2<K> tb = make_tab2<K>();
-    mx = -INFINITY;
-    mn = INFINITY;
-#pragma unroll
-    for (int i = K + 2; i < NSP; ++i) {          // the sample points x > 0
-        double rp[K1], rm[K1];
-#pragma unroll
-        for (int j = 0; j < K1; ++j) {
-            double ev = 0.0, od = 0.0;
-#pragma unroll
-            for (int c = 0; c < K1; ++c) {
-                if (!kept<K, PK>(c, j)) continue;
-                if (c & 1) od = fma(u[c][j], tb.sp[i][c], od);
-                else ev = c == 0 ? u[c][j] : fma(u[c][j], tb.sp[i][c], ev);
-            }
-            rp[j] = ev + od;
-            rm[j] = ev - od;
-        }
-#pragma unroll
-        for (int y = K + 2; y < NSP; ++y)
-#pragma unroll
-            for (int sg = 0; sg < 2; ++sg) {
-                const double *b = sg ? rm : rp;
-                double ev = b[0], od = 0.0;
-#pragma unroll
-                for (int j = 1; j < K1; ++j) {
-                    if (j & 1) od = fma(b[j], tb.sp[y][j], od);
-                    else ev = fma(b[j], tb.sp[y][j], ev);
-                }
-                mx = max_d(mx, ev + fabs(od));
-                mn = min_d(mn, ev - fabs(od));
-            }
-    }
-}
-
+// Workgroups 0 .. nred-1 reduce the stage's statistics meanwhile (reduce2d):
+// they depend on the stage kernel alone.
 template <int K, int FLUX, int TX, int TY, bool PK>
-__global__ __launch_bounds__(TX * TY) void k_delta2d(Stage2Args a) {
+__global__ __launch_bounds__(TX * TY) void k_delta2d(Stage2Args a, Red2Args red) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>();
-    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, NT = TX * TY, NW = NT / WAVE;
+    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, NT = TX * TY;
     constexpr Tab2<K> tb = make_tab2<K>();
+    static_assert(NT == RED2_NT && 2 * NM * NCELL >= RED2_LDS, "reduce2d runs in this workgroup");
     __shared__ double tile[2 * NM * NCELL];      // [mesh][mode][cell] of component q
-    __shared__ double red[NW * 8];
 
-    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    const int nt = a.ntx * a.nty, tileid = tile_of_block(nt), q = blockIdx.y;
+    if (blockIdx.x < (unsigned)a.nred) {
+        reduce2d<NC>(red, blockIdx.x, tile);
+        return;
+    }
+    const int tid = threadIdx.x;
+    const int nt = a.ntx * a.nty, b = blockIdx.x - a.nred, q = b / nt;
+    const int tileid = xcd_tile(b - q * nt, nt);
     const int i0 = (tileid % a.ntx) * TX, j0 = (tileid / a.ntx) * TY;
-    if (a.mode == M2_STAGE && a.st->done) return;
+    if (a.st->done[a.gpar]) return;
     const bool small = a.nx <= TX || a.ny <= TY;
 #pragma unroll
     for (int c0 = 0; c0 < 2 * NCELL; c0 += NT) {
@@ -868,7 +1070,6 @@ __global__ __launch_bounds__(TX * TY) void k_delta2d(Stage2Args a) {
     const long long gofs = valid ? (long long)gy * a.nx + gx : 0;
     __syncthreads();
 
-    double sx = -INFINITY, sy = -INFINITY;       // the wave speeds of both cells
 #pragma unroll 1
     for (int mesh = 0; mesh < 2; ++mesh) {
         const double *own = tile + mesh * NM * NCELL + (r + 1 - mesh) * W + s + 1 - mesh;
@@ -882,173 +1083,31 @@ __global__ __launch_bounds__(TX * TY) void k_delta2d(Stage2Args a) {
         for (int i = 0; i < K1; ++i)
 #pragma unroll
             for (int j = 0; j < K1; ++j) u[i][j] = kept<K, PK>(i, j) ? own[kept_index<K, PK>(i, j) * NCELL] : 0.0;
-        double mx, mn;
-        sample_extrema<K, PK>(u, mx, mn);
-        const double v0 = wave_reduce(0, valid ? u[0][0] : 0.0);
-        const double v1 = wave_reduce(1, valid ? mx : -INFINITY);
-        const double v2 = wave_reduce(2, valid ? mn : INFINITY);
-        if (lane == WAVE - 1) {
-            red[wave * 8 + 3 * mesh] = v0;
-            red[wave * 8 + 3 * mesh + 1] = v1;
-            red[wave * 8 + 3 * mesh + 2] = v2;
-        }
+        double X[K1], Y[K1], ut[K1][K1];
+        edge_norms<K, PK, false, NCELL>(u, oth, 1, W, a.hx, a.hy, X);
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j) ut[i][j] = u[j][i];
+        edge_norms<K, PK, true, NCELL>(ut, oth, W, 1, a.hy, a.hx, Y);
         double bx, by;
         F::speeds(ub, bx, by, a.fp);
-        if (q == 0 && valid) {
-            sx = max_d(sx, bx);
-            sy = max_d(sy, by);
-            if (!F::physical(ub, a.fp)) a.err[1] = 1;
+        double *N = (mesh ? a.numD : a.numC) + gofs;
+        double hxm = 1.0 / a.hx, hym = 1.0 / a.hy;         // h_e^(m-1)
+#pragma unroll
+        for (int m = 0; m < K1; ++m) {
+            if (valid) N[(long long)(m * NC + q) * a.plane] = 0.25 * tb.cdel[m] * (bx * hxm * X[m] + by * hym * Y[m]);
+            hxm = m == 0 ? 1.0 : hxm * a.hx;
+            hym = m == 0 ? 1.0 : hym * a.hy;
         }
-        if (a.numC) {
-            double X[K1], Y[K1], ut[K1][K1];
-            edge_norms<K, PK, false, NCELL>(u, oth, 1, W, a.hx, a.hy, X);
-#pragma unroll
-            for (int i = 0; i < K1; ++i)
-#pragma unroll
-                for (int j = 0; j < K1; ++j) ut[i][j] = u[j][i];
-            edge_norms<K, PK, true, NCELL>(ut, oth, W, 1, a.hy, a.hx, Y);
-            double *N = (mesh ? a.numD : a.numC) + gofs;
-            double hxm = 1.0 / a.hx, hym = 1.0 / a.hy;         // h_e^(m-1)
-#pragma unroll
-            for (int m = 0; m < K1; ++m) {
-                if (valid) N[(long long)(m * NC + q) * a.plane] = 0.25 * tb.cdel[m] * (bx * hxm * X[m] + by * hym * Y[m]);
-                hxm = m == 0 ? 1.0 : hxm * a.hx;
-                hym = m == 0 ? 1.0 : hym * a.hy;
-            }
-        }
-    }
-    // the tile's partials of component q (q = 0: the wave speeds too)
-    sx = wave_reduce(1, sx);
-    sy = wave_reduce(1, sy);
-    if (lane == WAVE - 1) {
-        red[wave * 8 + 6] = sx;
-        red[wave * 8 + 7] = sy;
-    }
-    __syncthreads();
-    if (tid < 6 || (tid < 8 && q == 0)) {
-        const int kind = tid < 6 ? tid % 3 : 1;
-        double v = red[tid];
-        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, red[w * 8 + tid]);
-        const int row = tid < 6 ? row2(NC, tid / 3, q, tid % 3) : 2 * NC * 3 + tid - 6;
-        a.part[(long long)row * nt + tileid] = v;
     }
 }
 
-// ------------------------------------------------------- reduce kernels ---
-// Two levels, both in a fixed order: k_fold2d folds contiguous ranges of
-// tiles into one partial per workgroup; k_reduce2d folds those in one
-// workgroup and updates the step scalars.
-
-constexpr int RED2_NT = 256;
-constexpr int FOLD2_MAXB = 64;
-
-template <int NC>
-__global__ __launch_bounds__(RED2_NT) void k_fold2d(const double *part, int ntiles, int per, double *out, int nb) {
-    constexpr int NR = nrow2<NC>(), NW = RED2_NT / WAVE;
-    __shared__ double red[NW * NR];
-    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    const int t0 = blockIdx.x * per, t1 = min(ntiles, t0 + per);
-    double acc[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) acc[j] = stat_identity(j < 2 * NC * 3 ? j % 3 : 1);
-    for (int t = t0 + tid; t < t1; t += RED2_NT)
-#pragma unroll
-        for (int j = 0; j < NR; ++j) acc[j] = stat_op(j < 2 * NC * 3 ? j % 3 : 1, acc[j], part[(long long)j * ntiles + t]);
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        const double v = wave_reduce(j < 2 * NC * 3 ? j % 3 : 1, acc[j]);
-        if (lane == WAVE - 1) red[wave * NR + j] = v;
-    }
-    __syncthreads();
-    if (tid < NR) {
-        const int kind = tid < 2 * NC * 3 ? tid % 3 : 1;
-        double v = red[tid];
-        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, red[w * NR + tid]);
-        out[(long long)tid * nb + blockIdx.x] = v;
-    }
-}
-
+// The reduction alone (before a run's first stage, at its end, with OE off).
 template <int NC>
 __global__ __launch_bounds__(RED2_NT) void k_reduce2d(Red2Args r) {
-    constexpr int NR = nrow2<NC>(), NW = RED2_NT / WAVE;
-    __shared__ double red[NW * NR];
-    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    Stats2 *st = r.st;
-    if ((r.mode == R2_STAGE) && st->done) return;
-    double acc[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) acc[j] = stat_identity(j < 2 * NC * 3 ? j % 3 : 1);
-    for (int t = tid; t < r.ntiles; t += RED2_NT)
-#pragma unroll
-        for (int j = 0; j < NR; ++j) acc[j] = stat_op(j < 2 * NC * 3 ? j % 3 : 1, acc[j], r.part[(long long)j * r.ntiles + t]);
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        const double v = wave_reduce(j < 2 * NC * 3 ? j % 3 : 1, acc[j]);
-        if (lane == WAVE - 1) red[wave * NR + j] = v;
-    }
-    __syncthreads();
-    if (tid != 0) return;
-    double tot[NR];
-#pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        const int kind = j < 2 * NC * 3 ? j % 3 : 1;
-        double v = red[j];
-        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, red[w * NR + j]);
-        tot[j] = v;
-    }
-    for (int mesh = 0; mesh < 2; ++mesh)
-        for (int q = 0; q < NC; ++q) {
-            const double avg = tot[row2(NC, mesh, q, 0)] / (double)r.ncell;
-            st->avg[mesh][q] = avg;
-            const double sig = fmax(tot[row2(NC, mesh, q, 1)] - avg, avg - tot[row2(NC, mesh, q, 2)]);
-            st->sig[mesh][q] = sig;
-            st->isig[mesh][q] = sig != 0.0 ? fmin(1.0 / sig, DBL_MAX) : 0.0;
-        }
-    st->bx = tot[2 * NC * 3];
-    st->by = tot[2 * NC * 3 + 1];
-    if (r.mode == R2_STEP || r.mode == R2_FINAL) {
-        if (st->pending) {                       // complete the previous step
-            st->t = st->last ? r.t_end : st->t + st->tau;
-            st->nexec += 1;
-            st->pending = 0;
-        }
-        st->tau_damp = st->tau;
-    }
-    if (r.mode == R2_STEP) {
-        if (!(st->t < r.t_end)) {
-            st->done = 1;
-            return;
-        }
-        double tm = r.dt_fixed;
-        if (!(tm > 0.0)) {
-            const double rate = st->bx / r.hx + st->by / r.hy;
-            if (!(rate > 0.0) || !isfinite(rate)) {
-                st->done = 1;
-                st->bad = 1;
-                r.err[2] = 1;
-                return;
-            }
-            tm = r.cfl / rate;
-        }
-        double tau = tm;
-        int last = 0;
-        if (st->t + tau >= r.t_end) {
-            tau = r.t_end - st->t;
-            last = 1;
-        }
-        st->tau = tau;
-        st->tau_max = tm;
-        st->last = last;
-        st->done = 0;
-        st->pending = 1;
-    } else if (r.mode == R2_STAGE) {
-        st->tau_damp = st->tau;
-    } else if (r.mode == R2_SINGLE) {
-        st->tau = r.tau_o;
-        st->tau_max = r.taumax_o;
-        st->tau_damp = r.tau_o;
-        st->done = 0;
-    }
+    __shared__ double lds[RED2_LDS];
+    reduce2d<NC>(r, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------ host side ---
@@ -1062,12 +1121,13 @@ template <int K, int FLUX> struct Tile2 {
     static constexpr int TX = 16, TY = 4, DX = 16, DY = 16;
 };
 
-// which: 0 stage, 1 delta, 2 damp
+// which: 0 stage, 1 delta, 2 damp, 3 statistics of given data
 template <int K, int FLUX, bool PK>
 void *kernel2d_fn(int which) {
     using T = Tile2<K, FLUX>;
     if (which == 1) return (void *)k_delta2d<K, FLUX, T::DX, T::DY, PK>;
     if (which == 2) return (void *)k_damp2d<K, FLUX, PK>;
+    if (which == 3) return (void *)k_stats2d<K, FLUX, PK>;
     return (void *)k_stage2d<K, FLUX, T::TX, T::TY, PK>;
 }
 
@@ -1098,7 +1158,7 @@ struct Ext2D {
     int rk, ns;                  // RK method (rk_stage) and its stages per step
     int nx, ny;
     int ntx, nty;                // k_stage2d's tiles
-    int dtx, dty, ntiles;        // k_delta2d's tiles (columns of the partial statistics)
+    int dtx, dty;                // k_delta2d's tiles
     double hx, hy, cfl;
     FPar2 fp;
     long long S1;                // doubles of one mesh
@@ -1108,8 +1168,8 @@ struct Ext2D {
     double *U = nullptr;
     double *A = nullptr;         // classical RK4: accumulated damped inputs of stages 1 and 2 (both meshes)
     double *part[2] = {nullptr, nullptr};
-    double *fold = nullptr;      // [row][nfold] first-level partials
-    int nfold = 1, fold_per = 1;
+    double *fold = nullptr;      // first-level records of the reduction
+    unsigned *count = nullptr;   // its arrival count
     Stats2 *st = nullptr;
     Stats2 *st_h = nullptr;      // pinned
     int *err = nullptr, *err_h = nullptr;
@@ -1131,36 +1191,50 @@ hipError_t launch_stage2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
     return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 0), dim3(x.ntx * x.nty), dim3(2 * x.t.tx * x.t.ty), args, 0, s);
 }
 
-hipError_t launch_delta2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
+// Workgroups of the reduction of nrec records: enough for a few rounds of loads
+// each (a workgroup has RED2_NT / G records in a round), at most RED2_MAXB.
+int red_blocks(int nrec) { return std::min(RED2_MAXB, (nrec + 127) / 128); }
+
+// Numerators of the state in a.inC/inD when OE is on, and (red) the reduction for
+// the next stage beside them.
+hipError_t launch_delta2d(const Ext2D &x, const Stage2Args &a, const Red2Args *red, hipStream_t s) {
     Stage2Args copy = a;
+    Red2Args r{};
     copy.ntx = x.dtx;
     copy.nty = x.dty;
+    copy.nred = 0;
+    if (red) {
+        r = *red;
+        copy.nred = r.nb;
+    }
+    if (x.oe && x.k > 0) {
+        void *args[] = {&copy, &r};
+        return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 1), dim3(copy.nred + x.dtx * x.dty * x.nc),
+                               dim3(x.t.dx * x.t.dy), args, 0, s);
+    }
+    if (!red) return hipSuccess;
+    void *args[] = {&r};
+    void *fn = x.nc == 4 ? (void *)k_reduce2d<4> : (void *)k_reduce2d<1>;
+    return hipLaunchKernel(fn, dim3(r.nb), dim3(RED2_NT), args, 0, s);
+}
+
+hipError_t launch_reduce2d(const Ext2D &x, const Red2Args &red, hipStream_t s) {
+    Red2Args r = red;
+    void *args[] = {&r};
+    void *fn = x.nc == 4 ? (void *)k_reduce2d<4> : (void *)k_reduce2d<1>;
+    return hipLaunchKernel(fn, dim3(r.nb), dim3(RED2_NT), args, 0, s);
+}
+
+hipError_t launch_stats2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
+    Stage2Args copy = a;
     void *args[] = {&copy};
-    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 1), dim3(x.ntiles, x.nc), dim3(x.t.dx * x.t.dy), args, 0, s);
+    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 3), dim3((unsigned)((a.plane + 255) / 256)), dim3(256), args, 0, s);
 }
 
 hipError_t launch_damp2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
     Stage2Args copy = a;
     void *args[] = {&copy};
     return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 2), dim3((unsigned)((a.plane + 255) / 256), 2), dim3(256), args, 0, s);
-}
-
-// Fold r.part (per-tile partials) into the global scalars: first level into
-// x.fold, then the single-workgroup finish.
-hipError_t launch_reduce2d(const Ext2D &x, const Red2Args &r, hipStream_t s) {
-    const double *part = r.part;
-    int n = r.ntiles, per = x.fold_per, nb = x.nfold;
-    double *out = x.fold;
-    void *args1[] = {&part, &n, &per, &out, &nb};
-    void *fold = x.nc == 4 ? (void *)k_fold2d<4> : (void *)k_fold2d<1>;
-    hipError_t e = hipLaunchKernel(fold, dim3(nb), dim3(RED2_NT), args1, 0, s);
-    if (e != hipSuccess) return e;
-    void *fn = x.nc == 4 ? (void *)k_reduce2d<4> : (void *)k_reduce2d<1>;
-    Red2Args copy = r;
-    copy.part = x.fold;
-    copy.ntiles = nb;
-    void *args[] = {&copy};
-    return hipLaunchKernel(fn, dim3(1), dim3(RED2_NT), args, 0, s);
 }
 
 Stage2Args stage_args(const Ext2D &x) {
@@ -1182,35 +1256,49 @@ Stage2Args stage_args(const Ext2D &x) {
     return a;
 }
 
-Red2Args red_args(const Ext2D &x, const double *part, int mode) {
+// Records of a stage's output: one per tile of k_stage2d; of given data: one per 64 cells.
+int stage_records(const Ext2D &x) { return x.ntx * x.nty; }
+int data_records(const Ext2D &x) { return (int)(((long long)x.nx * x.ny + 63) / 64); }
+
+// gpar: parity of the stage that the result is for.
+Red2Args red_args(const Ext2D &x, const double *part, int nrec, int mode, int gpar) {
     Red2Args r;
     memset(&r, 0, sizeof(r));
     r.part = part;
-    r.ntiles = x.ntiles;
+    r.nrec = nrec;
+    r.nb = red_blocks(nrec);
+    r.per = (nrec + r.nb - 1) / r.nb;
     r.mode = mode;
+    r.gpar = gpar;
     r.ncell = (long long)x.nx * x.ny;
     r.t_end = INFINITY;
     r.cfl = x.cfl;
     r.hx = x.hx;
     r.hy = x.hy;
+    r.fold = x.fold;
+    r.count = x.count;
     r.st = x.st;
     r.err = x.err;
     return r;
 }
 
-// Damping numerators (when OE is on) and partial statistics of a state into
-// num[i] / part[i]; mode M2_STAGE skips the work once the run is done.
-hipError_t delta_of(const Ext2D &x, const double *uC, const double *uD, int i, int mode, hipStream_t s) {
+// Arguments of k_delta2d for a state: its numerators into num[i].
+Stage2Args delta_args(const Ext2D &x, const double *uC, const double *uD, int i, int gpar) {
     Stage2Args a = stage_args(x);
-    a.mode = mode;
+    a.gpar = gpar;
+    a.inC = uC;
+    a.inD = uD;
+    a.numC = x.num[i];
+    a.numD = x.num[i] + x.SN;
+    return a;
+}
+
+hipError_t stats_of(const Ext2D &x, const double *uC, const double *uD, int i, hipStream_t s) {
+    Stage2Args a = stage_args(x);
     a.inC = uC;
     a.inD = uD;
     a.part = x.part[i];
-    if (x.oe && x.k > 0) {
-        a.numC = x.num[i];
-        a.numD = x.num[i] + x.SN;
-    }
-    return launch_delta2d(x, a, s);
+    return launch_stats2d(x, a, s);
 }
 
 int check2d(oecdg_handle *h, const Ext2D &x) {
@@ -1251,7 +1339,6 @@ int create_2d(oecdg_handle *h, const oecdg_desc *d) {
     x->nty = (x->ny + x->t.ty - 1) / x->t.ty;
     x->dtx = (x->nx + x->t.dx - 1) / x->t.dx;
     x->dty = (x->ny + x->t.dy - 1) / x->t.dy;
-    x->ntiles = x->dtx * x->dty;
     x->hx = (d->xhi - d->xlo) / d->nx;
     x->hy = (d->yhi - d->ylo) / d->ny;
     x->cfl = d->cfl;
@@ -1260,17 +1347,18 @@ int create_2d(oecdg_handle *h, const oecdg_desc *d) {
     x->fp.gamma = d->flux_param[0];
     x->S1 = (long long)x->nc * (x->k + 1) * (x->k + 1) * x->nx * x->ny;
     x->SN = (long long)x->nc * (x->k + 1) * x->nx * x->ny;
-    const size_t nrow = x->nc == 4 ? nrow2<4>() : nrow2<1>();
+    const size_t nval = x->nc == 4 ? Rec2<4>::N : Rec2<1>::N;   // doubles of a record
+    const size_t nrec = std::max(stage_records(*x), data_records(*x));
     for (int i = 0; i < 2; ++i) {
         HIPCHK2(h, hipMalloc(&x->B[i], sizeof(double) * 2 * x->S1));
         HIPCHK2(h, hipMalloc(&x->num[i], sizeof(double) * 2 * x->SN));
-        HIPCHK2(h, hipMalloc(&x->part[i], sizeof(double) * nrow * x->ntiles));
+        HIPCHK2(h, hipMalloc(&x->part[i], sizeof(double) * nval * nrec));
     }
     HIPCHK2(h, hipMalloc(&x->U, sizeof(double) * 2 * x->S1));
     if (x->rk == 4) HIPCHK2(h, hipMalloc(&x->A, sizeof(double) * 2 * x->S1));
-    x->nfold = x->ntiles < FOLD2_MAXB ? x->ntiles : FOLD2_MAXB;
-    x->fold_per = (x->ntiles + x->nfold - 1) / x->nfold;
-    HIPCHK2(h, hipMalloc(&x->fold, sizeof(double) * nrow * x->nfold));
+    HIPCHK2(h, hipMalloc(&x->fold, sizeof(double) * nval * RED2_MAXB));
+    HIPCHK2(h, hipMalloc(&x->count, sizeof(unsigned)));
+    HIPCHK2(h, hipMemset(x->count, 0, sizeof(unsigned)));
     HIPCHK2(h, hipMalloc(&x->st, sizeof(Stats2)));
     HIPCHK2(h, hipHostMalloc((void **)&x->st_h, sizeof(Stats2), hipHostMallocDefault));
     HIPCHK2(h, hipMalloc(&x->err, 4 * sizeof(int)));
@@ -1289,6 +1377,7 @@ void destroy_2d(oecdg_handle *h) {
     if (x->U) (void)hipFree(x->U);
     if (x->A) (void)hipFree(x->A);
     if (x->fold) (void)hipFree(x->fold);
+    if (x->count) (void)hipFree(x->count);
     if (x->st) (void)hipFree(x->st);
     if (x->st_h) (void)hipHostFree(x->st_h);
     if (x->err) (void)hipFree(x->err);
@@ -1302,8 +1391,8 @@ int dt_2d(oecdg_handle *h, const double *uC, const double *uD, double *dt_out) {
     hipStream_t s = handle_stream(h);
     int rc = reset2d(h, x);
     if (rc != OECDG_OK) return rc;
-    HIPCHK2(h, delta_of(x, uC, uD, 0, M2_ALWAYS, s));
-    HIPCHK2(h, launch_reduce2d(x, red_args(x, x.part[0], R2_STATS), s));
+    HIPCHK2(h, stats_of(x, uC, uD, 0, s));
+    HIPCHK2(h, launch_reduce2d(x, red_args(x, x.part[0], data_records(x), R2_STATS, 0), s));
     HIPCHK2(h, hipMemcpyAsync(x.st_h, x.st, sizeof(Stats2), hipMemcpyDeviceToHost, s));
     HIPCHK2(h, hipStreamSynchronize(s));
     const double rate = x.st_h->bx / x.hx + x.st_h->by / x.hy;
@@ -1318,14 +1407,12 @@ int stage_2d(oecdg_handle *h, int stage, double dt, double tau_max, const double
     hipStream_t s = handle_stream(h);
     int rc = reset2d(h, x);
     if (rc != OECDG_OK) return rc;
-    // the step scalars only (the partials read here are discarded by mode)
-    Red2Args r = red_args(x, x.part[1], R2_SINGLE);
+    Red2Args r = red_args(x, nullptr, 1, R2_SINGLE, 0);       // the step scalars only
     r.tau_o = dt;
     r.taumax_o = tau_max;
-    HIPCHK2(h, hipMemsetAsync(x.part[1], 0, sizeof(double) * (x.nc == 4 ? nrow2<4>() : nrow2<1>()) * x.ntiles, s));
     HIPCHK2(h, launch_reduce2d(x, r, s));
     Stage2Args a = stage_args(x);
-    a.mode = M2_STAGE;
+    a.part = x.part[0];
     a.l = stage;
     a.rs = rk_stage(x.rk, stage);
     a.damp = 0;
@@ -1337,8 +1424,8 @@ int stage_2d(oecdg_handle *h, int stage, double dt, double tau_max, const double
     a.outC = x.B[0];
     a.outD = x.B[0] + x.S1;
     HIPCHK2(h, launch_stage2d(x, a, s));
-    HIPCHK2(h, delta_of(x, x.B[0], x.B[0] + x.S1, 0, M2_ALWAYS, s));
-    HIPCHK2(h, launch_reduce2d(x, red_args(x, x.part[0], R2_STAGE), s));
+    r = red_args(x, x.part[0], stage_records(x), R2_STAGE, 1);
+    HIPCHK2(h, launch_delta2d(x, delta_args(x, x.B[0], x.B[0] + x.S1, 0, 0), &r, s));
     Stage2Args f = stage_args(x);
     f.damp = x.oe && x.k > 0;
     f.inC = x.B[0];
@@ -1370,8 +1457,15 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
                             HIPCHK2(h, hipMemsetAsync(x.B[0] + mesh * x.S1 + ((q * (x.k + 1) + i) * (x.k + 1) + j) * plane,
                                                       0, sizeof(double) * plane, s));
     }
-    // statistics of the initial data (wave speeds for the first step) into part[0]
-    HIPCHK2(h, delta_of(x, x.B[0], x.B[0] + x.S1, 0, M2_ALWAYS, s));
+    // statistics of the initial data, and from them the first step
+    auto reduction = [&](const double *part, int nrec, long long g, int mode) {   // for stage g of the run
+        Red2Args r = red_args(x, part, nrec, mode, (int)(g & 1));
+        r.t_end = t_end;
+        r.dt_fixed = dt_fixed;
+        return r;
+    };
+    HIPCHK2(h, stats_of(x, x.B[0], x.B[0] + x.S1, 0, s));
+    if (nsteps != 0) HIPCHK2(h, launch_reduce2d(x, reduction(x.part[0], data_records(x), 0, R2_STEP), s));
     const int chunk = 16;
     long long n = 0;
     while (nsteps < 0 || n < nsteps) {
@@ -1380,15 +1474,11 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
             for (int l = 0; l < x.ns; ++l) {
                 const long long g = (long long)x.ns * (n + j) + l;
                 const int ib = (int)(g & 1), ob = (int)((g + 1) & 1);
-                Red2Args r = red_args(x, x.part[ib], l == 0 ? R2_STEP : R2_STAGE);
-                r.t_end = t_end;
-                r.dt_fixed = dt_fixed;
-                HIPCHK2(h, launch_reduce2d(x, r, s));
                 Stage2Args a = stage_args(x);
-                a.mode = M2_STAGE;
                 a.l = l;
+                a.gpar = ib;
                 a.rs = rk_stage(x.rk, l);
-                a.damp = x.oe && x.k > 0 && !(n + j == 0 && l == 0);
+                a.damp = x.oe && x.k > 0 && g > 0;
                 a.write_u = l == 0;
                 a.inC = x.B[ib];
                 a.inD = x.B[ib] + x.S1;
@@ -1398,19 +1488,21 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
                 a.outD = x.B[ob] + x.S1;
                 a.UC = x.U;
                 a.UD = x.U + x.S1;
+                a.part = x.part[ob];
                 HIPCHK2(h, launch_stage2d(x, a, s));
-                HIPCHK2(h, delta_of(x, x.B[ob], x.B[ob] + x.S1, ob, M2_STAGE, s));
+                // the numerators of its output and, beside them, the statistics for the next stage
+                const bool end = l == x.ns - 1 && n + j + 1 == nsteps;
+                const Red2Args r = reduction(x.part[ob], stage_records(x), g + 1, l == x.ns - 1 ? R2_STEP : R2_STAGE);
+                HIPCHK2(h, launch_delta2d(x, delta_args(x, x.B[ob], x.B[ob] + x.S1, ob, ib), end ? nullptr : &r, s));
             }
         n += m;
         HIPCHK2(h, hipMemcpyAsync(x.st_h, x.st, sizeof(Stats2), hipMemcpyDeviceToHost, s));
         HIPCHK2(h, hipStreamSynchronize(s));
-        if (x.st_h->done) break;
+        if (x.st_h->done[(x.ns * n) & 1]) break;           // (of the stage after the last one launched)
     }
     const long long N = x.st_h->nexec + x.st_h->pending;   // executed steps
     const int fb = (int)((x.ns * N) & 1);                  // buffer of the last stage's output
-    Red2Args r = red_args(x, x.part[fb], R2_FINAL);
-    r.t_end = t_end;
-    HIPCHK2(h, launch_reduce2d(x, r, s));
+    HIPCHK2(h, launch_reduce2d(x, reduction(x.part[fb], N > 0 ? stage_records(x) : data_records(x), 0, R2_FINAL), s));
     Stage2Args f = stage_args(x);
     f.damp = x.oe && x.k > 0 && N > 0;
     f.inC = x.B[fb];
