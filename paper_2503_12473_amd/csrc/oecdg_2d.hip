@@ -285,22 +285,26 @@ __host__ __device__ constexpr int kept_index(int a, int b) {
     return n;
 }
 
-// Damping factors exp(-tau sum_{m<=j} delta^m), j = 1..K, of global cell g of a
-// mesh, delta^m = max_q N^m_q / sigma_q (isig: 1 / sigma_q, 0 where sigma_q is 0).
+// The damping numerators N^m_q of global cell g of a mesh.
 template <int K, int NC>
-__device__ inline void damp_factors(const double *__restrict__ N, long long plane, long long g,
-                                    const double *__restrict__ isig, double tau, double (&f)[K]) {
-    double nv[K + 1][NC];
+__device__ inline void load_numerators(const double *__restrict__ N, long long plane, long long g,
+                                       double (&nv)[(K + 1) * NC]) {
+    const double *p = N + g;
 #pragma unroll
-    for (int m = 0; m <= K; ++m)
-#pragma unroll
-        for (int q = 0; q < NC; ++q) nv[m][q] = N[(m * NC + q) * plane + g];
+    for (int e = 0; e < (K + 1) * NC; ++e, p += plane) nv[e] = *p;
+}
+
+// Damping factors exp(-tau sum_{m<=j} delta^m), j = 1..K, of a cell,
+// delta^m = max_q N^m_q / sigma_q (isig: 1 / sigma_q, 0 where sigma_q is 0).
+template <int K, int NC>
+__device__ inline void damp_factors(const double (&nv)[(K + 1) * NC], const double *__restrict__ isig, double tau,
+                                    double (&f)[K]) {
     double S = 0.0;
 #pragma unroll
     for (int m = 0; m <= K; ++m) {
-        double dm = nv[m][0] * isig[0];
+        double dm = nv[m * NC] * isig[0];
 #pragma unroll
-        for (int q = 1; q < NC; ++q) dm = max_d(dm, nv[m][q] * isig[q]);
+        for (int q = 1; q < NC; ++q) dm = max_d(dm, nv[m * NC + q] * isig[q]);
         S += dm;
         if (m >= 1) f[m - 1] = exp(-tau * S);
     }
@@ -346,6 +350,7 @@ __device__ inline void sample_extrema(const double (&u)[K + 1][K + 1], double &m
                 mx = max_d(mx, ev + fabs(od));
                 mn = min_d(mn, ev - fabs(od));
             }
+        __builtin_amdgcn_sched_barrier(0);       // one line of samples at a time: bounds the live registers
     }
 }
 
@@ -414,9 +419,9 @@ __constant__ constexpr NodeTabs<K> node_tabs = make_node_tabs<K>();
 template <int K>
 __device__ inline NodeTab<K> node_tab(int p) { return node_tabs<K>.t[p]; }
 
-// Quadrant loop and edges of eq:2D_H for one owned cell: R[q][a][b] = the
-// integral of the rate against P_a P_b (own-cell part of the coupling left to
-// the caller), from the damped cells of the other mesh in LDS (oth, [entry][cell]).
+// Coupling and volume terms of eq:2D_H for one owned cell: R[q][a][b] = their
+// integral against P_a P_b (own-cell part of the coupling left to the caller),
+// from the damped cells of the other mesh in LDS (oth, [entry][cell]).
 //
 // A quadrant (sx, sy) is evaluated in its mirror image on the upper right one.
 // With P_n(-x) = (-1)^n P_n(x) and the symmetric Gauss rule, mirroring x turns a
@@ -425,8 +430,8 @@ __device__ inline NodeTab<K> node_tab(int p) { return node_tabs<K>.t[p]; }
 // compile-time tables, and only signs of the loaded modes (flip_sign) and, where
 // the quadrant loop crosses an axis, of the sums R change.
 template <int K, int FLUX, int TX, int TY, bool PK>
-__device__ inline void operator2d(const Stage2Args &a, const double *oth, int s, int r, double itm,
-                                  double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
+__device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, int r, double itm,
+                                double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NM = kept_modes<K, PK>();
     constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N;
@@ -536,13 +541,23 @@ __device__ inline void operator2d(const Stage2Args &a, const double *oth, int s,
             for (int j = 0; j < K1; ++j)
                 if (kept<K, PK>(i, j) && (i & 1) != (int)vecx(q)) R[q][i][j] = -R[q][i][j];
 
-    // edges of direction dir: f_dir of the other mesh on its centre line along each
-    // half-edge, mirrored onto the upper half of the E (N) edge as above
+}
+
+// Edge terms of eq:2D_H added to R: f_dir of the other mesh on its centre line
+// along each half-edge of direction dir, mirrored onto the upper half of the E (N)
+// edge as above.
+template <int K, int FLUX, int TX, int TY, bool PK>
+__device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, int r,
+                               double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
+    using F = Flux2D<FLUX>;
+    constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NM = kept_modes<K, PK>();
+    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N;
+    constexpr Tab2<K> tb = make_tab2<K>();
 #pragma unroll
     for (int dir = 0; dir < 2; ++dir) {
         constexpr auto vecn = [](int dr, int q) { return NC == 4 && q == 1 + dr; };   // momentum normal to the edge
         constexpr auto vect = [](int dr, int q) { return NC == 4 && q == 2 - dr; };   // and along it
-        const double ht = -0.25 * (dir ? hx : hy);
+        const double ht = -0.25 * (dir ? a.hx : a.hy);
 #pragma unroll 1
         for (int side = 0; side < 2; ++side) {
             const unsigned fn = side ? 0u : 0x80000000u;
@@ -617,7 +632,7 @@ __device__ inline void operator2d(const Stage2Args &a, const double *oth, int s,
 
 // One RK stage (see the top of the file).
 template <int K, int FLUX, int TX, int TY, bool PK>
-__global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
+__global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3 && !PK ? 3 : 4)) void k_stage2d(Stage2Args a) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>(), NE = NC * NM;
     constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, NT = 2 * TX * TY;
@@ -630,28 +645,58 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
     const Stats2 *st = a.st;
     if (st->done[a.gpar]) return;
 
-    // the tile's cells into LDS, damped on the way; a thread takes a cell of
-    // either mesh with all its entries
+    // the tile's cells into LDS, damped on the way: a cell of either mesh per
+    // thread, and the cells beyond the threads shared by the waves, PART entries
+    // each.  Every load is issued before the first wait.
+    constexpr int REST = 2 * NCELL - NT, PARTS = NC == 4 ? 2 : 1, PART = NE / PARTS;
+    static_assert(REST > 0 && REST <= WAVE && NT / WAVE >= PARTS, "one more cell per lane");
     const bool small = a.nx <= TX || a.ny <= TY;
-#pragma unroll 1
-    for (int c = tid; c < 2 * NCELL; c += NT) {
-        const int mesh = c >= NCELL, cell = c - mesh * NCELL;
-        const int gx = wrap_idx(i0 - 1 + mesh + cell % W, a.nx, small);
-        const int gy = wrap_idx(j0 - 1 + mesh + cell / W, a.ny, small);
-        const long long g = (long long)gy * a.nx + gx;
-        const double *in = (mesh ? a.inD : a.inC) + g;
-        double v[NE];
+    const int wave = tid / WAVE, lane = tid % WAVE;
+    struct Cell {
+        int mesh, cell;
+        long long g;
+    };
+    auto cell_of = [&](int c) {
+        Cell t;
+        t.mesh = c >= NCELL;
+        t.cell = c - t.mesh * NCELL;
+        const int gx = wrap_idx(i0 - 1 + t.mesh + t.cell % W, a.nx, small);
+        const int gy = wrap_idx(j0 - 1 + t.mesh + t.cell / W, a.ny, small);
+        t.g = (long long)gy * a.nx + gx;
+        return t;
+    };
+    const Cell c0 = cell_of(tid), c1 = cell_of(NT + (lane < REST ? lane : 0));
+    const bool more = lane < REST && wave < PARTS;
+    const int q1 = PARTS == 2 ? wave * (NC / 2) : 0;         // first component of this wave's part
+    double v0[NE], v1[PART], n0[K1 * NC], n1[K1 * NC];
+    {
+        const double *p = (c0.mesh ? a.inD : a.inC) + c0.g;
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
             for (int i = 0; i < K1; ++i)
 #pragma unroll
-                for (int j = 0; j < K1; ++j)
-                    if (kept<K, PK>(i, j))
-                        v[q * NM + kept_index<K, PK>(i, j)] = in[((q * K1 + i) * K1 + j) * a.plane];
+                for (int j = 0; j < K1; ++j, p += a.plane)
+                    if (kept<K, PK>(i, j)) v0[q * NM + kept_index<K, PK>(i, j)] = *p;
+    }
+    if (more) {
+        const double *p = (c1.mesh ? a.inD : a.inC) + c1.g + (long long)q1 * K1 * K1 * a.plane;
+#pragma unroll
+        for (int q = 0; q < NC / PARTS; ++q)
+#pragma unroll
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j, p += a.plane)
+                    if (kept<K, PK>(i, j)) v1[q * NM + kept_index<K, PK>(i, j)] = *p;
+    }
+    if (a.damp) {
+        load_numerators<K, NC>(c0.mesh ? a.numD : a.numC, a.plane, c0.g, n0);
+        if (more) load_numerators<K, NC>(c1.mesh ? a.numD : a.numC, a.plane, c1.g, n1);
+    }
+    {
+        double f[K];
         if (a.damp) {
-            double f[K];
-            damp_factors<K, NC>(mesh ? a.numD : a.numC, a.plane, g, st->isig[mesh], st->tau_damp, f);
+            damp_factors<K, NC>(n0, st->isig[c0.mesh], st->tau_damp, f);
 #pragma unroll
             for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -659,11 +704,28 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
 #pragma unroll
                     for (int j = 0; j < K1; ++j)
                         if (kept<K, PK>(i, j) && i + j > 0)
-                            v[q * NM + kept_index<K, PK>(i, j)] *= f[(i + j < K ? i + j : K) - 1];
+                            v0[q * NM + kept_index<K, PK>(i, j)] *= f[(i + j < K ? i + j : K) - 1];
         }
-        double *o = tile + mesh * NE * NCELL + cell;
+        double *o = tile + c0.mesh * NE * NCELL + c0.cell;
 #pragma unroll
-        for (int e = 0; e < NE; ++e) o[e * NCELL] = v[e];
+        for (int e = 0; e < NE; ++e) o[e * NCELL] = v0[e];
+    }
+    if (more) {
+        double f[K];
+        if (a.damp) {
+            damp_factors<K, NC>(n1, st->isig[c1.mesh], st->tau_damp, f);
+#pragma unroll
+            for (int q = 0; q < NC / PARTS; ++q)
+#pragma unroll
+                for (int i = 0; i < K1; ++i)
+#pragma unroll
+                    for (int j = 0; j < K1; ++j)
+                        if (kept<K, PK>(i, j) && i + j > 0)
+                            v1[q * NM + kept_index<K, PK>(i, j)] *= f[(i + j < K ? i + j : K) - 1];
+        }
+        double *o = tile + (c1.mesh * NE + q1 * NM) * NCELL + c1.cell;
+#pragma unroll
+        for (int e = 0; e < PART; ++e) o[e * NCELL] = v1[e];
     }
     __syncthreads();
 
@@ -675,12 +737,12 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
     const long long gofs = valid ? (long long)gy * a.nx + gx : 0;
     const double *own = tile + mesh * NE * NCELL + (r + 1 - mesh) * W + s + 1 - mesh;
     const double itm = 1.0 / st->tau_max, tau = st->tau;
+    const double *oth = tile + (1 - mesh) * NE * NCELL;
     double R[NC][K1][K1];
-    operator2d<K, FLUX, TX, TY, PK>(a, tile + (1 - mesh) * NE * NCELL, s, r, itm, R);
-
-    // own part of the coupling, mass inverse, RK combination
+    volume2d<K, FLUX, TX, TY, PK>(a, oth, s, r, itm, R);
+    // u^n, asked for before the edges, which leave the registers for it
     double *UM = (mesh ? a.UD : a.UC) + gofs, *OM = (mesh ? a.outD : a.outC) + gofs, *AM = (mesh ? a.AD : a.AC) + gofs;
-    double base[NC][K1][K1];                     // c_{l0} u^n [+ the accumulated earlier stages]
+    double base[NC][K1][K1];                     // u^n
 #pragma unroll
     for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -695,9 +757,11 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
             for (int i = 0; i < K1; ++i)
 #pragma unroll
                 for (int j = 0; j < K1; ++j, p += a.plane)
-                    if (kept<K, PK>(i, j)) base[q][i][j] = a.rs.cn * *p;
+                    if (kept<K, PK>(i, j)) base[q][i][j] = *p;
     }
-    if (a.rs.acc_read) {
+    edges2d<K, FLUX, TX, TY, PK>(a, oth, s, r, R);
+    double cn = a.rs.cn;
+    if (a.rs.acc_read) {                         // classical RK4's last stage: the accumulated earlier stages
         const double *p = AM;
 #pragma unroll
         for (int q = 0; q < NC; ++q)
@@ -705,8 +769,11 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
             for (int i = 0; i < K1; ++i)
 #pragma unroll
                 for (int j = 0; j < K1; ++j, p += a.plane)
-                    if (kept<K, PK>(i, j)) base[q][i][j] += *p;
+                    if (kept<K, PK>(i, j)) base[q][i][j] = fma(cn, base[q][i][j], *p);
+        cn = 1.0;
     }
+
+    // own part of the coupling, mass inverse, RK combination
     const double im = 1.0 / (a.hx * a.hy), td = tau * a.rs.d;
     double bad = 0.0;                            // 0 times every output: 0, or NaN if one is not finite
     double *po = OM;
@@ -722,7 +789,7 @@ __global__ __launch_bounds__(2 * TX * TY, 2) void k_stage2d(Stage2Args a) {
                 }
                 const double s0 = own[(q * NM + kept_index<K, PK>(i, j)) * NCELL];
                 const double Lv = fma(R[q][i][j], (2.0 * i + 1.0) * (2.0 * j + 1.0) * im, -itm * s0);
-                const double o = base[q][i][j] + fma(td, Lv, a.rs.cw * s0);
+                const double o = fma(cn, base[q][i][j], fma(td, Lv, a.rs.cw * s0));
                 bad = fma(o, 0.0, bad);
                 if (valid) *po = o;
                 R[q][i][j] = o;
@@ -781,7 +848,11 @@ __global__ __launch_bounds__(256) void k_damp2d(Stage2Args a) {
     double f[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) f[j] = 1.0;
-    if (a.damp) damp_factors<K, NC>(mesh ? a.numD : a.numC, a.plane, g, a.st->isig[mesh], a.st->tau_damp, f);
+    if (a.damp) {
+        double nv[K1 * NC];
+        load_numerators<K, NC>(mesh ? a.numD : a.numC, a.plane, g, nv);
+        damp_factors<K, NC>(nv, a.st->isig[mesh], a.st->tau_damp, f);
+    }
     const double *in = (mesh ? a.inD : a.inC) + g;
     double *out = (mesh ? a.outD : a.outC) + g;
 #pragma unroll
@@ -1028,78 +1099,91 @@ __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double 
     for (int m = 1; m < K1; ++m) acc[m] *= sct[m];
 }
 
-// Workgroups 0 .. nred-1 reduce the stage's statistics meanwhile (reduce2d):
-// they depend on the stage kernel alone.
+// A workgroup takes one mesh of one component of a tile, a cell per thread: only
+// the other mesh is staged in LDS (21 KB for k = 2), the own cell is in registers,
+// and registers alone limit the waves in flight.  Workgroups 0 .. nred-1 reduce
+// the stage's statistics meanwhile (reduce2d): they depend on the stage kernel
+// alone.
+__host__ __device__ constexpr int delta_blocks(int nt) { return 2 * ((nt + 7) / 8 * 8); }   // per component
+
 template <int K, int FLUX, int TX, int TY, bool PK>
-__global__ __launch_bounds__(TX * TY) void k_delta2d(Stage2Args a, Red2Args red) {
+__global__ __launch_bounds__(TX * TY, K == 3 ? 2 : 4) void k_delta2d(Stage2Args a, Red2Args red) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>();
     constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, NT = TX * TY;
     constexpr Tab2<K> tb = make_tab2<K>();
-    static_assert(NT == RED2_NT && 2 * NM * NCELL >= RED2_LDS, "reduce2d runs in this workgroup");
-    __shared__ double tile[2 * NM * NCELL];      // [mesh][mode][cell] of component q
+    static_assert(NT == RED2_NT && NM * NCELL >= RED2_LDS, "reduce2d runs in this workgroup");
+    __shared__ double tile[NM * NCELL];          // [mode][cell] of component q of the other mesh
 
     if (blockIdx.x < (unsigned)a.nred) {
         reduce2d<NC>(red, blockIdx.x, tile);
         return;
     }
+    // component, then (per XCD) a band of tiles, both meshes of a tile next to each other
     const int tid = threadIdx.x;
-    const int nt = a.ntx * a.nty, b = blockIdx.x - a.nred, q = b / nt;
-    const int tileid = xcd_tile(b - q * nt, nt);
+    const int nt = a.ntx * a.nty, per = delta_blocks(nt), b = blockIdx.x - a.nred, q = b / per, l = b - q * per;
+    const int mesh = (l >> 3) & 1, tileid = (l & 7) * (per / 16) + (l >> 4);
+    if (tileid >= nt || a.st->done[a.gpar]) return;
     const int i0 = (tileid % a.ntx) * TX, j0 = (tileid / a.ntx) * TY;
-    if (a.st->done[a.gpar]) return;
-    const bool small = a.nx <= TX || a.ny <= TY;
-#pragma unroll
-    for (int c0 = 0; c0 < 2 * NCELL; c0 += NT) {
-        const int c = c0 + tid;
-        if (c < 2 * NCELL) {
-            const int mesh = c >= NCELL, cell = c - mesh * NCELL;
-            const int gx = wrap_idx(i0 - 1 + mesh + cell % W, a.nx, small);
-            const int gy = wrap_idx(j0 - 1 + mesh + cell / W, a.ny, small);
-            const double *in = (mesh ? a.inD : a.inC) + (long long)q * K1 * K1 * a.plane + (long long)gy * a.nx + gx;
-            double *o = tile + mesh * NM * NCELL + cell;
-#pragma unroll
-            for (int i = 0; i < K1; ++i)
-#pragma unroll
-                for (int j = 0; j < K1; ++j)
-                    if (kept<K, PK>(i, j)) o[kept_index<K, PK>(i, j) * NCELL] = in[(i * K1 + j) * a.plane];
-        }
-    }
     const int s = tid % TX, r = tid / TX, gx = i0 + s, gy = j0 + r;
     const bool valid = gx < a.nx && gy < a.ny;
-    const long long gofs = valid ? (long long)gy * a.nx + gx : 0;
+    const long long gofs = valid ? (long long)gy * a.nx + gx : 0, qofs = (long long)q * K1 * K1 * a.plane;
+    const bool small = a.nx <= TX || a.ny <= TY;
+
+    // every load before the first wait: the own cell and its averages, the other mesh's cells
+    double u[K1][K1], ub[NC];
+    {
+        const double *p = (mesh ? a.inD : a.inC) + gofs + qofs;
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j, p += a.plane) u[i][j] = kept<K, PK>(i, j) ? *p : 0.0;
+        p = (mesh ? a.inD : a.inC) + gofs;
+#pragma unroll
+        for (int c = 0; c < NC; ++c, p += K1 * K1 * a.plane) ub[c] = *p;
+    }
+    constexpr int REST = NCELL - NT;
+    static_assert(REST > 0 && REST <= WAVE, "one more cell per lane of the first wave");
+    auto cell_ptr = [&](int c) {                 // cell c of the other mesh: primal from i0-1, dual from i0
+        const int x = wrap_idx(i0 - mesh + c % W, a.nx, small), y = wrap_idx(j0 - mesh + c / W, a.ny, small);
+        return (mesh ? a.inC : a.inD) + qofs + (long long)y * a.nx + x;
+    };
+    double v0[NM], v1[NM];
+    auto load = [&](const double *p, double (&v)[NM]) {
+#pragma unroll
+        for (int i = 0; i < K1; ++i)
+#pragma unroll
+            for (int j = 0; j < K1; ++j, p += a.plane)
+                if (kept<K, PK>(i, j)) v[kept_index<K, PK>(i, j)] = *p;
+    };
+    load(cell_ptr(tid), v0);
+    if (tid < REST) load(cell_ptr(NT + tid), v1);
+#pragma unroll
+    for (int e = 0; e < NM; ++e) tile[e * NCELL + tid] = v0[e];
+    if (tid < REST) {
+#pragma unroll
+        for (int e = 0; e < NM; ++e) tile[e * NCELL + NT + tid] = v1[e];
+    }
     __syncthreads();
 
-#pragma unroll 1
-    for (int mesh = 0; mesh < 2; ++mesh) {
-        const double *own = tile + mesh * NM * NCELL + (r + 1 - mesh) * W + s + 1 - mesh;
-        const double *oth = tile + (1 - mesh) * NM * NCELL + r * W + s;
-        const double *bar = (mesh ? a.inD : a.inC) + gofs;
-        double ub[NC];                           // the cell averages of every component
+    const double *oth = tile + r * W + s;
+    double X[K1], Y[K1], ut[K1][K1];
+    edge_norms<K, PK, false, NCELL>(u, oth, 1, W, a.hx, a.hy, X);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) ub[c] = bar[(long long)c * K1 * K1 * a.plane];
-        double u[K1][K1];
+    for (int i = 0; i < K1; ++i)
 #pragma unroll
-        for (int i = 0; i < K1; ++i)
+        for (int j = 0; j < K1; ++j) ut[i][j] = u[j][i];
+    edge_norms<K, PK, true, NCELL>(ut, oth, W, 1, a.hy, a.hx, Y);
+    if (!valid) return;
+    double bx, by;
+    F::speeds(ub, bx, by, a.fp);
+    double *N = (mesh ? a.numD : a.numC) + gofs;
+    double hxm = 1.0 / a.hx, hym = 1.0 / a.hy;             // h_e^(m-1)
 #pragma unroll
-            for (int j = 0; j < K1; ++j) u[i][j] = kept<K, PK>(i, j) ? own[kept_index<K, PK>(i, j) * NCELL] : 0.0;
-        double X[K1], Y[K1], ut[K1][K1];
-        edge_norms<K, PK, false, NCELL>(u, oth, 1, W, a.hx, a.hy, X);
-#pragma unroll
-        for (int i = 0; i < K1; ++i)
-#pragma unroll
-            for (int j = 0; j < K1; ++j) ut[i][j] = u[j][i];
-        edge_norms<K, PK, true, NCELL>(ut, oth, W, 1, a.hy, a.hx, Y);
-        double bx, by;
-        F::speeds(ub, bx, by, a.fp);
-        double *N = (mesh ? a.numD : a.numC) + gofs;
-        double hxm = 1.0 / a.hx, hym = 1.0 / a.hy;         // h_e^(m-1)
-#pragma unroll
-        for (int m = 0; m < K1; ++m) {
-            if (valid) N[(long long)(m * NC + q) * a.plane] = 0.25 * tb.cdel[m] * (bx * hxm * X[m] + by * hym * Y[m]);
-            hxm = m == 0 ? 1.0 : hxm * a.hx;
-            hym = m == 0 ? 1.0 : hym * a.hy;
-        }
+    for (int m = 0; m < K1; ++m) {
+        N[(long long)(m * NC + q) * a.plane] = 0.25 * tb.cdel[m] * (bx * hxm * X[m] + by * hym * Y[m]);
+        hxm = m == 0 ? 1.0 : hxm * a.hx;
+        hym = m == 0 ? 1.0 : hym * a.hy;
     }
 }
 
@@ -1209,7 +1293,7 @@ hipError_t launch_delta2d(const Ext2D &x, const Stage2Args &a, const Red2Args *r
     }
     if (x.oe && x.k > 0) {
         void *args[] = {&copy, &r};
-        return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 1), dim3(copy.nred + x.dtx * x.dty * x.nc),
+        return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 1), dim3(copy.nred + delta_blocks(x.dtx * x.dty) * x.nc),
                                dim3(x.t.dx * x.t.dy), args, 0, s);
     }
     if (!red) return hipSuccess;
