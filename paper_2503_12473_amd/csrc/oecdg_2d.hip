@@ -240,17 +240,17 @@ template <int NC> struct Rec2 {
 // Tile of a workgroup; a band of consecutive tiles per XCD (xcd_tile).
 __device__ inline int tile_of_block(int nt) { return xcd_tile(blockIdx.x, nt); }
 
-// sqrt(x) for x >= SQRT_TINY from the hardware estimate of 1/sqrt (relative
-// error below 2^-22), one Goldschmidt step and one correction by the residual
-// x - g^2: within an ulp of the correctly rounded root up to 1e300.  The IEEE
-// sequence (range scaling, three steps, class checks) was 40 % of k_delta2d.
+// sqrt(x) for x >= SQRT_TINY from the hardware estimate r of 1/sqrt (relative
+// error below 2^-22) and one third-order step: with t = x r and e = 1 - t r,
+// sqrt(x) = t (1 - e)^(-1/2) = t + t e (1/2 + 3/8 e + O(e^2)), within an ulp of the
+// correctly rounded root up to 1e300.  The IEEE sequence (range scaling, three
+// steps, class checks) was 40 % of k_delta2d.
 constexpr double SQRT_TINY = 1e-300;
 __device__ inline double sqrt_nr(double x) {
     const double r = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * r;
-    double g = x * r;
-    g = fma(g, fma(-h, g, 0.5), g);
-    return fma(fma(-g, g, x), h, g);
+    const double t = x * r;
+    const double e = fma(-t, r, 1.0);
+    return fma(t * e, fma(e, 0.375, 0.5), t);
 }
 
 // c x + y and c x for a constant c: no multiplication by 1 (the compiler may not
@@ -341,14 +341,19 @@ __device__ inline void sample_extrema(const double (&u)[K + 1][K + 1], double &m
 #pragma unroll
             for (int sg = 0; sg < 2; ++sg) {
                 const double *b = sg ? rm : rp;
-                double ev = b[0], od = 0.0;
+                double ev = b[0], hi, lo;
 #pragma unroll
-                for (int j = 1; j < K1; ++j) {
-                    if (j & 1) od = fma(b[j], tb.sp[y][j], od);
-                    else ev = fma(b[j], tb.sp[y][j], ev);
+                for (int j = 2; j < K1; j += 2) ev = mad_c(tb.sp[y][j], b[j], ev);
+                if constexpr (K1 < 4) {          // one odd mode: |od| = y |b_1|
+                    hi = fma(tb.sp[y][1], fabs(b[1]), ev);
+                    lo = fma(-tb.sp[y][1], fabs(b[1]), ev);
+                } else {
+                    const double od = fma(b[3], tb.sp[y][3], b[1] * tb.sp[y][1]);
+                    hi = ev + fabs(od);
+                    lo = ev - fabs(od);
                 }
-                mx = max_d(mx, ev + fabs(od));
-                mn = min_d(mn, ev - fabs(od));
+                mx = max_d(mx, hi);
+                mn = min_d(mn, lo);
             }
         __builtin_amdgcn_sched_barrier(0);       // one line of samples at a time: bounds the live registers
     }
@@ -470,9 +475,21 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
             fp.a = flip_sign(fp.a, mx);
             fp.b = flip_sign(fp.b, my);
         }
+        double d[NC][K1][K1];                    // the overlapping cell's modes, mirrored
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int c = 0; c < K1; ++c)
+#pragma unroll
+                for (int e = 0; e < K1; ++e) {
+                    d[q][c][e] = 0.0;
+                    if (!kept<K, PK>(c, e)) continue;
+                    const double x = o[(q * NM + kept_index<K, PK>(c, e)) * NCELL];
+                    const bool ox = (c & 1) != (int)vecx(q), oy = (e & 1) != (int)vecy(q);
+                    d[q][c][e] = (ox || oy) ? flip_sign(x, (ox ? mx : 0u) ^ (oy ? my : 0u)) : x;
+                }
         // One node in x at a time, a loop at run time (its table entries are
-        // uniform loads): the modes are read from LDS again for each node, as
-        // keeping them beside R, A and B passes 256 registers.
+        // uniform loads): unrolled, the live values pass 256 registers.
 #pragma unroll 1
         for (int p = 0; p < Q; ++p) {
             const NodeTab<K> nt = node_tab<K>(p);
@@ -481,16 +498,11 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
             for (int q = 0; q < NC; ++q)
 #pragma unroll
                 for (int e = 0; e < K1; ++e) {
-                    double t = 0.0;
+                    double t = d[q][0][e];
 #pragma unroll
-                    for (int c = 0; c < K1; ++c) {
-                        if (!kept<K, PK>(c, e)) continue;
-                        const double x = o[(q * NM + kept_index<K, PK>(c, e)) * NCELL];
-                        const bool ox = (c & 1) != (int)vecx(q);
-                        if (c == 0) t = ox ? flip_sign(x, mx) : x;
-                        else t = fma(x, flip_sign(nt.nb[c], ox ? mx : 0u), t);
-                    }
-                    cxv[q][e] = (e & 1) != (int)vecy(q) ? flip_sign(t, my) : t;
+                    for (int c = 1; c < K1; ++c)
+                        if (kept<K, PK>(c, e)) t = fma(d[q][c][e], nt.nb[c], t);
+                    cxv[q][e] = t;
                 }
             // A_j: coupling and y flux against P_j(y), P_j'(y); B_j: x flux against P_j(y)
             double A[NC][K1], B[NC][K1];
@@ -1010,20 +1022,17 @@ __device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
 // sqrt terms of one direction: acc[m] = sum over both edges, both halves and the
 // Gauss nodes of w_g (sum_alpha (d^alpha (u_K - w))^2)^(1/2).  u[n][t]: the own
 // cell's modes, normal to the edge and along it; oth: the other mesh's, of which
-// cell oc0 + side sn + half st (strides sn, st) overlaps each half-edge, mode
-// (n, t) at n mn + t mt.
-// Each half-edge is evaluated as its mirror image on the upper half of the E (N)
-// edge: the odd modes of a mirrored direction change sign in both cells, the
-// derivatives at most their sign, so one loop body with compile-time tables
-// serves all four.
+// cell side sn + half st (strides sn, st) overlaps each half-edge.
+// The W (S) edge is evaluated as its mirror image on the E (N) edge: the odd modes
+// of the normal direction change sign in both cells, the derivatives at most
+// their sign.  Derivatives are scaled by the tangential (2/h_t)^m of their order m:
+// the factor leaves the root and is applied to the sum at the end, and a normal
+// derivative brings (h_t/h_n) each.
 template <int K, bool PK, bool DIRY, int NCELL>
 __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double *oth, int sn, int st, double hn,
                                   double ht, double (&acc)[K + 1]) {
     constexpr int K1 = K + 1, Q = K + 1;
     constexpr Tab2<K> tb = make_tab2<K>();
-    // Derivatives scaled by the tangential (2/h_t)^m of their order m: the factor
-    // leaves the root and is applied to the sum at the end, and a normal derivative
-    // brings (h_t/h_n) each.
     double kap[K1], sct[K1];
     kap[0] = sct[0] = 1.0;
 #pragma unroll
@@ -1033,67 +1042,82 @@ __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double 
     }
 #pragma unroll
     for (int m = 0; m < K1; ++m) acc[m] = 0.0;
+    double tiny = SQRT_TINY;                     // in a register: as a constant it is moved there for every sum
+    asm volatile("" : "+v"(tiny));
 #pragma unroll 1
-    for (int e = 0; e < 4; ++e) {
-        const int side = e >> 1, half = e & 1;
-        const unsigned fn = side ? 0u : 0x80000000u, ft = half ? 0u : 0x80000000u;
-        const double *o = oth + side * sn + half * st;
-        double D[K1][K1];                        // [normal derivative][mode along the edge], own coordinate
+    for (int side = 0; side < 2; ++side) {
+        const unsigned fn = side ? 0u : 0x80000000u;
+        double own[K1][K1], ks[K1];              // own trace by [normal derivative][mode along the edge], scaled
 #pragma unroll
         for (int dn = 0; dn < K1; ++dn) {
-            double r[K1];                        // derivative dn of the other trace at its centre line
+            ks[dn] = (dn & 1) ? flip_sign(kap[dn], fn) : kap[dn];
 #pragma unroll
             for (int t = 0; t < K1; ++t) {
-                r[t] = 0.0;
+                own[dn][t] = 0.0;
                 if (!kept<K, PK>(dn, t)) continue;
-#pragma unroll
-                for (int n = dn; n < K1; n += 2)
-                    if (kept<K, PK>(n, t)) {
-                        const double w = o[(DIRY ? kept_index<K, PK>(t, n) : kept_index<K, PK>(n, t)) * NCELL];
-                        r[t] = n == dn ? mul_c(tb.e0[dn][n], w) : mad_c(tb.e0[dn][n], w, r[t]);
-                    }
-                // (the modes n of one derivative have one parity)
-                if ((dn & 1) || (t & 1)) r[t] = flip_sign(r[t], ((dn & 1) ? fn : 0u) ^ ((t & 1) ? ft : 0u));
-            }
-#pragma unroll
-            for (int t = 0; t < K1; ++t) {
-                D[dn][t] = 0.0;
-                if (!kept<K, PK>(dn, t)) continue;
-                double x = 0.0;                  // own trace at the edge
+                double ev = 0.0, od = 0.0;       // even and odd normal modes
+                bool e0 = true, o0 = true;
 #pragma unroll
                 for (int n = dn; n < K1; ++n) {
                     if (!kept<K, PK>(n, t)) continue;
-                    const bool fl = (n & 1) || (t & 1);
-                    const double v = fl ? flip_sign(u[n][t], ((n & 1) ? fn : 0u) ^ ((t & 1) ? ft : 0u)) : u[n][t];
-                    x = n == dn ? mul_c(tb.e1[dn][n], v) : mad_c(tb.e1[dn][n], v, x);
+                    if (n & 1) od = o0 ? mul_c(tb.e1[dn][n], u[n][t]) : mad_c(tb.e1[dn][n], u[n][t], od), o0 = false;
+                    else ev = e0 ? mul_c(tb.e1[dn][n], u[n][t]) : mad_c(tb.e1[dn][n], u[n][t], ev), e0 = false;
                 }
-#pragma unroll
-                for (int j = t; j < K1; ++j)
-                    if (kept<K, PK>(dn, j)) x = j == t ? x - r[j] : fma(r[j], -tb.sh[1][j][t], x);
-                D[dn][t] = dn == 0 ? x : x * kap[dn];
+                const double x = o0 ? ev : (e0 ? flip_sign(od, fn) : ev + flip_sign(od, fn));
+                own[dn][t] = dn == 0 ? x : x * kap[dn];
             }
         }
 #pragma unroll
-        for (int g = 0; g < Q; ++g)
+        for (int half = 0; half < 2; ++half) {
+            const double *o = oth + side * sn + half * st;
+            double D[K1][K1];                    // the traces' difference, own coordinate
 #pragma unroll
-            for (int m = 0; m < K1; ++m) {
-                double ss = SQRT_TINY;
+            for (int dn = 0; dn < K1; ++dn) {
+                double r[K1];                    // derivative dn of the other trace at its centre line
 #pragma unroll
-                for (int dn = 0; dn <= m; ++dn) {
-                    const int dt = m - dn;
-                    double v = 0.0;
-                    bool first = true;
+                for (int t = 0; t < K1; ++t) {
+                    r[t] = 0.0;
+                    if (!kept<K, PK>(dn, t)) continue;
 #pragma unroll
-                    for (int t = dt; t < K1; ++t)
-                        if (kept<K, PK>(dn, t) && tb.own[dt][1][g][t] != 0.0) {
-                            const double c = tb.own[dt][1][g][t];
-                            v = first ? mul_c(c, D[dn][t]) : mad_c(c, D[dn][t], v);
-                            first = false;
+                    for (int n = dn; n < K1; n += 2)                  // (one parity)
+                        if (kept<K, PK>(n, t)) {
+                            const double w = o[(DIRY ? kept_index<K, PK>(t, n) : kept_index<K, PK>(n, t)) * NCELL];
+                            r[t] = n == dn ? mul_c(tb.e0[dn][n], w) : mad_c(tb.e0[dn][n], w, r[t]);
                         }
-                    ss = m == 0 ? fabs(v) : fma(v, v, ss);
+                    if (dn > 0) r[t] *= ks[dn];
                 }
-                acc[m] = fma(tb.w[g], m == 0 ? ss : sqrt_nr(ss), acc[m]);   // |d| = (d^2)^(1/2) for m = 0
+#pragma unroll
+                for (int t = 0; t < K1; ++t) {
+                    double x = own[dn][t];
+#pragma unroll
+                    for (int j = t; j < K1; ++j)
+                        if (kept<K, PK>(dn, j)) x = j == t ? x - r[j] : fma(r[j], -tb.sh[half][j][t], x);
+                    D[dn][t] = x;
+                }
             }
+#pragma unroll
+            for (int g = 0; g < Q; ++g)
+#pragma unroll
+                for (int m = 0; m < K1; ++m) {
+                    double ss = tiny;
+#pragma unroll
+                    for (int dn = 0; dn <= m; ++dn) {
+                        const int dt = m - dn;
+                        double v = 0.0;
+                        bool first = true;
+#pragma unroll
+                        for (int t = dt; t < K1; ++t)
+                            if (kept<K, PK>(dn, t) && tb.own[dt][half][g][t] != 0.0) {
+                                const double c = tb.own[dt][half][g][t];
+                                v = first ? mul_c(c, D[dn][t]) : mad_c(c, D[dn][t], v);
+                                first = false;
+                            }
+                        ss = m == 0 ? fabs(v) : fma(v, v, ss);
+                    }
+                    acc[m] = fma(tb.w[g], m == 0 ? ss : sqrt_nr(ss), acc[m]);   // |d| = (d^2)^(1/2) for m = 0
+                }
+            __builtin_amdgcn_sched_barrier(0);   // one half-edge at a time: bounds the live registers
+        }
     }
 #pragma unroll
     for (int m = 1; m < K1; ++m) acc[m] *= sct[m];
