@@ -202,7 +202,7 @@ struct Stage2Args {
     const double *inC, *inD;      // tile input (pre-damping, or damped when damp == 0)
     double *outC, *outD;          // stage output (undamped) or damped state (final mode)
     double *UC, *UD;              // damped u^n: written at stage 0 (write_u), read at stages 1, 2
-    double *part;                 // partial statistics, one record (Rec2) per tile
+    double *part;                 // partial statistics, a record (Rec2) per wave of primal and of dual cells
     double *numC, *numD;          // damping numerators [m*NC + q][ny][nx]: written by k_delta2d, read by k_stage2d
     double *AC, *AD;              // classical RK4: weighted sum of the damped inputs of stages 1 and 2
     const Stats2 *st;
@@ -396,6 +396,13 @@ struct Halo2 {
     static constexpr int W = TX + 1, H = TY + 1, N = W * H;
 };
 
+// Doubles of a cell in LDS: its entries one after another (an entry is then at a
+// constant offset from the cell's address), to an odd stride, which spreads the
+// cells of a wave over the banks.
+__host__ __device__ constexpr int lds_stride(int ne) { return ne | 1; }
+// Threads of a stage workgroup: whole waves of primal and of dual cells.
+__host__ __device__ constexpr int mesh_threads(int tx, int ty) { return (tx * ty + 63) / 64 * 64; }
+
 // Table entries of Gauss node p of the upper half, for a loop over the nodes.
 template <int K>
 struct NodeTab {
@@ -426,7 +433,7 @@ __device__ inline NodeTab<K> node_tab(int p) { return node_tabs<K>.t[p]; }
 
 // Coupling and volume terms of eq:2D_H for one owned cell: R[q][a][b] = their
 // integral against P_a P_b (own-cell part of the coupling left to the caller),
-// from the damped cells of the other mesh in LDS (oth, [entry][cell]).
+// from the damped cells of the other mesh in LDS (oth, lds_stride apart).
 //
 // A quadrant (sx, sy) is evaluated in its mirror image on the upper right one.
 // With P_n(-x) = (-1)^n P_n(x) and the symmetric Gauss rule, mirroring x turns a
@@ -439,7 +446,7 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
                                 double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NM = kept_modes<K, PK>();
-    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N;
+    constexpr int W = Halo2<TX, TY>::W, LS = lds_stride(NC * NM);
     constexpr Tab2<K> tb = make_tab2<K>();
     const double hx = a.hx, hy = a.hy;
     const double sxx = 2.0 / hx, syy = 2.0 / hy, area = hx * hy / 16.0;
@@ -469,7 +476,7 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
                     const bool ox = (i & 1) != (int)vecx(q), oy = (j & 1) != (int)vecy(q);
                     if (ox || oy) R[q][i][j] = flip_sign(R[q][i][j], (ox ? cx : 0u) ^ (oy ? cy : 0u));
                 }
-        const double *o = oth + (r + sy) * W + s + sx;
+        const double *o = oth + ((r + sy) * W + s + sx) * LS;
         FPar2 fp = a.fp;
         if constexpr (NC == 1) {                 // advection: the mirrored velocity
             fp.a = flip_sign(fp.a, mx);
@@ -484,7 +491,7 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
                 for (int e = 0; e < K1; ++e) {
                     d[q][c][e] = 0.0;
                     if (!kept<K, PK>(c, e)) continue;
-                    const double x = o[(q * NM + kept_index<K, PK>(c, e)) * NCELL];
+                    const double x = o[q * NM + kept_index<K, PK>(c, e)];
                     const bool ox = (c & 1) != (int)vecx(q), oy = (e & 1) != (int)vecy(q);
                     d[q][c][e] = (ox || oy) ? flip_sign(x, (ox ? mx : 0u) ^ (oy ? my : 0u)) : x;
                 }
@@ -556,34 +563,35 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
 }
 
 // Edge terms of eq:2D_H added to R: f_dir of the other mesh on its centre line
-// along each half-edge of direction dir, mirrored onto the upper half of the E (N)
-// edge as above.
+// along each half-edge of direction dir; the W (S) edge is mirrored onto the E (N)
+// edge as above, the halves have tables of their own.
 template <int K, int FLUX, int TX, int TY, bool PK>
 __device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, int r,
                                double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NM = kept_modes<K, PK>();
-    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N;
+    constexpr int W = Halo2<TX, TY>::W, LS = lds_stride(NC * NM);
     constexpr Tab2<K> tb = make_tab2<K>();
 #pragma unroll
     for (int dir = 0; dir < 2; ++dir) {
         constexpr auto vecn = [](int dr, int q) { return NC == 4 && q == 1 + dr; };   // momentum normal to the edge
-        constexpr auto vect = [](int dr, int q) { return NC == 4 && q == 2 - dr; };   // and along it
         const double ht = -0.25 * (dir ? a.hx : a.hy);
 #pragma unroll 1
         for (int side = 0; side < 2; ++side) {
             const unsigned fn = side ? 0u : 0x80000000u;
+            FPar2 fp = a.fp;
+            if constexpr (NC == 1) {
+                fp.a = flip_sign(fp.a, fn);
+                fp.b = flip_sign(fp.b, fn);
+            }
             double Y[NC][K1];
 #pragma unroll
             for (int q = 0; q < NC; ++q)
 #pragma unroll
                 for (int t = 0; t < K1; ++t) Y[q][t] = 0.0;
-#pragma unroll 1
+#pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const unsigned ft = h ? 0u : 0x80000000u;
-                const double *o = oth + (dir ? (r + side) * W + s + h : (r + h) * W + s + side);
-                // into the frame of this half: the odd Y_t (and of the momentum along the edge the even ones)
-                const unsigned cross = h ? 0x80000000u : 0u;
+                const double *o = oth + (dir ? (r + side) * W + s + h : (r + h) * W + s + side) * LS;
                 double l[NC][K1];
 #pragma unroll
                 for (int q = 0; q < NC; ++q)
@@ -593,19 +601,11 @@ __device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, in
 #pragma unroll
                         for (int n = 0; n < K1; n += 2) {             // P_n(0) = 0 for odd n
                             if (!kept<K, PK>(t, n)) continue;
-                            const int m = dir ? kept_index<K, PK>(t, n) : kept_index<K, PK>(n, t);
-                            const double x = o[(q * NM + m) * NCELL];
+                            const double x = o[q * NM + (dir ? kept_index<K, PK>(t, n) : kept_index<K, PK>(n, t))];
                             sum = n == 0 ? x : fma(x, tb.e0[0][n], sum);
                         }
-                        const bool on = vecn(dir, q), ot = (t & 1) != (int)vect(dir, q);
-                        l[q][t] = (on || ot) ? flip_sign(sum, (on ? fn : 0u) ^ (ot ? ft : 0u)) : sum;
-                        if (ot) Y[q][t] = flip_sign(Y[q][t], cross);
+                        l[q][t] = vecn(dir, q) ? flip_sign(sum, fn) : sum;
                     }
-                FPar2 fp = a.fp;
-                if constexpr (NC == 1) {
-                    fp.a = flip_sign(fp.a, fn);
-                    fp.b = flip_sign(fp.b, fn);
-                }
 #pragma unroll
                 for (int g = 0; g < Q; ++g) {
                     double w[NC], f[NC];
@@ -613,7 +613,7 @@ __device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, in
                     for (int q = 0; q < NC; ++q) {
                         double t = l[q][0];
 #pragma unroll
-                        for (int e = 1; e < K1; ++e) t = fma(l[q][e], tb.nb[0][1][g][e], t);
+                        for (int e = 1; e < K1; ++e) t = fma(l[q][e], tb.nb[0][h][g][e], t);
                         w[q] = t;
                     }
                     F::one(dir, w, f, fp);
@@ -621,8 +621,9 @@ __device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, in
                     for (int q = 0; q < NC; ++q)
 #pragma unroll
                         for (int t = 0; t < K1; ++t)
-                            Y[q][t] = fma(tb.w[g] * tb.own[0][1][g][t], f[q], Y[q][t]);
+                            Y[q][t] = fma(tb.w[g] * tb.own[0][h][g][t], f[q], Y[q][t]);
                 }
+                __builtin_amdgcn_sched_barrier(0);   // one half-edge at a time: bounds the live registers
             }
             // P_n(1) = 1; out of the frame of the side
 #pragma unroll
@@ -643,13 +644,12 @@ __device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, in
 }
 
 // One RK stage (see the top of the file).
-template <int K, int FLUX, int TX, int TY, bool PK>
-__global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3 && !PK ? 3 : 4)) void k_stage2d(Stage2Args a) {
+template <int K, int FLUX, int TX, int TY, int WPS, bool PK>
+__global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage2Args a) {
     using F = Flux2D<FLUX>;
-    constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>(), NE = NC * NM;
-    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, NT = 2 * TX * TY;
-    static_assert((TX * TY) % WAVE == 0, "a wave holds cells of one mesh");
-    __shared__ double tile[2 * NE * NCELL];      // [mesh][entry][cell], damped
+    constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>(), NE = NC * NM, LS = lds_stride(NE);
+    constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, MT = mesh_threads(TX, TY), NT = 2 * MT;
+    __shared__ double tile[2 * NCELL * LS];      // [mesh][cell][entry], damped
 
     const int tid = threadIdx.x;
     const int tileid = tile_of_block(a.ntx * a.nty);
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3
     // the tile's cells into LDS, damped on the way: a cell of either mesh per
     // thread, and the cells beyond the threads shared by the waves, PART entries
     // each.  Every load is issued before the first wait.
-    constexpr int REST = 2 * NCELL - NT, PARTS = NC == 4 ? 2 : 1, PART = NE / PARTS;
+    constexpr int REST = 2 * NCELL - NT, PARTS = NC == 4 ? (NT >= 4 * WAVE ? 4 : 2) : 1, PART = NE / PARTS;
     static_assert(REST > 0 && REST <= WAVE && NT / WAVE >= PARTS, "one more cell per lane");
     const bool small = a.nx <= TX || a.ny <= TY;
     const int wave = tid / WAVE, lane = tid % WAVE;
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3
     };
     const Cell c0 = cell_of(tid), c1 = cell_of(NT + (lane < REST ? lane : 0));
     const bool more = lane < REST && wave < PARTS;
-    const int q1 = PARTS == 2 ? wave * (NC / 2) : 0;         // first component of this wave's part
+    const int q1 = more ? wave * (NC / PARTS) : 0;           // first component of this wave's part
     double v0[NE], v1[PART], n0[K1 * NC], n1[K1 * NC];
     {
         const double *p = (c0.mesh ? a.inD : a.inC) + c0.g;
@@ -718,9 +718,9 @@ __global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3
                         if (kept<K, PK>(i, j) && i + j > 0)
                             v0[q * NM + kept_index<K, PK>(i, j)] *= f[(i + j < K ? i + j : K) - 1];
         }
-        double *o = tile + c0.mesh * NE * NCELL + c0.cell;
+        double *o = tile + (c0.mesh * NCELL + c0.cell) * LS;
 #pragma unroll
-        for (int e = 0; e < NE; ++e) o[e * NCELL] = v0[e];
+        for (int e = 0; e < NE; ++e) o[e] = v0[e];
     }
     if (more) {
         double f[K];
@@ -735,21 +735,22 @@ __global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3
                         if (kept<K, PK>(i, j) && i + j > 0)
                             v1[q * NM + kept_index<K, PK>(i, j)] *= f[(i + j < K ? i + j : K) - 1];
         }
-        double *o = tile + (c1.mesh * NE + q1 * NM) * NCELL + c1.cell;
+        double *o = tile + (c1.mesh * NCELL + c1.cell) * LS + q1 * NM;
 #pragma unroll
-        for (int e = 0; e < PART; ++e) o[e * NCELL] = v1[e];
+        for (int e = 0; e < PART; ++e) o[e] = v1[e];
     }
     __syncthreads();
 
-    // owned cells: the first half of the threads primal, the second dual
-    const int mesh = tid >= TX * TY, rr = tid - mesh * TX * TY;
+    // owned cells: the first half of the threads primal, the second dual (threads
+    // beyond the tile's cells take cell 0 along and store nothing)
+    const int mesh = tid >= MT, rr = tid - mesh * MT < TX * TY ? tid - mesh * MT : 0;
     const int s = rr % TX, r = rr / TX;
     const int gx = i0 + s, gy = j0 + r;
-    const bool valid = gx < a.nx && gy < a.ny;
+    const bool valid = tid - mesh * MT < TX * TY && gx < a.nx && gy < a.ny;
     const long long gofs = valid ? (long long)gy * a.nx + gx : 0;
-    const double *own = tile + mesh * NE * NCELL + (r + 1 - mesh) * W + s + 1 - mesh;
+    const double *own = tile + (mesh * NCELL + (r + 1 - mesh) * W + s + 1 - mesh) * LS;
     const double itm = 1.0 / st->tau_max, tau = st->tau;
-    const double *oth = tile + (1 - mesh) * NE * NCELL;
+    const double *oth = tile + (1 - mesh) * NCELL * LS;
     double R[NC][K1][K1];
     volume2d<K, FLUX, TX, TY, PK>(a, oth, s, r, itm, R);
     // u^n, asked for before the edges, which leave the registers for it
@@ -799,7 +800,7 @@ __global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3
                     if (valid) *po = 0.0;
                     continue;
                 }
-                const double s0 = own[(q * NM + kept_index<K, PK>(i, j)) * NCELL];
+                const double s0 = own[q * NM + kept_index<K, PK>(i, j)];
                 const double Lv = fma(R[q][i][j], (2.0 * i + 1.0) * (2.0 * j + 1.0) * im, -itm * s0);
                 const double o = fma(cn, base[q][i][j], fma(td, Lv, a.rs.cw * s0));
                 bad = fma(o, 0.0, bad);
@@ -816,7 +817,7 @@ __global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3
             for (int i = 0; i < K1; ++i)
 #pragma unroll
                 for (int j = 0; j < K1; ++j, p += a.plane) {
-                    const double s0 = kept<K, PK>(i, j) ? own[(q * NM + kept_index<K, PK>(i, j)) * NCELL] : 0.0;
+                    const double s0 = kept<K, PK>(i, j) ? own[q * NM + kept_index<K, PK>(i, j)] : 0.0;
                     if (a.write_u) *p = s0;
                     else *p = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, *p);
                 }
@@ -828,7 +829,7 @@ __global__ __launch_bounds__(2 * TX * TY, FLUX == OECDG_FLUX_EULER ? 2 : (K == 3
         for (int i = 0; i < K1; ++i)
 #pragma unroll
             for (int j = 0; j < K1; ++j) m[i][j] = R[q][i][j];
-    }, a.part + (long long)tileid * Rec2<NC>::N);
+    }, a.part + ((long long)tileid * (MT / WAVE) + tid % MT / WAVE) * Rec2<NC>::N);
 }
 
 // Statistics of given data (a run's initial data, oecdg_dt): a record per 64 cells.
@@ -1222,47 +1223,56 @@ __global__ __launch_bounds__(RED2_NT) void k_reduce2d(Red2Args r) {
 
 namespace {
 
-// Tiles in primal cells.  k_stage2d: 16 x 4 (full 128-byte lines of a row, 49 KB
-// of LDS for Euler at k = 2: three workgroups per CU), 8 x 8 would read 64-byte
-// pieces; one thread per cell.  k_delta2d: 16 x 16 of one component.
-template <int K, int FLUX> struct Tile2 {
-    static constexpr int TX = 16, TY = 4, DX = 16, DY = 16;
+// Tiles of k_stage2d in primal cells and waves per SIMD asked for.  Rows of 16 cells
+// are whole 128-byte lines.  The Euler tiles are the largest of which two fit the
+// 160 KB of LDS (2 x 80.5 KB for Q2 at 16 x 7: eight waves per CU and a halo of
+// 1.21 cells per owned one; three of 16 x 4 left six waves on four SIMDs at 1.33,
+// and 8 x 4, a wave each, measured the same or slower in every space).  Q3 needs
+// 74.9 KB for 8 x 7, four waves per CU.  k_delta2d takes 16 x 16 of one component.
+template <int K, int FLUX, bool PK> struct Tile2 {
+    static constexpr bool EULER = FLUX == OECDG_FLUX_EULER;
+    static constexpr int TX = EULER && K == 3 && !PK ? 8 : 16;
+    static constexpr int TY = !EULER || K == 1 ? 4 : (K == 3 ? (PK ? 4 : 7) : (PK ? 8 : 7));
+    static constexpr int WPS = !EULER ? (K == 3 && !PK ? 3 : 4) : (K == 3 ? 1 : (K == 1 ? 4 : 2));
+};
+constexpr int DELTA_T = 16;
+struct Tiles2 {
+    int tx, ty;
 };
 
 // which: 0 stage, 1 delta, 2 damp, 3 statistics of given data
 template <int K, int FLUX, bool PK>
-void *kernel2d_fn(int which) {
-    using T = Tile2<K, FLUX>;
-    if (which == 1) return (void *)k_delta2d<K, FLUX, T::DX, T::DY, PK>;
+void *kernel2d_fn(int which, Tiles2 &t) {
+    using T = Tile2<K, FLUX, PK>;
+    t = {T::TX, T::TY};
+    if (which == 1) return (void *)k_delta2d<K, FLUX, DELTA_T, DELTA_T, PK>;
     if (which == 2) return (void *)k_damp2d<K, FLUX, PK>;
     if (which == 3) return (void *)k_stats2d<K, FLUX, PK>;
-    return (void *)k_stage2d<K, FLUX, T::TX, T::TY, PK>;
+    return (void *)k_stage2d<K, FLUX, T::TX, T::TY, T::WPS, PK>;
 }
 
 template <int K>
-void *pick2_k(int flux, bool pk, int which) {
+void *pick2_k(int flux, bool pk, int which, Tiles2 &t) {
     if (flux == OECDG_FLUX_EULER)
-        return pk ? kernel2d_fn<K, OECDG_FLUX_EULER, true>(which) : kernel2d_fn<K, OECDG_FLUX_EULER, false>(which);
-    return pk ? kernel2d_fn<K, OECDG_FLUX_ADVECTION, true>(which) : kernel2d_fn<K, OECDG_FLUX_ADVECTION, false>(which);
+        return pk ? kernel2d_fn<K, OECDG_FLUX_EULER, true>(which, t) : kernel2d_fn<K, OECDG_FLUX_EULER, false>(which, t);
+    return pk ? kernel2d_fn<K, OECDG_FLUX_ADVECTION, true>(which, t)
+              : kernel2d_fn<K, OECDG_FLUX_ADVECTION, false>(which, t);
 }
 
-void *pick2(int k, int flux, bool pk, int which) {
+// Kernel of a kind, and the stage kernel's tile.
+void *pick2(int k, int flux, bool pk, int which, Tiles2 &t) {
     switch (k) {
-    case 1: return pick2_k<1>(flux, pk, which);
-    case 2: return pick2_k<2>(flux, pk, which);
-    default: return pick2_k<3>(flux, pk, which);
+    case 1: return pick2_k<1>(flux, pk, which, t);
+    case 2: return pick2_k<2>(flux, pk, which, t);
+    default: return pick2_k<3>(flux, pk, which, t);
     }
 }
-
-struct Tiles2 {
-    int tx, ty, dx, dy;
-};
-Tiles2 tiles2(int, int) { return {16, 4, 16, 16}; }
 
 struct Ext2D {
     int k, nc, flux, oe;
     int pk;                      // total-degree space P^k
-    Tiles2 t;                    // primal cells per tile and direction
+    Tiles2 t;                    // k_stage2d: primal cells per tile and direction
+    void *fn[4];                 // kernels (pick2)
     int rk, ns;                  // RK method (rk_stage) and its stages per step
     int nx, ny;
     int ntx, nty;                // k_stage2d's tiles
@@ -1296,7 +1306,7 @@ hipError_t launch_stage2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
     copy.ntx = x.ntx;
     copy.nty = x.nty;
     void *args[] = {&copy};
-    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 0), dim3(x.ntx * x.nty), dim3(2 * x.t.tx * x.t.ty), args, 0, s);
+    return hipLaunchKernel(x.fn[0], dim3(x.ntx * x.nty), dim3(2 * mesh_threads(x.t.tx, x.t.ty)), args, 0, s);
 }
 
 // Workgroups of the reduction of nrec records: enough for a few rounds of loads
@@ -1317,8 +1327,8 @@ hipError_t launch_delta2d(const Ext2D &x, const Stage2Args &a, const Red2Args *r
     }
     if (x.oe && x.k > 0) {
         void *args[] = {&copy, &r};
-        return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 1), dim3(copy.nred + delta_blocks(x.dtx * x.dty) * x.nc),
-                               dim3(x.t.dx * x.t.dy), args, 0, s);
+        return hipLaunchKernel(x.fn[1], dim3(copy.nred + delta_blocks(x.dtx * x.dty) * x.nc),
+                               dim3(DELTA_T * DELTA_T), args, 0, s);
     }
     if (!red) return hipSuccess;
     void *args[] = {&r};
@@ -1336,13 +1346,13 @@ hipError_t launch_reduce2d(const Ext2D &x, const Red2Args &red, hipStream_t s) {
 hipError_t launch_stats2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
     Stage2Args copy = a;
     void *args[] = {&copy};
-    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 3), dim3((unsigned)((a.plane + 255) / 256)), dim3(256), args, 0, s);
+    return hipLaunchKernel(x.fn[3], dim3((unsigned)((a.plane + 255) / 256)), dim3(256), args, 0, s);
 }
 
 hipError_t launch_damp2d(const Ext2D &x, const Stage2Args &a, hipStream_t s) {
     Stage2Args copy = a;
     void *args[] = {&copy};
-    return hipLaunchKernel(pick2(x.k, x.flux, x.pk, 2), dim3((unsigned)((a.plane + 255) / 256), 2), dim3(256), args, 0, s);
+    return hipLaunchKernel(x.fn[2], dim3((unsigned)((a.plane + 255) / 256), 2), dim3(256), args, 0, s);
 }
 
 Stage2Args stage_args(const Ext2D &x) {
@@ -1364,8 +1374,8 @@ Stage2Args stage_args(const Ext2D &x) {
     return a;
 }
 
-// Records of a stage's output: one per tile of k_stage2d; of given data: one per 64 cells.
-int stage_records(const Ext2D &x) { return x.ntx * x.nty; }
+// Records of a stage's output: one per wave of primal cells of k_stage2d; of given data: one per 64 cells.
+int stage_records(const Ext2D &x) { return x.ntx * x.nty * (mesh_threads(x.t.tx, x.t.ty) / WAVE); }
 int data_records(const Ext2D &x) { return (int)(((long long)x.nx * x.ny + 63) / 64); }
 
 // gpar: parity of the stage that the result is for.
@@ -1440,13 +1450,13 @@ int create_2d(oecdg_handle *h, const oecdg_desc *d) {
     x->pk = d->space == 1;
     x->nx = (int)d->nx;
     x->ny = (int)d->ny;
-    x->t = tiles2(x->k, x->flux);
+    for (int i = 0; i < 4; ++i) x->fn[i] = pick2(x->k, x->flux, x->pk, i, x->t);
     x->rk = d->rk == 0 ? 3 : d->rk;
     x->ns = rk_stages(x->rk);
     x->ntx = (x->nx + x->t.tx - 1) / x->t.tx;
     x->nty = (x->ny + x->t.ty - 1) / x->t.ty;
-    x->dtx = (x->nx + x->t.dx - 1) / x->t.dx;
-    x->dty = (x->ny + x->t.dy - 1) / x->t.dy;
+    x->dtx = (x->nx + DELTA_T - 1) / DELTA_T;
+    x->dty = (x->ny + DELTA_T - 1) / DELTA_T;
     x->hx = (d->xhi - d->xlo) / d->nx;
     x->hy = (d->yhi - d->ylo) / d->ny;
     x->cfl = d->cfl;
