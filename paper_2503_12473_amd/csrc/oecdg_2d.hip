@@ -201,13 +201,14 @@ struct Stage2Args {
     FPar2 fp;
     const double *inC, *inD;      // tile input (pre-damping, or damped when damp == 0)
     double *outC, *outD;          // stage output (undamped) or damped state (final mode)
-    double *UC, *UD;              // damped u^n: written at stage 0 (write_u), read at stages 1, 2
+    const double *unC, *unD;      // u^n as the step's first stage read it (stages l > 0)
+    double *facC, *facD;          // its damping factors [K][ny][nx]: written at stage 0, read later (null: undamped)
     double *part;                 // partial statistics, a record (Rec2) per wave of primal and of dual cells
     double *numC, *numD;          // damping numerators [m*NC + q][ny][nx]: written by k_delta2d, read by k_stage2d
     double *AC, *AD;              // classical RK4: weighted sum of the damped inputs of stages 1 and 2
     const Stats2 *st;
     int *err;                     // [0] non-finite, [1] non-physical, [2] no admissible step
-    int l, gpar, damp, write_u;   // stage, parity of the stage index (st->done)
+    int l, gpar, damp;            // stage, parity of the stage index (st->done), OE on the input
     int nred;                     // k_delta2d: leading workgroups that reduce the statistics (reduce2d)
     RKStage rs;                   // c/d coefficients of stage l of the RK method (eq:RKCDG)
 };
@@ -753,9 +754,16 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
     const double *oth = tile + (1 - mesh) * NCELL * LS;
     double R[NC][K1][K1];
     volume2d<K, FLUX, TX, TY, PK>(a, oth, s, r, itm, R);
-    // u^n, asked for before the edges, which leave the registers for it
-    double *UM = (mesh ? a.UD : a.UC) + gofs, *OM = (mesh ? a.outD : a.outC) + gofs, *AM = (mesh ? a.AD : a.AC) + gofs;
-    double base[NC][K1][K1];                     // u^n
+    // u^n and its factors, asked for before the edges, which leave the registers for
+    // them.  The undamped u^n is still there (the last stage overwrites it, each
+    // cell by its own thread) and is damped again: K factors are stored instead of
+    // the damped state.
+    const double *UM = (mesh ? a.unD : a.unC) + gofs;
+    double *OM = (mesh ? a.outD : a.outC) + gofs, *AM = (mesh ? a.AD : a.AC) + gofs;
+    double *FM = a.facC ? (mesh ? a.facD : a.facC) + gofs : nullptr;
+    double base[NC][K1][K1], fn[K];              // u^n
+#pragma unroll
+    for (int j = 0; j < K; ++j) fn[j] = 1.0;
 #pragma unroll
     for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -771,9 +779,22 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
 #pragma unroll
                 for (int j = 0; j < K1; ++j, p += a.plane)
                     if (kept<K, PK>(i, j)) base[q][i][j] = *p;
+        if (FM) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) fn[j] = FM[j * a.plane];
+        }
     }
     edges2d<K, FLUX, TX, TY, PK>(a, oth, s, r, R);
     double cn = a.rs.cn;
+    if (FM && a.l > 0) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int i = 0; i < K1; ++i)
+#pragma unroll
+                for (int j = 0; j < K1; ++j)
+                    if (kept<K, PK>(i, j) && i + j > 0) base[q][i][j] *= fn[(i + j < K ? i + j : K) - 1];
+    }
     if (a.rs.acc_read) {                         // classical RK4's last stage: the accumulated earlier stages
         const double *p = AM;
 #pragma unroll
@@ -808,9 +829,8 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
                 R[q][i][j] = o;
             }
     if (valid && !(bad == 0.0)) a.err[0] = 1;
-    // damped input: u^n of the step, and classical RK4's sum of the stages that its last one needs
-    if (valid && (a.write_u || a.rs.ca != 0.0)) {
-        double *p = a.write_u ? UM : AM;
+    if (valid && a.rs.ca != 0.0) {               // classical RK4: the sum of the damped inputs that its last stage needs
+        double *p = AM;
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -818,9 +838,15 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
 #pragma unroll
                 for (int j = 0; j < K1; ++j, p += a.plane) {
                     const double s0 = kept<K, PK>(i, j) ? own[q * NM + kept_index<K, PK>(i, j)] : 0.0;
-                    if (a.write_u) *p = s0;
-                    else *p = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, *p);
+                    *p = a.rs.acc_first ? a.rs.ca * s0 : fma(a.rs.ca, s0, *p);
                 }
+    }
+    if (valid && FM && a.l == 0) {               // the factors of the step's input, for its later stages
+        double nv[K1 * NC];
+        load_numerators<K, NC>(mesh ? a.numD : a.numC, a.plane, gofs, nv);
+        damp_factors<K, NC>(nv, st->isig[mesh], st->tau_damp, fn);
+#pragma unroll
+        for (int j = 0; j < K; ++j) FM[j * a.plane] = fn[j];
     }
     // Statistics of the output, from registers: this kernel waits on memory
     // where k_delta2d, which had them, is bound by VALU issue.
@@ -1281,10 +1307,10 @@ struct Ext2D {
     FPar2 fp;
     long long S1;                // doubles of one mesh
     long long SN;                // damping numerators of one mesh: (k+1) nc nx ny
-    double *B[2] = {nullptr, nullptr};      // stage states, both meshes each
+    double *B[3] = {nullptr, nullptr, nullptr};   // stage states, both meshes each (run_2d)
     double *num[2] = {nullptr, nullptr};    // damping numerators of B[i], both meshes each
-    double *U = nullptr;
     double *A = nullptr;         // classical RK4: accumulated damped inputs of stages 1 and 2 (both meshes)
+    double *fac = nullptr;       // damping factors of the step's input, K per cell (both meshes)
     double *part[2] = {nullptr, nullptr};
     double *fold = nullptr;      // first-level records of the reduction
     unsigned *count = nullptr;   // its arrival count
@@ -1467,12 +1493,12 @@ int create_2d(oecdg_handle *h, const oecdg_desc *d) {
     x->SN = (long long)x->nc * (x->k + 1) * x->nx * x->ny;
     const size_t nval = x->nc == 4 ? Rec2<4>::N : Rec2<1>::N;   // doubles of a record
     const size_t nrec = std::max(stage_records(*x), data_records(*x));
+    for (int i = 0; i < (x->ns > 2 ? 3 : 2); ++i) HIPCHK2(h, hipMalloc(&x->B[i], sizeof(double) * 2 * x->S1));
+    HIPCHK2(h, hipMalloc(&x->fac, sizeof(double) * 2 * x->k * x->nx * x->ny));
     for (int i = 0; i < 2; ++i) {
-        HIPCHK2(h, hipMalloc(&x->B[i], sizeof(double) * 2 * x->S1));
         HIPCHK2(h, hipMalloc(&x->num[i], sizeof(double) * 2 * x->SN));
         HIPCHK2(h, hipMalloc(&x->part[i], sizeof(double) * nval * nrec));
     }
-    HIPCHK2(h, hipMalloc(&x->U, sizeof(double) * 2 * x->S1));
     if (x->rk == 4) HIPCHK2(h, hipMalloc(&x->A, sizeof(double) * 2 * x->S1));
     HIPCHK2(h, hipMalloc(&x->fold, sizeof(double) * nval * RED2_MAXB));
     HIPCHK2(h, hipMalloc(&x->count, sizeof(unsigned)));
@@ -1487,12 +1513,13 @@ int create_2d(oecdg_handle *h, const oecdg_desc *d) {
 void destroy_2d(oecdg_handle *h) {
     Ext2D *x = ext(h);
     if (!x) return;
+    for (double *b : x->B)
+        if (b) (void)hipFree(b);
+    if (x->fac) (void)hipFree(x->fac);
     for (int i = 0; i < 2; ++i) {
-        if (x->B[i]) (void)hipFree(x->B[i]);
         if (x->num[i]) (void)hipFree(x->num[i]);
         if (x->part[i]) (void)hipFree(x->part[i]);
     }
-    if (x->U) (void)hipFree(x->U);
     if (x->A) (void)hipFree(x->A);
     if (x->fold) (void)hipFree(x->fold);
     if (x->count) (void)hipFree(x->count);
@@ -1534,11 +1561,10 @@ int stage_2d(oecdg_handle *h, int stage, double dt, double tau_max, const double
     a.l = stage;
     a.rs = rk_stage(x.rk, stage);
     a.damp = 0;
-    a.write_u = 0;
     a.inC = stage == 0 ? uCn : uCl;
     a.inD = stage == 0 ? uDn : uDl;
-    a.UC = const_cast<double *>(uCn);
-    a.UD = const_cast<double *>(uDn);
+    a.unC = uCn;
+    a.unD = uDn;
     a.outC = x.B[0];
     a.outD = x.B[0] + x.S1;
     HIPCHK2(h, launch_stage2d(x, a, s));
@@ -1563,18 +1589,6 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
     if (nsteps < 0 && !std::isfinite(t_end)) return handle_fail(h, OECDG_EINVAL, "give a finite t_end or nsteps >= 0");
     int rc = reset2d(h, x);
     if (rc != OECDG_OK) return rc;
-    HIPCHK2(h, hipMemcpyAsync(x.B[0], uC, sizeof(double) * x.S1, hipMemcpyDeviceToDevice, s));
-    HIPCHK2(h, hipMemcpyAsync(x.B[0] + x.S1, uD, sizeof(double) * x.S1, hipMemcpyDeviceToDevice, s));
-    if (x.pk) {   // P^k: the modes of total degree above k are not part of the state
-        const long long plane = (long long)x.nx * x.ny;
-        for (int mesh = 0; mesh < 2; ++mesh)
-            for (int q = 0; q < x.nc; ++q)
-                for (int i = 0; i <= x.k; ++i)
-                    for (int j = 0; j <= x.k; ++j)
-                        if (i + j > x.k)
-                            HIPCHK2(h, hipMemsetAsync(x.B[0] + mesh * x.S1 + ((q * (x.k + 1) + i) * (x.k + 1) + j) * plane,
-                                                      0, sizeof(double) * plane, s));
-    }
     // statistics of the initial data, and from them the first step
     auto reduction = [&](const double *part, int nrec, long long g, int mode) {   // for stage g of the run
         Red2Args r = red_args(x, part, nrec, mode, (int)(g & 1));
@@ -1582,8 +1596,16 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
         r.dt_fixed = dt_fixed;
         return r;
     };
-    HIPCHK2(h, stats_of(x, x.B[0], x.B[0] + x.S1, 0, s));
+    HIPCHK2(h, stats_of(x, uC, uD, 0, s));
     if (nsteps != 0) HIPCHK2(h, launch_reduce2d(x, reduction(x.part[0], data_records(x), 0, R2_STEP), s));
+    // Stage states.  The caller's arrays are the input of step 0 (P^k: the kernels
+    // read no mode beyond k); a step's output is in B[0] and, but for forward Euler,
+    // overwrites the step's input there in its last stage, which reads of it only
+    // the cell it writes.  Between, the stages alternate between B[1] and B[2].
+    auto buffer = [&](long long n, int l) -> double * {   // output of stage l of step n
+        if (x.ns == 1) return x.B[n & 1];
+        return l == x.ns - 1 ? x.B[0] : x.B[1 + (l & 1)];
+    };
     const int chunk = 16;
     long long n = 0;
     while (nsteps < 0 || n < nsteps) {
@@ -1597,21 +1619,27 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
                 a.gpar = ib;
                 a.rs = rk_stage(x.rk, l);
                 a.damp = x.oe && x.k > 0 && g > 0;
-                a.write_u = l == 0;
-                a.inC = x.B[ib];
-                a.inD = x.B[ib] + x.S1;
+                const bool first = n + j == 0;
+                const double *un = first ? uC : buffer(n + j - 1, x.ns - 1), *in = l > 0 ? buffer(n + j, l - 1) : un;
+                double *out = buffer(n + j, l);
+                a.inC = in;
+                a.inD = l == 0 && first ? uD : in + x.S1;
+                a.unC = un;
+                a.unD = first ? uD : un + x.S1;
+                if (x.oe && x.k > 0 && !first) {
+                    a.facC = x.fac;
+                    a.facD = x.fac + (size_t)x.k * x.nx * x.ny;
+                }
                 a.numC = x.num[ib];
                 a.numD = x.num[ib] + x.SN;
-                a.outC = x.B[ob];
-                a.outD = x.B[ob] + x.S1;
-                a.UC = x.U;
-                a.UD = x.U + x.S1;
+                a.outC = out;
+                a.outD = out + x.S1;
                 a.part = x.part[ob];
                 HIPCHK2(h, launch_stage2d(x, a, s));
                 // the numerators of its output and, beside them, the statistics for the next stage
                 const bool end = l == x.ns - 1 && n + j + 1 == nsteps;
                 const Red2Args r = reduction(x.part[ob], stage_records(x), g + 1, l == x.ns - 1 ? R2_STEP : R2_STAGE);
-                HIPCHK2(h, launch_delta2d(x, delta_args(x, x.B[ob], x.B[ob] + x.S1, ob, ib), end ? nullptr : &r, s));
+                HIPCHK2(h, launch_delta2d(x, delta_args(x, out, out + x.S1, ob, ib), end ? nullptr : &r, s));
             }
         n += m;
         HIPCHK2(h, hipMemcpyAsync(x.st_h, x.st, sizeof(Stats2), hipMemcpyDeviceToHost, s));
@@ -1619,12 +1647,13 @@ int run_2d(oecdg_handle *h, double *uC, double *uD, double t_end, int64_t nsteps
         if (x.st_h->done[(x.ns * n) & 1]) break;           // (of the stage after the last one launched)
     }
     const long long N = x.st_h->nexec + x.st_h->pending;   // executed steps
-    const int fb = (int)((x.ns * N) & 1);                  // buffer of the last stage's output
+    const int fb = (int)((x.ns * N) & 1);                  // parity of the last stage's numerators and statistics
+    const double *last = N > 0 ? buffer(N - 1, x.ns - 1) : uC;   // its output
     HIPCHK2(h, launch_reduce2d(x, reduction(x.part[fb], N > 0 ? stage_records(x) : data_records(x), 0, R2_FINAL), s));
     Stage2Args f = stage_args(x);
     f.damp = x.oe && x.k > 0 && N > 0;
-    f.inC = x.B[fb];
-    f.inD = x.B[fb] + x.S1;
+    f.inC = last;
+    f.inD = N > 0 ? last + x.S1 : uD;
     f.numC = x.num[fb];
     f.numD = x.num[fb] + x.SN;
     f.outC = uC;
