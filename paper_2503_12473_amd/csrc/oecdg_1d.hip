@@ -46,10 +46,12 @@ __host__ __device__ constexpr int nthreads(int T) { return 2 * T + WAVE; }
 // Damping factors of one cell: fac[j] = exp(-tau * sum_{m<=j} delta^m), j >= 1,
 // delta^m = (2m+1) 2^m / ((2k-1) m! h) * max_q beta (|dR_q| + |dL_q|) / sigma_q
 // with dR, dL the xi-derivatives of order m of (own trace - other mesh at its
-// centre) at the right and left edge; components with sigma_q = 0 are skipped.
+// centre) at the right and left edge.  isig: 1 / sigma_q, 0 where sigma_q = 0 (the
+// component then contributes 0): one product per order and component instead of a
+// division and a branch.
 template <int K, int NC>
 __device__ inline void oe_factors(const double (&own)[NC][K + 1], const double (&nl)[NC][K + 1],
-                                  const double (&nr)[NC][K + 1], double beta, const double *sig, double hinv,
+                                  const double (&nr)[NC][K + 1], double beta, const double *isig, double hinv,
                                   double tau, double (&fac)[K + 1]) {
     constexpr Tab<K> tb = make_tab<K>();
     fac[0] = 1.0;
@@ -68,10 +70,7 @@ __device__ inline void oe_factors(const double (&own)[NC][K + 1], const double (
                 vr += nr[q][n] * tb.D0[m][n];
                 vl += nl[q][n] * tb.D0[m][n];
             }
-            if (sig[q] != 0.0) {
-                const double val = beta * (fabs(ur - vr) + fabs(ul - vl)) / sig[q];
-                dm = fmax(dm, val);
-            }
+            dm = max_d(dm, beta * (fabs(ur - vr) + fabs(ul - vl)) * isig[q]);
         }
         S += tb.C[m] * hinv * dm;
         if (m >= 1) fac[m] = exp(-tau * S);
@@ -318,8 +317,8 @@ __device__ inline void lds_overlaps(const TCell &c, const double *uo, CellIn<K, 
 }
 
 template <int K, int FLUX>
-__device__ inline void damp_cell(const Inst1D &I, const TCell &c, CellIn<K, FLUX> &ci, const double (*sig)[3],
-                                 double tau, bool damp) {
+__device__ inline void damp_cell(const Inst1D &I, const TCell &c, CellIn<K, FLUX> &ci,
+                                 const double (&isig)[FluxT<FLUX>::NC], double tau, bool damp) {
     using F = FluxT<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1;
     if (damp && c.damps && (ci.real || ci.mirror)) {
@@ -328,7 +327,7 @@ __device__ inline void damp_cell(const Inst1D &I, const TCell &c, CellIn<K, FLUX
         for (int q = 0; q < NC; ++q) ubar[q] = ci.own[q][0];
         const double beta = F::speed(ubar, I.p0);
         double fac[K1];
-        oe_factors<K, NC>(ci.own, ci.nl, ci.nr, beta, sig[c.mesh], 1.0 / I.h, tau, fac);
+        oe_factors<K, NC>(ci.own, ci.nl, ci.nr, beta, isig, I.hinv, tau, fac);
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -356,16 +355,35 @@ __device__ inline void cell_stats(const Inst1D &I, bool valid, const double (&ou
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
         double mx = -INFINITY, mn = INFINITY;
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const double flip = hf ? 1.0 : -1.0;
+        if constexpr (K <= 2) {
+            // one odd mode: of the values at +-x the larger has +|a_1 x|, and rounding
+            // keeps the order, so half the comparisons give the same bits
 #pragma unroll
             for (int sidx = K + 2; sidx < 2 * K + 4; ++sidx) {
-                double x = 0.0;
+                double hi = out[q][0], lo = out[q][0];
+                if constexpr (K >= 1) {
+                    hi = fma(fabs(out[q][1]), tb.SP[sidx][1], out[q][0]);
+                    lo = fma(-fabs(out[q][1]), tb.SP[sidx][1], out[q][0]);
+                }
+                if constexpr (K == 2) {
+                    hi = fma(out[q][2], tb.SP[sidx][2], hi);
+                    lo = fma(out[q][2], tb.SP[sidx][2], lo);
+                }
+                mx = max_d(mx, hi);
+                mn = min_d(mn, lo);
+            }
+        } else {
 #pragma unroll
-                for (int n = 0; n <= K; ++n) x += ((n & 1) ? flip * out[q][n] : out[q][n]) * tb.SP[sidx][n];
-                mx = fmax(mx, x);
-                mn = fmin(mn, x);
+            for (int hf = 0; hf < 2; ++hf) {
+                const double flip = hf ? 1.0 : -1.0;
+#pragma unroll
+                for (int sidx = K + 2; sidx < 2 * K + 4; ++sidx) {
+                    double x = 0.0;
+#pragma unroll
+                    for (int n = 0; n <= K; ++n) x += ((n & 1) ? flip * out[q][n] : out[q][n]) * tb.SP[sidx][n];
+                    mx = max_d(mx, x);
+                    mn = min_d(mn, x);
+                }
             }
         }
         v[3 * q] = valid ? out[q][0] : 0.0;
@@ -457,18 +475,12 @@ __device__ inline void tile_partials(const Inst1D &I, const TCell &c, const doub
     }
 }
 
-// Reduced statistics -> avg and sigma per mesh and component.
-template <int NC>
-__device__ inline void finish_stats(const Inst1D &I, const double *red, double (*sig)[3]) {
-#pragma unroll
-    for (int mesh = 0; mesh < 2; ++mesh) {
-        const double ncell = mesh == 0 ? (double)I.np : (double)I.nd;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            const double avg = red[stat_index(mesh, q, 0)] / ncell;
-            sig[mesh][q] = fmax(red[stat_index(mesh, q, 1)] - avg, avg - red[stat_index(mesh, q, 2)]);
-        }
-    }
+// 1 / sigma of a component (0 where sigma = 0) from its reduced statistics of a
+// mesh of ncell cells.  (Clamped, so that a subnormal sigma gives no infinity.)
+__device__ inline double inv_sigma(double sum, double mx, double mn, double ncell) {
+    const double avg = div_nr(sum, ncell);
+    const double sig = fmax(mx - avg, avg - mn);
+    return sig != 0.0 ? fmin(1.0 / sig, 1.7976931348623157e308) : 0.0;
 }
 
 // LDS of a tile: the damped and the undamped image of both meshes, columns
@@ -479,17 +491,16 @@ constexpr int scratch_doubles(int T) { return NSTAT * ((nthreads(T) + WAVE - 1) 
 
 // ---------------------------------------------------------- stage tile ---
 
-// folded: the instance's statistics were reduced by k_fold into a.red (batched
+// FOLDED: the instance's statistics were reduced by k_fold into a.red (batched
 // launches); otherwise every workgroup reduces the per-tile records itself.
 // COH: the persistent launch, whose step records other workgroups of the same
 // launch write (read with device-scope atomic loads after the grid barrier).
-template <int K, int FLUX, int T, bool COH = false>
-__device__ void stage_tile(const StageArgs &a, int l, int par, int first, int tile, double *smem, bool xwl,
-                           bool folded) {
+template <int K, int FLUX, int T, bool FOLDED, bool COH = false>
+__device__ void stage_tile(const StageArgs &a, int l, int par, int first, int tile, double *smem, bool xwl) {
     using F = FluxT<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, W = lds_width(T), PER = NC * K1 * W, NT = nthreads(T);
     const int tid = threadIdx.x;
-    constexpr bool coh = COH;
+    constexpr bool coh = COH, folded = FOLDED;
     Tile1D tl;
     Inst1D I;
     if (a.ninst == 1) {                      // single instance: everything from the kernel arguments
@@ -536,9 +547,15 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
     for (int q = 0; q < NC; ++q)
 #pragma unroll
         for (int m = 0; m < K1; ++m) {
-            un[q][m] = UM[(long long)(q * K1 + m) * ncell + gi];   // gi: a valid index
+            un[q][m] = 0.0;
             acc[q][m] = 0.0;
         }
+    if (!FOLDED || l > 0) {                  // (a batch does not load what stage 0 does not read)
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int m = 0; m < K1; ++m) un[q][m] = UM[(long long)(q * K1 + m) * ncell + gi];   // gi: a valid index
+    }
     if (rs.acc_read) {
 #pragma unroll
         for (int q = 0; q < NC; ++q)
@@ -546,10 +563,16 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
             for (int m = 0; m < K1; ++m) acc[q][m] = AM[(long long)(q * K1 + m) * ncell + gi];
     }
     Partials<NC> pv;
-    double redv = 0.0;                       // folded: row tid of the instance's reduced statistics
+    double isig[NC], beta[2] = {0.0, 0.0};   // of this thread's mesh; the wave speeds of both
+#pragma unroll
+    for (int q = 0; q < NC; ++q) isig[q] = 0.0;
     if (need_red) {
         if (folded) {
-            if (tid < NSTAT) redv = a.red[(long long)tl.inst * NSTAT + tid];
+            const double *rd = a.red + (long long)tl.inst * NSTAT;
+#pragma unroll
+            for (int q = 0; q < NC; ++q) isig[q] = rd[stat_index(c.mesh, q, 1)];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) beta[j] = rd[ST_BETA + j];
         } else {
             load_partials_raw<NT, NC>(a.part[sp ^ 1], I.tile0, I.npart, pv);
         }
@@ -574,15 +597,12 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
             for (int m = 0; m < K1; ++m) g[q][m] = ci.mirror ? mirror_sign(q, m) * ci.own[q][m] : ci.own[q][m];
         lds_put<K, NC, W>(smem + (2 + c.mesh) * PER, c.col, g);
     }
-    double red[NSTAT];                       // the reduced statistics, in every thread
-    if (need_red) {
-        if (folded) {
-            if (tid < NSTAT) scratch[tid] = redv;
-            __syncthreads();
+    if (need_red && !folded) {
+        double own[3 * NC];
+        finish_partials_mesh<NT, NC>(pv, a.part[sp ^ 1], I.tile0, I.npart, ns, c.mesh, own, beta, scratch);
+        if (damp) {
 #pragma unroll
-            for (int i = 0; i < NSTAT; ++i) red[i] = scratch[i];
-        } else {
-            finish_partials_all<NT, NC>(pv, a.part[sp ^ 1], I.tile0, I.npart, ns, red, scratch);
+            for (int q = 0; q < NC; ++q) isig[q] = inv_sigma(own[3 * q], own[3 * q + 1], own[3 * q + 2], (double)ncell);
         }
     } else {
         __syncthreads();
@@ -594,7 +614,7 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
         tau = a.tau_override;
         taumax = a.taumax_override;
     } else if (l == 0) {
-        taumax = a.dt_fixed > 0.0 ? a.dt_fixed : I.cfl * I.h / fmax(red[ST_BETA], red[ST_BETA + 1]);
+        taumax = a.dt_fixed > 0.0 ? a.dt_fixed : I.cfl * I.h / fmax(beta[0], beta[1]);
         tau = taumax;
         if (cur.t + tau >= a.t_end) {
             tau = a.t_end - cur.t;
@@ -620,12 +640,10 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
         f->nexec = ld_ll(&f->nexec, coh) + 1;
     }
 
-    double sig[2][3] = {{0, 0, 0}, {0, 0, 0}};
     if (damp) {
-        finish_stats<NC>(I, red, sig);
         if (c.damps && (ci.real || ci.mirror)) lds_overlaps<K, FLUX, W>(c, smem + (3 - c.mesh) * PER, ci);
     }
-    damp_cell<K, FLUX>(I, c, ci, sig, (l == 0) ? prev.tau : tau, damp);
+    damp_cell<K, FLUX>(I, c, ci, isig, (l == 0) ? prev.tau : tau, damp);
     if (c.damps) lds_put<K, NC, W>(smem + c.mesh * PER, c.col, ci.own);
     __syncthreads();
 
@@ -651,14 +669,14 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
         }
         // the damped cells of the other mesh that overlap this one (left, right)
         double nb[NC][K1], rl[NC][K1], rr[NC][K1];
-        const double ft = taumax * (1.0 / I.h);
+        const double ft = taumax * I.hinv;
         lds_cell<K, NC, W>(smem + (1 - c.mesh) * PER, c.mesh == 0 ? c.col : c.col - 1, nb);
         cdg_rate_half<K, FLUX>(nb, 0, I.p0, ft, rl);
         lds_cell<K, NC, W>(smem + (1 - c.mesh) * PER, c.mesh == 0 ? c.col + 1 : c.col, nb);
         cdg_rate_half<K, FLUX>(nb, 1, I.p0, ft, rr);
 
         // eq:RKCDG: out = c_{l0} u^n [+ accumulated earlier stages] + c_{ll} u^l + tau d_{ll} L(u^l)
-        const double inv_tm = 1.0 / taumax;
+        const double inv_tm = div_nr(1.0, taumax);
         const double td = tau * rs.d;
         bool finite = true;
 #pragma unroll
@@ -745,18 +763,24 @@ __device__ void final_tile(const StageArgs &a, int tile, double *smem, bool xwl)
     const TCell c = tile_cell<T>(I, tile, tl.i0, xwl);
     CellIn<K, FLUX> ci;
     load_cell_in<K, FLUX>(I, c, a.BC[bp] + I.offC, a.BD[bp] + I.offD, ci);
-    double sig[2][3] = {{0, 0, 0}, {0, 0, 0}};
+    double isig[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) isig[q] = 0.0;
     if (damp) {
         if (a.red) {                         // folded (launch_fold_final_1d)
-            if (threadIdx.x < NSTAT) red[threadIdx.x] = a.red[(long long)tl.inst * NSTAT + threadIdx.x];
-            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < NC; ++q) isig[q] = a.red[(long long)tl.inst * NSTAT + stat_index(c.mesh, q, 1)];
         } else {
             reduce_instance<nthreads(T), NC>(a.part[(int)((a.ns * N - 1) & 1)], I.tile0, I.npart, false, red,
                                              scratch);
+            const double ncell = (double)(c.mesh == 0 ? I.np : I.nd);
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                isig[q] = inv_sigma(red[stat_index(c.mesh, q, 0)], red[stat_index(c.mesh, q, 1)],
+                                    red[stat_index(c.mesh, q, 2)], ncell);
         }
-        finish_stats<NC>(I, red, sig);
     }
-    damp_cell<K, FLUX>(I, c, ci, sig, tau, damp);
+    damp_cell<K, FLUX>(I, c, ci, isig, tau, damp);
     if (c.owned) {
         const int ncell = c.mesh == 0 ? I.np : I.nd;
         double *dst = c.mesh == 0 ? a.dstC + I.offC : a.dstD + I.offD;
@@ -781,15 +805,13 @@ struct Disp {
 };
 
 template <int K, int FLUX, int T> struct StageFn {
-    __device__ static void go(const StageArgs &a, int l, int par, int first, int tile, double *smem, bool xwl,
-                              bool folded) {
-        stage_tile<K, FLUX, T>(a, l, par, first, tile, smem, xwl, folded);
+    __device__ static void go(const StageArgs &a, int l, int par, int first, int tile, double *smem, bool xwl) {
+        stage_tile<K, FLUX, T, false>(a, l, par, first, tile, smem, xwl);
     }
 };
 template <int K, int FLUX, int T> struct StageCohFn {
-    __device__ static void go(const StageArgs &a, int l, int par, int first, int tile, double *smem, bool xwl,
-                              bool folded) {
-        stage_tile<K, FLUX, T, true>(a, l, par, first, tile, smem, xwl, folded);
+    __device__ static void go(const StageArgs &a, int l, int par, int first, int tile, double *smem, bool xwl) {
+        stage_tile<K, FLUX, T, false, true>(a, l, par, first, tile, smem, xwl);
     }
 };
 template <int K, int FLUX, int T> struct StatsFn {
@@ -811,7 +833,7 @@ __global__ __launch_bounds__(nthreads(T)) void k_stage(StageArgs a) {
     using D = Disp<KM, FLUX, T>;
     __shared__ double smem[D::LDS];
     const int tile = a.tbeg + xcd_tile(blockIdx.x, a.tend - a.tbeg);
-    if (tile < a.tend) D::template run<StageFn>(a, a.l, a.par, a.first, tile, smem, XW, false);
+    if (tile < a.tend) D::template run<StageFn>(a, a.l, a.par, a.first, tile, smem, XW);
 }
 
 // The stage kernel of batched launches (one degree per launch): the
@@ -824,13 +846,14 @@ template <int K, int FLUX, int T>
 __global__ __launch_bounds__(nthreads(T), T == 64 && K <= 2 ? 3 : 1) void k_stage_folded(StageArgs a) {
     __shared__ double smem[lds_doubles(K, FluxT<FLUX>::NC, T) + scratch_doubles(T)];
     const int tile = a.tbeg + xcd_tile(blockIdx.x, a.tend - a.tbeg);     // one tile per workgroup
-    if (tile < a.tend) stage_tile<K, FLUX, T>(a, a.l, a.par, a.first, tile, smem, false, true);
+    if (tile < a.tend) stage_tile<K, FLUX, T, true>(a, a.l, a.par, a.first, tile, smem, false);
 }
 
 // One workgroup per instance: the partial columns of the state the next stage
 // reads (part[src]) reduced in the same fixed order as a stage kernel's own
 // reduction (same thread count, same tree), so batched instances keep the bits
-// of single-instance runs.  All NSTAT rows go to red[instance][row].  src < 0:
+// of single-instance runs.  The rows go to red[instance][row], with 1 / sigma in
+// the place of the max (once here instead of in every stage thread).  src < 0:
 // the state that the final kernel damps (the output of the instance's last
 // executed stage).
 __device__ inline int fold_source(const StageArgs &a, int src, int inst) {
@@ -846,42 +869,84 @@ __global__ __launch_bounds__(nthreads(T)) void k_fold(StageArgs a, int src) {
     __syncthreads();
     const Inst1D I = a.ninst == 1 ? a.inst0 : a.inst[b];
     reduce_instance<nthreads(T), NC>(a.part[fold_source(a, src, b)], I.tile0, I.npart, true, red, scratch);
-    if (tid < NSTAT) a.red[(long long)b * NSTAT + tid] = red[tid];
+    double v = tid < NSTAT ? red[tid] : 0.0;
+    if (tid < ST_BETA && tid % 3 == 1)
+        v = inv_sigma(red[tid - 1], v, red[tid + 1], (double)(tid < ST_BETA / 2 ? I.np : I.nd));
+    if (tid < NSTAT) a.red[(long long)b * NSTAT + tid] = v;
 }
 
-// The same reduction with a workgroup per row (grid: instances x rows), for
-// instances of many tiles, where k_fold is bound by one workgroup's chain of
-// waits (81 rounds of 20 loads at 15626 tiles: 87 us, the other CUs idle).  A
-// workgroup per row with FOLD_AHEAD loads in flight per thread takes 22 us there.
-// Thread count, order and tree are k_fold's, so the bits are too.
+// The same reduction for instances of many tiles, where k_fold is bound by one
+// workgroup's chain of waits (81 rounds of 20 loads at 15626 tiles: 87 us, the
+// other CUs idle): a workgroup of one wave per wave of k_fold and per mesh and
+// component (one more for the wave speeds; grid: instances x groups x waves), each
+// with FOLD_AHEAD records in flight per thread.  The last wave of a group to arrive
+// combines them.  Which thread takes which tiles, the order and the tree are
+// k_fold's, so the bits are too.
 constexpr int FOLD_AHEAD = 8;
 
 template <int NC, int T>
-__global__ __launch_bounds__(nthreads(T)) void k_fold_rows(StageArgs a, int src) {
+__global__ __launch_bounds__(WAVE) void k_fold_rows(StageArgs a, int src) {
     constexpr int NT = nthreads(T), NW = NT / WAVE;
-    __shared__ double scratch[NW];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid % WAVE;
+    const int b = blockIdx.x, g = blockIdx.y, wave = blockIdx.z, lane = threadIdx.x;
     const Inst1D I = a.ninst == 1 ? a.inst0 : a.inst[b];
-    const int row = stat_row<NC>(blockIdx.y), kind = stat_kind(row), n = I.npart;
+    const bool speeds = g == 2 * NC;         // (their third value is a duplicate)
+    const int row = speeds ? ST_BETA : stat_index(g / NC, g % NC, 0), n = I.npart;
     const double *col = a.part[fold_source(a, src, b)] + (long long)I.tile0 * NSTAT + row;
-    double acc = stat_identity(kind);
-    for (int t0 = tid; t0 < n; t0 += FOLD_AHEAD * NT) {
-        double x[FOLD_AHEAD];
+    const int step = speeds ? 0 : 2;         // of the third value's row
+    auto op = [speeds](int j, double x, double y) {
+        if (speeds || j == 1) return max_d(x, y);
+        return j == 0 ? x + y : min_d(x, y);
+    };
+    double acc[3];
 #pragma unroll
-        for (int i = 0; i < FOLD_AHEAD; ++i) x[i] = col[(long long)min(t0 + i * NT, n - 1) * NSTAT];
+    for (int j = 0; j < 3; ++j) acc[j] = stat_identity(speeds ? 1 : j);
+    for (int t0 = wave * WAVE + lane; t0 < n; t0 += FOLD_AHEAD * NT) {
+        double x[FOLD_AHEAD][3];
 #pragma unroll
         for (int i = 0; i < FOLD_AHEAD; ++i) {
-            const double y = stat_op(kind, acc, x[i]);
-            acc = t0 + i * NT < n ? y : acc;
+            const double *r = col + (long long)min(t0 + i * NT, n - 1) * NSTAT;
+            x[i][0] = r[0];
+            x[i][1] = r[1];
+            x[i][2] = r[step];
         }
+#pragma unroll
+        for (int i = 0; i < FOLD_AHEAD; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const double y = op(j, acc[j], x[i][j]);
+                acc[j] = t0 + i * NT < n ? y : acc[j];
+            }
     }
-    acc = wave_reduce(kind, acc);
-    if (lane == WAVE - 1) scratch[tid / WAVE] = acc;
-    __syncthreads();
-    if (tid == 0) {
-        double v = scratch[0];
-        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, scratch[w]);
-        a.red[(long long)b * NSTAT + row] = v;
+    if (speeds) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) acc[j] = wave_reduce(1, acc[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) acc[j] = wave_reduce(j, acc[j]);
+    }
+    if (lane != WAVE - 1) return;
+    double *out = a.foldw + ((long long)b * FOLD_GROUPS + g) * FOLD_WAVES * 3;
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        __hip_atomic_store(out + 3 * wave + j, acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned *count = a.foldn + (long long)b * FOLD_GROUPS + g;
+    if (__hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)NW - 1) return;
+    __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    double v[3];
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double x = __hip_atomic_load(out + 3 * w + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            v[j] = w == 0 ? x : op(j, v[j], x);
+        }
+    double *r = a.red + (long long)b * NSTAT + row;
+    r[0] = v[0];
+    if (speeds) {
+        r[1] = v[1];
+    } else {
+        r[1] = inv_sigma(v[0], v[1], v[2], (double)(g < NC ? I.np : I.nd));
+        r[2] = v[2];
     }
 }
 
@@ -969,7 +1034,7 @@ __global__ __launch_bounds__(nthreads(T)) void k_persistent(StageArgs a, long lo
         const int par = (int)(n & 1);
         for (int l = 0; l < a.ns; ++l) {
             for (int tile = a.tbeg + blockIdx.x; tile < a.tend; tile += gridDim.x) {
-                D::template run<StageCohFn>(a, l, par, n == 0, tile, smem, XW, false);
+                D::template run<StageCohFn>(a, l, par, n == 0, tile, smem, XW);
             }
             grid_barrier(a);
             if (l == 0 && single_instance && ld_i(&a.slots[par].done, true)) return;
@@ -1072,7 +1137,7 @@ hipError_t launch_stage_1d(const StageArgs &a, int kmax, int flux, int tile, hip
     return launch(pick<0>(kmax, flux, ti), b.tend - b.tbeg, tile, b, s);   // one workgroup per tile
 }
 
-// Instances of more tiles than this are folded with a workgroup per row: up to
+// Instances of more tiles than this are folded by k_fold_rows: up to
 // it, k_fold's threads have all their tiles' rows in flight in one round of loads
 // (6.2 us for 512 instances of up to 129 tiles), beyond it they wait round by round.
 static int fold_rows(int tile) { return 2 * nthreads(tile); }
@@ -1094,7 +1159,9 @@ static hipError_t launch_fold(const StageArgs &a, int src, int flux, int tile, i
     StageArgs copy = a;
     int srcv = src;
     void *args[] = {&copy, &srcv};
-    return hipLaunchKernel(fn, dim3(a.ninst, rows ? 6 * nc + 2 : 1), dim3(nthreads(tile)), args, 0, s);
+    const int nw = nthreads(tile) / WAVE;
+    return rows ? hipLaunchKernel(fn, dim3(a.ninst, 2 * nc + 1, nw), dim3(WAVE), args, 0, s)
+                : hipLaunchKernel(fn, dim3(a.ninst), dim3(nthreads(tile)), args, 0, s);
 }
 
 hipError_t launch_fold_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s) {

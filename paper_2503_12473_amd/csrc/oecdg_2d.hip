@@ -1502,7 +1502,8 @@ int create_2d(oecdg_handle *h, const oecdg_desc *d) {
     if (x->rk == 4) HIPCHK2(h, hipMalloc(&x->A, sizeof(double) * 2 * x->S1));
     HIPCHK2(h, hipMalloc(&x->fold, sizeof(double) * nval * RED2_MAXB));
     HIPCHK2(h, hipMalloc(&x->count, sizeof(unsigned)));
-    HIPCHK2(h, hipMemset(x->count, 0, sizeof(unsigned)));
+    const unsigned none = 0;
+    HIPCHK2(h, hipMemcpy(x->count, &none, sizeof(none), hipMemcpyHostToDevice));
     HIPCHK2(h, hipMalloc(&x->st, sizeof(Stats2)));
     HIPCHK2(h, hipHostMalloc((void **)&x->st_h, sizeof(Stats2), hipHostMallocDefault));
     HIPCHK2(h, hipMalloc(&x->err, 4 * sizeof(int)));

@@ -54,7 +54,8 @@ struct oecdg_handle {
     double *A = nullptr;     // AC | AD: classical RK4 only (sum of earlier stages for the last one)
     int *err = nullptr;
     unsigned *bar = nullptr;
-    double *red = nullptr;   // [nbatch][NSTAT] statistics folded by k_fold
+    double *red = nullptr;   // [nbatch][NSTAT] statistics folded by k_fold, then the scratch of k_fold_rows
+    unsigned *foldn = nullptr;
     // pinned host mirrors (one block: records, then flags), host-coherent and
     // mapped: the final kernel of a short run writes them directly
     Final *fin_h = nullptr;
@@ -166,6 +167,7 @@ Inst1D oecdg::make_inst(const oecdg_desc &e) {
     I.np = (int)e.nx;
     I.nd = (int)(e.bc == OECDG_BC_PERIODIC ? e.nx : e.nx + 1);
     I.h = (e.xhi - e.xlo) / (double)e.nx;
+    I.hinv = 1.0 / I.h;
     I.cfl = e.cfl;
     I.p0 = e.flux_param[0];
     I.oe = e.oe;
@@ -279,6 +281,8 @@ StageArgs base_args(oecdg_handle *h) {
     a.ninst = h->nbatch;
     if (h->nbatch == 1) a.inst0 = h->inst_h[0];
     a.red = fold_on(h) ? h->red : nullptr;
+    a.foldw = h->red + (size_t)NSTAT * h->nbatch;
+    a.foldn = h->foldn;
     a.t_end = INFINITY;
     return a;
 }
@@ -898,8 +902,14 @@ int oecdg_init(const oecdg_desc *d, int32_t nbatch, void *stream, oecdg_handle *
     ALLOC(h->U, sizeof(double) * (h->totC + h->totD));
     if (h->rk == 4) ALLOC(h->A, sizeof(double) * (h->totC + h->totD));
     ALLOC(h->bar, sizeof(unsigned) * 2);
-    ALLOC(h->red, sizeof(double) * NSTAT * nbatch);
+    ALLOC(h->red, sizeof(double) * (NSTAT + FOLD_GROUPS * FOLD_WAVES * 3) * nbatch);
+    ALLOC(h->foldn, sizeof(unsigned) * FOLD_GROUPS * nbatch);
 #undef ALLOC
+    const std::vector<unsigned> none((size_t)FOLD_GROUPS * nbatch, 0u);
+    if (hipMemcpy(h->foldn, none.data(), sizeof(unsigned) * none.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        oecdg_destroy(h);
+        return OECDG_EHIP;
+    }
     if (hipHostMalloc((void **)&h->fin_h, rec_bytes(nbatch), hipHostMallocMapped | hipHostMallocCoherent) !=
             hipSuccess ||
         hipHostGetDevicePointer((void **)&h->fin_hd, h->fin_h, 0) != hipSuccess) {
@@ -1088,6 +1098,7 @@ void oecdg_destroy(oecdg_handle *h) {
     (void)hipFree(h->A);
     (void)hipFree(h->bar);
     (void)hipFree(h->red);
+    (void)hipFree(h->foldn);
     if (h->fin_h) (void)hipHostFree(h->fin_h);
     if (h->ext2d) {
         oecdg::destroy_2d(h);

@@ -11,6 +11,18 @@ namespace oecdg {
 
 constexpr int WAVE = 64;
 
+// a / b by the steps of the IEEE division without its range scaling and fix-up:
+// the same bits wherever those do nothing (b and the quotient within about
+// 2^+-1000 and neither 0 nor infinite), 8 instructions instead of 11.  b = 0
+// gives NaN instead of an infinity; both make the output non-finite.
+__device__ inline double div_nr(double a, double b) {
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(r, fma(-b, r, 1.0), r);
+    r = fma(r, fma(-b, r, 1.0), r);
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
+
 // ---------------------------------------------------------------- fluxes ---
 
 template <int FLUX> struct FluxT;
@@ -32,7 +44,7 @@ template <> struct FluxT<1> {          // Burgers f = u^2 / 2
 template <> struct FluxT<2> {          // Euler (rho, m, E), ideal gas
     static constexpr int NC = 3;
     __device__ static inline void f(const double *w, double *o, double g) {
-        const double v = w[1] / w[0];
+        const double v = div_nr(w[1], w[0]);
         const double p = (g - 1.0) * (w[2] - 0.5 * w[1] * v);
         o[0] = w[1];
         o[1] = w[1] * v + p;
@@ -41,13 +53,13 @@ template <> struct FluxT<2> {          // Euler (rho, m, E), ideal gas
     // |v| + sqrt(gamma |p| / rho): |v| + c for every physical state, finite
     // where a tolerated non-positive pressure sits at a cell average
     __device__ static inline double speed(const double *u, double g) {
-        const double v = u[1] / u[0];
+        const double v = div_nr(u[1], u[0]);
         const double p = (g - 1.0) * (u[2] - 0.5 * u[1] * v);
-        return fabs(v) + sqrt(g * fabs(p) / u[0]);
+        return fabs(v) + sqrt(div_nr(g * fabs(p), u[0]));
     }
     __device__ static inline bool physical(const double *u, double g) {
         if (!(u[0] > 0.0)) return false;
-        const double p = (g - 1.0) * (u[2] - 0.5 * u[1] * u[1] / u[0]);
+        const double p = (g - 1.0) * (u[2] - div_nr(0.5 * u[1] * u[1], u[0]));
         return p > 0.0;
     }
 };
@@ -267,26 +279,27 @@ __device__ void finish_partials(const Partials<NC> &p, const double *part, int t
     __syncthreads();
 }
 
-// The same reduction, with every thread combining the per-wave results itself
-// (the order of finish_partials), so that all of them hold all NSTAT rows (rows
-// beyond ns are zero) after one barrier.
+// The same reduction, with every thread combining the per-wave results of the rows
+// of its own mesh itself (the order of finish_partials), after one barrier:
+// own[3 q + kind], and with ns = NS the wave speeds of both meshes.
 template <int NT, int NC>
-__device__ void finish_partials_all(const Partials<NC> &p, const double *part, int tile0, int ntiles, int ns,
-                                    double (&red)[NSTAT], double *scratch) {
+__device__ inline void finish_partials_mesh(const Partials<NC> &p, const double *part, int tile0, int ntiles, int ns,
+                                            int mesh, double (&own)[3 * NC], double (&beta)[2], double *scratch) {
     constexpr int NS = Partials<NC>::NS;
     constexpr int NW = (NT + WAVE - 1) / WAVE;
     wave_partials<NT, NC>(p, part, tile0, ntiles, ns, scratch);
     __syncthreads();
+    auto combine = [&](int kind, const double *s) {
+        double v = s[0];
 #pragma unroll
-    for (int i = 0; i < NSTAT; ++i) red[i] = 0.0;
+        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, s[w * NS]);
+        return v;
+    };
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        if (i < ns) {
-            const int kd = stat_kind(stat_row<NC>(i));
-            double v = scratch[i];
-            for (int w = 1; w < NW; ++w) v = stat_op(kd, v, scratch[w * NS + i]);
-            red[stat_row<NC>(i)] = v;
-        }
+    for (int i = 0; i < 3 * NC; ++i) own[i] = combine(i % 3, scratch + mesh * 3 * NC + i);
+    if (ns == NS) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) beta[j] = combine(1, scratch + 6 * NC + j);
     }
 }
 

@@ -16,6 +16,8 @@ constexpr int MAXK = 3;
 // sigma sample points; ST_BETA = largest wave speed at a cell average.
 constexpr int NSTAT = 20;
 constexpr int ST_BETA = 18;
+// Folds of many tiles: groups (mesh and component, and the wave speeds) and the most waves per group.
+constexpr int FOLD_GROUPS = 7, FOLD_WAVES = 5;
 
 __host__ __device__ constexpr int stat_index(int mesh, int q, int kind) { return (mesh * 3 + q) * 3 + kind; }
 
@@ -26,6 +28,7 @@ struct Inst1D {
     int tile0, ntiles;       // tiles [tile0, tile0 + ntiles) of the global tile list
     long long offC, offD;    // element offsets in the concatenated state arrays
     double h, cfl, p0;       // cell width, C_CFL, flux parameter (speed or gamma)
+    double hinv;             // 1 / h
     int oe;
     int tail;                // the last tile also updates dual cell np (outflow/walls, np a multiple of T)
     int npart;               // partial-statistics columns [tile0, tile0 + npart): ntiles, plus one with a tail
@@ -103,7 +106,10 @@ struct StageArgs {
     double *UC, *UD;         // damped u^n of the current step
     double *DC, *DD;         // optional: damped input of stages 1 and 2 (adjoint recomputation)
     double *AC, *AD;         // classical RK4: weighted sum of the damped inputs of stages 1 and 2
-    double *red;             // batched launches: [ninst][NSTAT] statistics reduced by k_fold (else null)
+    double *red;             // batched launches: [ninst][NSTAT] statistics reduced by k_fold (else null), with
+                             // 1 / sigma (0 where sigma is 0) in the place of the max
+    double *foldw;           // [ninst][FOLD_GROUPS][FOLD_WAVES][3] waves' results of k_fold_rows
+    unsigned *foldn;         // [ninst][FOLD_GROUPS] arrivals (0 between launches)
     int *err;                // [0] non-finite, [1] non-physical, [2] barrier timeout, [3] step+1 of an error
     int rk, ns;              // RK method (rk_stage) and its stages per step
     RKStage rs;              // rk_stage(rk, l), set by the stage launcher (the persistent launch forms its own)
