@@ -487,7 +487,7 @@ __device__ inline double inv_sigma(double sum, double mx, double mn, double ncel
 // 0 .. T + 2 (cells i0 - 1 .. i0 + T + 1).
 constexpr int lds_width(int T) { return T + 3; }
 constexpr int lds_doubles(int K, int NC, int T) { return 4 * NC * (K + 1) * lds_width(T); }
-constexpr int scratch_doubles(int T) { return NSTAT * ((nthreads(T) + WAVE - 1) / WAVE) + NSTAT; }
+constexpr int scratch_doubles(int T) { return NSTAT * (T == 128 ? 5 : 1); }   // (T = 128: a row of statistics per wave)
 
 // ---------------------------------------------------------- stage tile ---
 
@@ -521,7 +521,7 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
     const int sp = ((a.ns & 1 ? par : 0) + l) & 1;   // parity of the global stage index ns n + l
     // LDS images, [damped C, damped D, undamped C, undamped D] x PER (offsets,
     // not selected pointers: the compiler mishandles a select of LDS pointers)
-    double *scratch = smem + lds_doubles(K, NC, T) + NSTAT;
+    double *scratch = smem + lds_doubles(K, NC, T);
 
     const TCell c = tile_cell<T>(I, tile, i0, xwl);
     const bool xcell = xwl && I.tail && tile == I.tile0 + I.ntiles - 1;
@@ -531,7 +531,6 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
     const bool damp = a.damp_input && I.oe && K > 0 && !(l == 0 && first);
     const bool need_beta = l == 0 && !single && a.dt_fixed <= 0.0;
     const bool need_red = damp || need_beta;
-    const int ns = need_beta ? Partials<NC>::NS : Partials<NC>::NS - 2;
     const RKStage rs = COH ? rk_stage(a.rk, l) : a.rs;   // (l = a.l outside the persistent launch)
     double *AM = (rs.acc_read || rs.ca != 0.0) ? (c.mesh == 0 ? a.AC + I.offC : a.AD + I.offD) : nullptr;
 
@@ -562,7 +561,7 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
 #pragma unroll
             for (int m = 0; m < K1; ++m) acc[q][m] = AM[(long long)(q * K1 + m) * ncell + gi];
     }
-    Partials<NC> pv;
+    Partials<NT, NC> pv;
     double isig[NC], beta[2] = {0.0, 0.0};   // of this thread's mesh; the wave speeds of both
 #pragma unroll
     for (int q = 0; q < NC; ++q) isig[q] = 0.0;
@@ -574,7 +573,7 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
 #pragma unroll
             for (int j = 0; j < 2; ++j) beta[j] = rd[ST_BETA + j];
         } else {
-            load_partials_raw<NT, NC>(a.part[sp ^ 1], I.tile0, I.npart, pv);
+            load_partials<NT, NC>(a.part[sp ^ 1], I.tile0, I.npart, need_beta, pv);
         }
     }
 
@@ -598,11 +597,15 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
         lds_put<K, NC, W>(smem + (2 + c.mesh) * PER, c.col, g);
     }
     if (need_red && !folded) {
-        double own[3 * NC];
-        finish_partials_mesh<NT, NC>(pv, a.part[sp ^ 1], I.tile0, I.npart, ns, c.mesh, own, beta, scratch);
+        finish_partials<NT, NC>(pv, a.part[sp ^ 1], I.tile0, I.npart, need_beta, scratch);
         if (damp) {
+            const double *own = scratch + 3 * NC * c.mesh;
 #pragma unroll
             for (int q = 0; q < NC; ++q) isig[q] = inv_sigma(own[3 * q], own[3 * q + 1], own[3 * q + 2], (double)ncell);
+        }
+        if (need_beta) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) beta[j] = scratch[6 * NC + j];
         }
     } else {
         __syncthreads();
@@ -757,8 +760,7 @@ __device__ void final_tile(const StageArgs &a, int tile, double *smem, bool xwl)
     const long long N = a.fin[tl.inst].nexec;
     const double tau = a.fin[tl.inst].tau;
     const int bp = (int)((a.ns * N) & 1);   // buffer holding the last stage's output (or the input when N = 0)
-    double *red = smem + lds_doubles(K, NC, T);
-    double *scratch = red + NSTAT;
+    double *scratch = smem + lds_doubles(K, NC, T);
     const bool damp = N > 0 && I.oe && K > 0;
     const TCell c = tile_cell<T>(I, tile, tl.i0, xwl);
     CellIn<K, FLUX> ci;
@@ -771,13 +773,10 @@ __device__ void final_tile(const StageArgs &a, int tile, double *smem, bool xwl)
 #pragma unroll
             for (int q = 0; q < NC; ++q) isig[q] = a.red[(long long)tl.inst * NSTAT + stat_index(c.mesh, q, 1)];
         } else {
-            reduce_instance<nthreads(T), NC>(a.part[(int)((a.ns * N - 1) & 1)], I.tile0, I.npart, false, red,
-                                             scratch);
-            const double ncell = (double)(c.mesh == 0 ? I.np : I.nd);
+            reduce_instance<nthreads(T), NC>(a.part[(int)((a.ns * N - 1) & 1)], I.tile0, I.npart, false, scratch);
+            const double ncell = (double)(c.mesh == 0 ? I.np : I.nd), *own = scratch + 3 * NC * c.mesh;
 #pragma unroll
-            for (int q = 0; q < NC; ++q)
-                isig[q] = inv_sigma(red[stat_index(c.mesh, q, 0)], red[stat_index(c.mesh, q, 1)],
-                                    red[stat_index(c.mesh, q, 2)], ncell);
+            for (int q = 0; q < NC; ++q) isig[q] = inv_sigma(own[3 * q], own[3 * q + 1], own[3 * q + 2], ncell);
         }
     }
     damp_cell<K, FLUX>(I, c, ci, isig, tau, damp);
@@ -862,91 +861,94 @@ __device__ inline int fold_source(const StageArgs &a, int src, int inst) {
 
 template <int NC, int T>
 __global__ __launch_bounds__(nthreads(T)) void k_fold(StageArgs a, int src) {
-    __shared__ double red[NSTAT];
-    __shared__ double scratch[scratch_doubles(T)];
+    __shared__ double out[NSTAT];
     const int b = blockIdx.x, tid = threadIdx.x;
-    if (tid < NSTAT) red[tid] = 0.0;
-    __syncthreads();
     const Inst1D I = a.ninst == 1 ? a.inst0 : a.inst[b];
-    reduce_instance<nthreads(T), NC>(a.part[fold_source(a, src, b)], I.tile0, I.npart, true, red, scratch);
-    double v = tid < NSTAT ? red[tid] : 0.0;
-    if (tid < ST_BETA && tid % 3 == 1)
-        v = inv_sigma(red[tid - 1], v, red[tid + 1], (double)(tid < ST_BETA / 2 ? I.np : I.nd));
-    if (tid < NSTAT) a.red[(long long)b * NSTAT + tid] = v;
+    reduce_instance<nthreads(T), NC>(a.part[fold_source(a, src, b)], I.tile0, I.npart, true, out);
+    double *red = a.red + (long long)b * NSTAT;
+    if (tid < 2 * NC) {
+        const double *t = out + 3 * tid;
+        double *r = red + triple_row<NC>(tid);
+        r[0] = t[0];
+        r[1] = inv_sigma(t[0], t[1], t[2], (double)(tid < NC ? I.np : I.nd));
+        r[2] = t[2];
+    } else if (tid < 2 * NC + 2) {
+        red[ST_BETA + tid - 2 * NC] = out[6 * NC + tid - 2 * NC];
+    }
 }
 
 // The same reduction for instances of many tiles, where k_fold is bound by one
-// workgroup's chain of waits (81 rounds of 20 loads at 15626 tiles: 87 us, the
-// other CUs idle): a workgroup of one wave per wave of k_fold and per mesh and
-// component (one more for the wave speeds; grid: instances x groups x waves), each
-// with FOLD_AHEAD records in flight per thread.  The last wave of a group to arrive
-// combines them.  Which thread takes which tiles, the order and the tree are
-// k_fold's, so the bits are too.
-constexpr int FOLD_AHEAD = 8;
+// workgroup's chain of waits (87 us at 15626 tiles, the other CUs idle): a wave per
+// block of tiles and group (a mesh and component, or the wave speeds; grid:
+// instances x groups x FOLD_WG blocks).  The last workgroup of a group to arrive
+// combines its blocks in order.  Blocks, order and tree are k_fold's, so the bits
+// are too.  The groups' arrival counts are a line apart: in one line the arrivals of
+// all groups wait for each other.
+constexpr int FOLD_WG = 4;                   // blocks (waves) per workgroup
 
-template <int NC, int T>
-__global__ __launch_bounds__(WAVE) void k_fold_rows(StageArgs a, int src) {
-    constexpr int NT = nthreads(T), NW = NT / WAVE;
-    const int b = blockIdx.x, g = blockIdx.y, wave = blockIdx.z, lane = threadIdx.x;
+template <int NC, int PRE>
+__global__ __launch_bounds__(FOLD_WG * WAVE) void k_fold_rows(StageArgs a, int src) {
+    const int b = blockIdx.x, g = blockIdx.y, lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
     const Inst1D I = a.ninst == 1 ? a.inst0 : a.inst[b];
+    const int nblk = (I.npart + PRE * WAVE - 1) / (PRE * WAVE), nwg = (nblk + FOLD_WG - 1) / FOLD_WG;
+    if ((int)blockIdx.z >= nwg) return;
+    const int blk = blockIdx.z * FOLD_WG + wave, t0 = blk * PRE * WAVE, n = I.npart - t0;
+    __shared__ int last;
     const bool speeds = g == 2 * NC;         // (their third value is a duplicate)
-    const int row = speeds ? ST_BETA : stat_index(g / NC, g % NC, 0), n = I.npart;
-    const double *col = a.part[fold_source(a, src, b)] + (long long)I.tile0 * NSTAT + row;
-    const int step = speeds ? 0 : 2;         // of the third value's row
-    auto op = [speeds](int j, double x, double y) {
-        if (speeds || j == 1) return max_d(x, y);
-        return j == 0 ? x + y : min_d(x, y);
-    };
-    double acc[3];
+    const int row = speeds ? ST_BETA : triple_row<NC>(g), step = speeds ? 0 : 2;
+    auto kind = [speeds](int j) { return speeds ? 1 : j; };
+    double *out = a.foldw + ((long long)b * FOLD_GROUPS + g) * a.foldblk * 3;
+    if (blk < nblk) {                        // uniform over the wave
+        const double *col = a.part[fold_source(a, src, b)] + (long long)(I.tile0 + t0) * NSTAT + row;
+        double x[PRE][3], acc[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) acc[j] = stat_identity(speeds ? 1 : j);
-    for (int t0 = wave * WAVE + lane; t0 < n; t0 += FOLD_AHEAD * NT) {
-        double x[FOLD_AHEAD][3];
-#pragma unroll
-        for (int i = 0; i < FOLD_AHEAD; ++i) {
-            const double *r = col + (long long)min(t0 + i * NT, n - 1) * NSTAT;
+        for (int i = 0; i < PRE; ++i) {
+            const double *r = col + (long long)min(lane + i * WAVE, n - 1) * NSTAT;
             x[i][0] = r[0];
             x[i][1] = r[1];
             x[i][2] = r[step];
         }
 #pragma unroll
-        for (int i = 0; i < FOLD_AHEAD; ++i)
+        for (int j = 0; j < 3; ++j) {
+            acc[j] = stat_identity(kind(j));
+#pragma unroll
+            for (int i = 0; i < PRE; ++i)
+                acc[j] = stat_op(kind(j), acc[j], lane + i * WAVE < n ? x[i][j] : stat_identity(kind(j)));
+            acc[j] = wave_reduce(kind(j), acc[j]);
+        }
+        if (lane == WAVE - 1) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                __hip_atomic_store(out + 3 * blk + j, acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned *count = a.foldn + ((long long)b * FOLD_GROUPS + g) * FOLD_PAD;
+        last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nwg - 1;
+        if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last || wave > 0) return;
+    // the blocks in turn: 64 of them at a time in the lanes
+    double v[3];
+    for (int k0 = 0; k0 < nblk; k0 += WAVE) {
+        double y[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            y[j] = __hip_atomic_load(out + 3 * min(k0 + lane, nblk - 1) + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int k = 0; k < min(WAVE, nblk - k0); ++k)
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                const double y = op(j, acc[j], x[i][j]);
-                acc[j] = t0 + i * NT < n ? y : acc[j];
+                const double z = lane_value(y[j], k);
+                v[j] = k0 + k == 0 ? z : stat_op(kind(j), v[j], z);
             }
     }
-    if (speeds) {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) acc[j] = wave_reduce(1, acc[j]);
-    } else {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) acc[j] = wave_reduce(j, acc[j]);
-    }
-    if (lane != WAVE - 1) return;
-    double *out = a.foldw + ((long long)b * FOLD_GROUPS + g) * FOLD_WAVES * 3;
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-        __hip_atomic_store(out + 3 * wave + j, acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    unsigned *count = a.foldn + (long long)b * FOLD_GROUPS + g;
-    if (__hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)NW - 1) return;
-    __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    double v[3];
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const double x = __hip_atomic_load(out + 3 * w + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            v[j] = w == 0 ? x : op(j, v[j], x);
-        }
-    double *r = a.red + (long long)b * NSTAT + row;
-    r[0] = v[0];
-    if (speeds) {
-        r[1] = v[1];
-    } else {
-        r[1] = inv_sigma(v[0], v[1], v[2], (double)(g < NC ? I.np : I.nd));
-        r[2] = v[2];
+    if (lane == 0) {
+        double *red = a.red + (long long)b * NSTAT + row;
+        red[0] = v[0];
+        red[1] = speeds ? v[1] : inv_sigma(v[0], v[1], v[2], (double)(g < NC ? I.np : I.nd));
+        if (!speeds) red[2] = v[2];
     }
 }
 
@@ -1137,32 +1139,31 @@ hipError_t launch_stage_1d(const StageArgs &a, int kmax, int flux, int tile, hip
     return launch(pick<0>(kmax, flux, ti), b.tend - b.tbeg, tile, b, s);   // one workgroup per tile
 }
 
-// Instances of more tiles than this are folded by k_fold_rows: up to
-// it, k_fold's threads have all their tiles' rows in flight in one round of loads
-// (6.2 us for 512 instances of up to 129 tiles), beyond it they wait round by round.
-static int fold_rows(int tile) { return 2 * nthreads(tile); }
+// Instances of more tiles than this are folded by k_fold_rows: up to it, k_fold has
+// all the tiles' rows in flight in one round of loads (6.2 us for 512 instances of
+// up to 129 tiles), beyond it it waits round by round.
+constexpr int FOLD_ROWS = 320;
 
 static hipError_t launch_fold(const StageArgs &a, int src, int flux, int tile, int maxpart, hipStream_t s) {
-    // the reduction uses nthreads(tile) threads, as a stage workgroup does
-    // (an extra-wave launch's fifth wave takes no part in it either)
     if (!a.red || tile_index(tile) < 0) return hipErrorInvalidValue;
     void *fn = nullptr;
     const int nc = flux == 0 || flux == 1 ? 1 : 3;
-    const bool rows = maxpart > fold_rows(tile);
-    if (rows) {
-        if (nc == 1) fn = tile == 32 ? (void *)k_fold_rows<1, 32> : (tile == 64 ? (void *)k_fold_rows<1, 64> : (void *)k_fold_rows<1, 128>);
-        else fn = tile == 32 ? (void *)k_fold_rows<3, 32> : (tile == 64 ? (void *)k_fold_rows<3, 64> : (void *)k_fold_rows<3, 128>);
-    } else {
-        if (nc == 1) fn = tile == 32 ? (void *)k_fold<1, 32> : (tile == 64 ? (void *)k_fold<1, 64> : (void *)k_fold<1, 128>);
-        else fn = tile == 32 ? (void *)k_fold<3, 32> : (tile == 64 ? (void *)k_fold<3, 64> : (void *)k_fold<3, 128>);
-    }
+    const bool rows = maxpart > FOLD_ROWS;
+    constexpr int P32 = Partials<nthreads(32), 3>::PRE, P64 = Partials<nthreads(64), 3>::PRE;
+    static_assert(P64 == Partials<nthreads(128), 3>::PRE, "one block size for tiles of 64 and 128");
+    if (rows && tile == 32) fn = nc == 1 ? (void *)k_fold_rows<1, P32> : (void *)k_fold_rows<3, P32>;
+    else if (rows) fn = nc == 1 ? (void *)k_fold_rows<1, P64> : (void *)k_fold_rows<3, P64>;
+    else if (nc == 1) fn = tile == 32 ? (void *)k_fold<1, 32> : (tile == 64 ? (void *)k_fold<1, 64> : (void *)k_fold<1, 128>);
+    else fn = tile == 32 ? (void *)k_fold<3, 32> : (tile == 64 ? (void *)k_fold<3, 64> : (void *)k_fold<3, 128>);
     StageArgs copy = a;
     int srcv = src;
     void *args[] = {&copy, &srcv};
-    const int nw = nthreads(tile) / WAVE;
-    return rows ? hipLaunchKernel(fn, dim3(a.ninst, 2 * nc + 1, nw), dim3(WAVE), args, 0, s)
+    return rows ? hipLaunchKernel(fn, dim3(a.ninst, 2 * nc + 1, (a.foldblk + FOLD_WG - 1) / FOLD_WG),
+                                  dim3(FOLD_WG * WAVE), args, 0, s)
                 : hipLaunchKernel(fn, dim3(a.ninst), dim3(nthreads(tile)), args, 0, s);
 }
+
+int fold_block_1d(int tile) { return WAVE * (tile == 32 ? Partials<nthreads(32), 3>::PRE : Partials<nthreads(64), 3>::PRE); }
 
 hipError_t launch_fold_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s) {
     // the partials the stage (a.l, a.par) reads: those of the previous global stage

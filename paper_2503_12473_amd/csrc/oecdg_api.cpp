@@ -54,7 +54,9 @@ struct oecdg_handle {
     double *A = nullptr;     // AC | AD: classical RK4 only (sum of earlier stages for the last one)
     int *err = nullptr;
     unsigned *bar = nullptr;
-    double *red = nullptr;   // [nbatch][NSTAT] statistics folded by k_fold, then the scratch of k_fold_rows
+    double *red = nullptr;   // [nbatch][NSTAT] statistics folded by k_fold
+    double *foldw = nullptr; // block results and arrival counts of k_fold_rows
+    int foldblk = 0;
     unsigned *foldn = nullptr;
     // pinned host mirrors (one block: records, then flags), host-coherent and
     // mapped: the final kernel of a short run writes them directly
@@ -229,6 +231,9 @@ int build_tiles(oecdg_handle *h) {
     }
     if (h->tiles_d) (void)hipFree(h->tiles_d), h->tiles_d = nullptr;
     if (h->part) (void)hipFree(h->part), h->part = nullptr;
+    if (h->foldw) (void)hipFree(h->foldw), h->foldw = nullptr;
+    h->foldblk = (h->maxpart + fold_block_1d(T) - 1) / fold_block_1d(T);
+    HIPCHK(h, hipMalloc(&h->foldw, sizeof(double) * 3 * FOLD_GROUPS * h->foldblk * (size_t)h->nbatch));
     HIPCHK(h, hipMalloc(&h->tiles_d, sizeof(Tile1D) * h->tiles_h.size()));
     HIPCHK(h, hipMemcpy(h->tiles_d, h->tiles_h.data(), sizeof(Tile1D) * h->tiles_h.size(), hipMemcpyHostToDevice));
     HIPCHK(h, hipMemcpy(h->inst_d, h->inst_h.data(), sizeof(Inst1D) * h->nbatch, hipMemcpyHostToDevice));
@@ -281,7 +286,8 @@ StageArgs base_args(oecdg_handle *h) {
     a.ninst = h->nbatch;
     if (h->nbatch == 1) a.inst0 = h->inst_h[0];
     a.red = fold_on(h) ? h->red : nullptr;
-    a.foldw = h->red + (size_t)NSTAT * h->nbatch;
+    a.foldw = h->foldw;
+    a.foldblk = h->foldblk;
     a.foldn = h->foldn;
     a.t_end = INFINITY;
     return a;
@@ -902,10 +908,10 @@ int oecdg_init(const oecdg_desc *d, int32_t nbatch, void *stream, oecdg_handle *
     ALLOC(h->U, sizeof(double) * (h->totC + h->totD));
     if (h->rk == 4) ALLOC(h->A, sizeof(double) * (h->totC + h->totD));
     ALLOC(h->bar, sizeof(unsigned) * 2);
-    ALLOC(h->red, sizeof(double) * (NSTAT + FOLD_GROUPS * FOLD_WAVES * 3) * nbatch);
-    ALLOC(h->foldn, sizeof(unsigned) * FOLD_GROUPS * nbatch);
+    ALLOC(h->red, sizeof(double) * NSTAT * nbatch);
+    ALLOC(h->foldn, sizeof(unsigned) * FOLD_PAD * FOLD_GROUPS * nbatch);
 #undef ALLOC
-    const std::vector<unsigned> none((size_t)FOLD_GROUPS * nbatch, 0u);
+    const std::vector<unsigned> none((size_t)FOLD_PAD * FOLD_GROUPS * nbatch, 0u);
     if (hipMemcpy(h->foldn, none.data(), sizeof(unsigned) * none.size(), hipMemcpyHostToDevice) != hipSuccess) {
         oecdg_destroy(h);
         return OECDG_EHIP;
@@ -1099,6 +1105,7 @@ void oecdg_destroy(oecdg_handle *h) {
     (void)hipFree(h->bar);
     (void)hipFree(h->red);
     (void)hipFree(h->foldn);
+    (void)hipFree(h->foldw);
     if (h->fin_h) (void)hipHostFree(h->fin_h);
     if (h->ext2d) {
         oecdg::destroy_2d(h);

@@ -107,8 +107,6 @@ __device__ inline int xcd_tile(int b, int n) {
 
 // ------------------------------------------------------------- reductions ---
 
-__device__ inline int stat_kind(int j) { return j >= ST_BETA ? 1 : j % 3; }
-
 __device__ inline double stat_identity(int kind) {
     return kind == 0 ? 0.0 : (kind == 1 ? -INFINITY : INFINITY);
 }
@@ -155,6 +153,13 @@ __device__ inline double dpp_all(double v) {
     return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
+// Value of lane k (uniform) in every lane.
+__device__ inline double lane_value(double v, int k) {
+    const long long x = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_readlane((int)x, k), hi = __builtin_amdgcn_readlane((int)(x >> 32), k);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
 // Value of the partner lane (lane ^ 1).
 __device__ inline double pair_swap(double v) { return dpp_all<0xB1>(v); }   // quad_perm [1,0,3,2]
 
@@ -172,143 +177,117 @@ __device__ inline double wave_reduce(int kind, double v) {
     return v;
 }
 
-// Rows of the partial statistics a consumer needs: (mesh, q, kind) for the
-// NC components, then the two wave-speed rows.
-template <int NC>
-__device__ inline int stat_row(int i) {
-    if (i >= 6 * NC) return ST_BETA + (i - 6 * NC);
-    const int mesh = i / (3 * NC), r = i - mesh * 3 * NC;
-    return stat_index(mesh, r / 3, r % 3);
-}
-
 // Per-tile partial statistics are stored [tile][NSTAT]: the NSTAT values of a
 // tile are contiguous (one 160-byte record, read with 16-byte loads).
 __device__ inline const double *part_tile(const double *part, long long tile) { return part + tile * NSTAT; }
 
-// Reduction of the per-tile partial statistics of tiles [tile0, tile0+ntiles)
-// in a fixed order: per-thread strided accumulation over tiles, a butterfly
-// within each wave, then the waves in order.  Split in two so that the loads of
-// the first two tiles per thread can be issued together with the kernel's other
-// independent loads.  The wave-speed rows take part only when ns = 6 NC + 2.
-template <int NC>
+// Reduction of the per-tile partial statistics of tiles [tile0, tile0+ntiles) in a
+// fixed order: in blocks of PRE x 64 tiles, of which lane l of a wave takes tiles
+// l, l + 64, ... in turn, then the wave's tree; the blocks in turn.  A wave of the workgroup reduces the rows of some of the
+// (mesh, component) triples over all tiles (and wave 0 and 1 one of the wave-speed
+// rows): with every wave reducing all 18 rows of a third of the tiles, the trees
+// were the longest phase of a stage launch.  Split in two so that the loads of the
+// first PRE tiles per lane are issued together with the kernel's other independent
+// loads (5 x 64 tiles hold the 257 columns of a mesh that fills the chip).
+template <int NT, int NC>
 struct Partials {
-    static constexpr int NS = 6 * NC + 2;
-    double v[2][NS];
+    static constexpr int NS = 6 * NC + 2, NW = (NT + WAVE - 1) / WAVE;
+    static constexpr int PRE = NT <= 2 * WAVE ? 3 : 5;       // tiles of 32 serve meshes of up to 129 columns
+    static constexpr int TPW = (2 * NC + NW - 1) / NW;       // triples per wave
+    double v[PRE][3 * TPW], beta[PRE];
 };
 
-// One tile's record into v (consumer order i -> row stat_row<NC>(i)).
-template <int NC>
-__device__ inline void load_tile_record(const double *rec, double (&v)[Partials<NC>::NS]) {
-    double r[NSTAT];
-    const double2 *q = reinterpret_cast<const double2 *>(rec);
-#pragma unroll
-    for (int j = 0; j < NSTAT / 2; ++j) {
-        const double2 x = q[j];
-        r[2 * j] = x.x;
-        r[2 * j + 1] = x.y;
-    }
-#pragma unroll
-    for (int i = 0; i < Partials<NC>::NS; ++i) v[i] = r[stat_row<NC>(i)];
-}
-
-// The loads of the first two tiles per thread (t and t + NT, clamped to a valid
-// tile; the selects are applied in the reduction, so that no wait follows the
-// loads before the kernel's other independent loads are issued).  A wave none
-// of whose threads has a second tile skips those loads.
 template <int NT, int NC>
-__device__ inline void load_partials_raw(const double *part, int tile0, int ntiles, Partials<NC> &p) {
-    const int tid = threadIdx.x;
-    load_tile_record<NC>(part_tile(part, tile0 + min(tid, ntiles - 1)), p.v[0]);
-    if (__builtin_amdgcn_readfirstlane(tid) + NT < ntiles) {
-        load_tile_record<NC>(part_tile(part, tile0 + min(tid + NT, ntiles - 1)), p.v[1]);
+__device__ inline int first_triple() {
+    return __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE) * Partials<NT, NC>::TPW;
+}
+// Row of a triple's sum in a record (max and min follow).
+template <int NC>
+__device__ inline int triple_row(int tr) { return NC == 3 ? 3 * tr : 9 * tr; }
+
+template <int NT, int NC>
+__device__ __forceinline__ void load_triples(const double *rec, int tr0, double (&v)[3 * Partials<NT, NC>::TPW]) {
+    constexpr int TPW = Partials<NT, NC>::TPW;
+    if constexpr (NC == 3 && TPW == 2) {             // 48 bytes, 16-byte aligned
+        const double2 *q = reinterpret_cast<const double2 *>(rec + 3 * tr0);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double2 x = q[j];
+            v[2 * j] = x.x;
+            v[2 * j + 1] = x.y;
+        }
     } else {
 #pragma unroll
-        for (int i = 0; i < Partials<NC>::NS; ++i) p.v[1][i] = 0.0;   // not used (tid + NT >= ntiles)
+        for (int k = 0; k < TPW; ++k)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) v[3 * k + j] = rec[triple_row<NC>(min(tr0 + k, 2 * NC - 1)) + j];
     }
 }
 
-// Per-wave part of the reduction: the thread's tiles (selects of the first
-// two, the rest strided), then a fixed-order butterfly; lane WAVE-1 writes
-// scratch[wave][NS].
 template <int NT, int NC>
-__device__ inline void wave_partials(const Partials<NC> &p, const double *part, int tile0, int ntiles, int ns,
-                                     double *scratch) {
-    constexpr int NS = Partials<NC>::NS;
-    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    double acc[NS];
+__device__ __forceinline__ void load_partials(const double *part, int tile0, int ntiles, bool beta, Partials<NT, NC> &p) {
+    using P = Partials<NT, NC>;
+    const int lane = threadIdx.x % WAVE, tr0 = first_triple<NT, NC>();
+    const int brow = ST_BETA + (tr0 > 0);
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        const double id = stat_identity(stat_kind(stat_row<NC>(i)));
-        const double x0 = (i < ns && tid < ntiles) ? p.v[0][i] : id;
-        const double x1 = (i < ns && tid + NT < ntiles) ? p.v[1][i] : id;
-        acc[i] = stat_op(stat_kind(stat_row<NC>(i)), x0, x1);
+    for (int i = 0; i < P::PRE; ++i) {
+        if (i * WAVE >= ntiles || tr0 >= 2 * NC) break;      // uniform
+        const double *rec = part_tile(part, tile0 + min(lane + i * WAVE, ntiles - 1));
+        load_triples<NT, NC>(rec, tr0, p.v[i]);
+        if (beta) p.beta[i] = rec[brow];
     }
-    for (int t = tid + 2 * NT; t < ntiles; t += NT) {   // more than two tiles per thread
-        const double *rec = part_tile(part, tile0 + t);
+}
+
+// The rest of the reduction; the rows (triples in order, then the wave speeds when
+// beta) are in out[0 .. NS) (LDS) after the barrier that ends it.
+template <int NT, int NC>
+__device__ __forceinline__ void finish_partials(Partials<NT, NC> &p, const double *part, int tile0, int ntiles, bool beta,
+                                                double *out) {
+    using P = Partials<NT, NC>;
+    constexpr int TPW = P::TPW, BLOCK = P::PRE * WAVE;
+    const int lane = threadIdx.x % WAVE, tr0 = first_triple<NT, NC>();
+    if (tr0 < 2 * NC) {                                      // uniform
+        double tot[3 * TPW], totb = -INFINITY;               // (in lane 63)
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            if (i < ns) {
-                const int j = stat_row<NC>(i);
-                acc[i] = stat_op(stat_kind(j), acc[i], rec[j]);
+        for (int r = 0; r < 3 * TPW; ++r) tot[r] = stat_identity(r % 3);
+        for (int t0 = 0;;) {
+            double acc[3 * TPW], b = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 3 * TPW; ++r) acc[r] = stat_identity(r % 3);
+#pragma unroll
+            for (int i = 0; i < P::PRE; ++i) {
+                if (i * WAVE >= ntiles - t0) break;          // uniform
+                const bool in = lane + i * WAVE < ntiles - t0;
+#pragma unroll
+                for (int r = 0; r < 3 * TPW; ++r)
+                    acc[r] = stat_op(r % 3, acc[r], in ? p.v[i][r] : stat_identity(r % 3));
+                if (beta) b = max_d(b, in ? p.beta[i] : -INFINITY);
             }
+#pragma unroll
+            for (int r = 0; r < 3 * TPW; ++r) {
+                acc[r] = wave_reduce(r % 3, acc[r]);
+                tot[r] = t0 == 0 ? acc[r] : stat_op(r % 3, tot[r], acc[r]);
+            }
+            if (beta) totb = max_d(totb, wave_reduce(1, b));
+            t0 += BLOCK;
+            if (t0 >= ntiles) break;                         // uniform
+            load_partials<NT, NC>(part, tile0 + t0, ntiles - t0, beta, p);
+        }
+        if (lane == WAVE - 1) {
+#pragma unroll
+            for (int r = 0; r < 3 * TPW; ++r)
+                if (tr0 + r / 3 < 2 * NC) out[3 * tr0 + r] = tot[r];
+            if (beta && tr0 <= TPW) out[6 * NC + (tr0 > 0)] = totb;
         }
     }
-#pragma unroll
-    for (int i = 0; i < NS; ++i) acc[i] = wave_reduce(stat_kind(stat_row<NC>(i)), acc[i]);
-    if (lane == WAVE - 1) {
-#pragma unroll
-        for (int i = 0; i < NS; ++i) scratch[wave * NS + i] = acc[i];
-    }
-}
-
-// The waves' results combined in order by thread i < NS into red[row] (LDS).
-template <int NT, int NC>
-__device__ void finish_partials(const Partials<NC> &p, const double *part, int tile0, int ntiles, int ns, double *red,
-                                double *scratch) {
-    constexpr int NS = Partials<NC>::NS;
-    constexpr int NW = (NT + WAVE - 1) / WAVE;
-    const int tid = threadIdx.x;
-    wave_partials<NT, NC>(p, part, tile0, ntiles, ns, scratch);
-    __syncthreads();
-    if (tid < NS) {
-        const int kd = stat_kind(stat_row<NC>(tid));
-        double v = scratch[tid];
-        for (int w = 1; w < NW; ++w) v = stat_op(kd, v, scratch[w * NS + tid]);
-        red[stat_row<NC>(tid)] = v;
-    }
     __syncthreads();
 }
 
-// The same reduction, with every thread combining the per-wave results of the rows
-// of its own mesh itself (the order of finish_partials), after one barrier:
-// own[3 q + kind], and with ns = NS the wave speeds of both meshes.
 template <int NT, int NC>
-__device__ inline void finish_partials_mesh(const Partials<NC> &p, const double *part, int tile0, int ntiles, int ns,
-                                            int mesh, double (&own)[3 * NC], double (&beta)[2], double *scratch) {
-    constexpr int NS = Partials<NC>::NS;
-    constexpr int NW = (NT + WAVE - 1) / WAVE;
-    wave_partials<NT, NC>(p, part, tile0, ntiles, ns, scratch);
-    __syncthreads();
-    auto combine = [&](int kind, const double *s) {
-        double v = s[0];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) v = stat_op(kind, v, s[w * NS]);
-        return v;
-    };
-#pragma unroll
-    for (int i = 0; i < 3 * NC; ++i) own[i] = combine(i % 3, scratch + mesh * 3 * NC + i);
-    if (ns == NS) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) beta[j] = combine(1, scratch + 6 * NC + j);
-    }
-}
-
-template <int NT, int NC>
-__device__ void reduce_instance(const double *part, int tile0, int ntiles, bool beta, double *red, double *scratch) {
-    const int ns = beta ? Partials<NC>::NS : Partials<NC>::NS - 2;
-    Partials<NC> p;
-    load_partials_raw<NT, NC>(part, tile0, ntiles, p);
-    finish_partials<NT, NC>(p, part, tile0, ntiles, ns, red, scratch);
+__device__ __forceinline__ void reduce_instance(const double *part, int tile0, int ntiles, bool beta, double *out) {
+    Partials<NT, NC> p;
+    load_partials<NT, NC>(part, tile0, ntiles, beta, p);
+    finish_partials<NT, NC>(p, part, tile0, ntiles, beta, out);
 }
 
 }  // namespace oecdg

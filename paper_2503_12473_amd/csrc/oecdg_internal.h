@@ -16,8 +16,9 @@ constexpr int MAXK = 3;
 // sigma sample points; ST_BETA = largest wave speed at a cell average.
 constexpr int NSTAT = 20;
 constexpr int ST_BETA = 18;
-// Folds of many tiles: groups (mesh and component, and the wave speeds) and the most waves per group.
-constexpr int FOLD_GROUPS = 7, FOLD_WAVES = 5;
+// Folds of many tiles: groups (a mesh and component, and the wave speeds) at most.
+constexpr int FOLD_GROUPS = 7;
+constexpr int FOLD_PAD = 32;                 // of their arrival counts: a 128-byte line each
 
 __host__ __device__ constexpr int stat_index(int mesh, int q, int kind) { return (mesh * 3 + q) * 3 + kind; }
 
@@ -108,8 +109,9 @@ struct StageArgs {
     double *AC, *AD;         // classical RK4: weighted sum of the damped inputs of stages 1 and 2
     double *red;             // batched launches: [ninst][NSTAT] statistics reduced by k_fold (else null), with
                              // 1 / sigma (0 where sigma is 0) in the place of the max
-    double *foldw;           // [ninst][FOLD_GROUPS][FOLD_WAVES][3] waves' results of k_fold_rows
-    unsigned *foldn;         // [ninst][FOLD_GROUPS] arrivals (0 between launches)
+    double *foldw;           // [ninst][FOLD_GROUPS][foldblk][3] block results of k_fold_rows
+    int foldblk;             // blocks of tiles of the largest instance
+    unsigned *foldn;         // [ninst][FOLD_GROUPS] arrivals (0 between launches), FOLD_PAD apart
     int *err;                // [0] non-finite, [1] non-physical, [2] barrier timeout, [3] step+1 of an error
     int rk, ns;              // RK method (rk_stage) and its stages per step
     RKStage rs;              // rk_stage(rk, l), set by the stage launcher (the persistent launch forms its own)
@@ -166,6 +168,7 @@ hipError_t launch_stage_1d(const StageArgs &a, int kmax, int flux, int tile, hip
 // Statistics into a.red: of the state the stage (a.l, a.par) reads, and of the
 // state the final kernel damps.  maxpart: the most partial columns of an instance.
 hipError_t launch_fold_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s);
+int fold_block_1d(int tile);                                    // tiles of a block of the reduction
 hipError_t launch_fold_final_1d(const StageArgs &a, int flux, int tile, int maxpart, hipStream_t s);
 hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s);
 hipError_t launch_persistent_1d(const StageArgs &a, int kmax, int flux, int tile, int grid,
