@@ -38,7 +38,8 @@
 namespace oecdg {
 
 // Threads per workgroup: one per cell for the T primal and the T dual cells of
-// a tile, and one wave for the cells next to it.
+// a tile, and one wave for the cells next to it.  (The folded stage kernel has no
+// wave for those: its first wave damps them after its own cells.)
 __host__ __device__ constexpr int nthreads(int T) { return 2 * T + WAVE; }
 
 // ------------------------------------------------------------ cell kernels ---
@@ -196,6 +197,28 @@ struct TCell {
     int mesh, col, g;
     bool has, damps, owned;
 };
+__device__ inline int wrap_cell(const Inst1D &I, int mesh, int g) {
+    if (I.bc == 0) {                         // periodic (meshes shorter than a tile too)
+        const int n = mesh == 0 ? I.np : I.nd;
+        g = g < 0 ? g + n : (g >= n ? g - n : g);
+        if (g < 0 || g >= n) g = ((g % n) + n) % n;
+    }
+    return g;
+}
+
+// The cells next to the tile, by lane (the index not yet wrapped).
+template <int T>
+__device__ inline TCell halo_cell(int lane, int i0) {
+    TCell c;
+    c.mesh = (lane == 1 || lane == 3 || lane == 4) ? 1 : 0;
+    c.g = (lane == 0 || lane == 3) ? i0 - 1 : (lane == 4 ? i0 + T + 1 : i0 + T);
+    c.col = (lane == 0 || lane == 3) ? 0 : (lane == 4 ? T + 2 : T + 1);
+    c.has = lane < 5;
+    c.damps = lane < 3;
+    c.owned = false;
+    return c;
+}
+
 template <int T>
 __device__ inline TCell tile_cell(const Inst1D &I, int tile, int i0, bool xwl) {
     const int tid = threadIdx.x;
@@ -209,20 +232,11 @@ __device__ inline TCell tile_cell(const Inst1D &I, int tile, int i0, bool xwl) {
         c.has = c.damps = true;
         c.owned = g < (c.mesh == 0 ? I.np : I.nd);
     } else {
-        const int lane = tid - 2 * T;
-        c.mesh = (lane == 1 || lane == 3 || lane == 4) ? 1 : 0;
-        g = (lane == 0 || lane == 3) ? i0 - 1 : (lane == 4 ? i0 + T + 1 : i0 + T);
-        c.col = (lane == 0 || lane == 3) ? 0 : (lane == 4 ? T + 2 : T + 1);
-        c.has = lane < 5;
-        c.damps = lane < 3;
-        c.owned = xwl && lane == 1 && I.tail && tile == I.tile0 + I.ntiles - 1 && g < I.nd;
+        c = halo_cell<T>(tid - 2 * T, i0);
+        g = c.g;
+        c.owned = xwl && tid == 2 * T + 1 && I.tail && tile == I.tile0 + I.ntiles - 1 && g < I.nd;
     }
-    if (I.bc == 0) {                         // periodic (meshes shorter than a tile too)
-        const int n = c.mesh == 0 ? I.np : I.nd;
-        g = g < 0 ? g + n : (g >= n ? g - n : g);
-        if (g < 0 || g >= n) g = ((g % n) + n) % n;
-    }
-    c.g = g;
+    c.g = wrap_cell(I, c.mesh, g);
     return c;
 }
 
@@ -489,6 +503,31 @@ constexpr int lds_width(int T) { return T + 3; }
 constexpr int lds_doubles(int K, int NC, int T) { return 4 * NC * (K + 1) * lds_width(T); }
 constexpr int scratch_doubles(int T) { return NSTAT * (T == 128 ? 5 : 1); }   // (T = 128: a row of statistics per wave)
 
+// The undamped cell of a thread into the LDS image (a wall ghost: the mirror image
+// of its end cell).
+template <int K, int FLUX, int T>
+__device__ inline void put_undamped(const TCell &c, const CellIn<K, FLUX> &ci, double *smem) {
+    constexpr int NC = FluxT<FLUX>::NC, K1 = K + 1, W = lds_width(T);
+    if (!c.has) return;
+    double g[NC][K1];
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+        for (int m = 0; m < K1; ++m) g[q][m] = ci.mirror ? mirror_sign(q, m) * ci.own[q][m] : ci.own[q][m];
+    lds_put<K, NC, W>(smem + (2 + c.mesh) * NC * K1 * W, c.col, g);
+}
+
+// The thread's cell damped (the overlapping cells from the undamped image), in
+// ci.own and in the damped image.
+template <int K, int FLUX, int T>
+__device__ inline void damp_and_put(const Inst1D &I, const TCell &c, CellIn<K, FLUX> &ci,
+                                    const double (&isig)[FluxT<FLUX>::NC], double tau, bool damp, double *smem) {
+    constexpr int NC = FluxT<FLUX>::NC, W = lds_width(T), PER = NC * (K + 1) * W;
+    if (damp && c.damps && (ci.real || ci.mirror)) lds_overlaps<K, FLUX, W>(c, smem + (3 - c.mesh) * PER, ci);
+    damp_cell<K, FLUX>(I, c, ci, isig, tau, damp);
+    if (c.damps) lds_put<K, NC, W>(smem + c.mesh * PER, c.col, ci.own);
+}
+
 // ---------------------------------------------------------- stage tile ---
 
 // FOLDED: the instance's statistics were reduced by k_fold into a.red (batched
@@ -539,8 +578,13 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
     // previous step's scalars, the thread's cell and its overlapping cells, u^n
     // and the RK4 sum of the cell, the previous stage's partial statistics.
     const Slot cur = ld_slot(&S[par], coh), prev = ld_slot(&S[par ^ 1], coh);
-    CellIn<K, FLUX> ci;
+    CellIn<K, FLUX> ci, hi;
+    TCell hc = halo_cell<T>(tid, i0);
     load_own<K, FLUX>(I, c, a.BC[sp] + I.offC, a.BD[sp] + I.offD, ci);
+    if constexpr (FOLDED) {
+        hc.g = wrap_cell(I, hc.mesh, hc.g);
+        if (tid < WAVE) load_own<K, FLUX>(I, hc, a.BC[sp] + I.offC, a.BD[sp] + I.offD, hi);
+    }
     double un[NC][K1], acc[NC][K1];
 #pragma unroll
     for (int q = 0; q < NC; ++q)
@@ -562,14 +606,16 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
             for (int m = 0; m < K1; ++m) acc[q][m] = AM[(long long)(q * K1 + m) * ncell + gi];
     }
     Partials<NT, NC> pv;
-    double isig[NC], beta[2] = {0.0, 0.0};   // of this thread's mesh; the wave speeds of both
+    double isig[NC], hsig[NC], beta[2] = {0.0, 0.0};   // of this thread's mesh; the wave speeds of both
 #pragma unroll
-    for (int q = 0; q < NC; ++q) isig[q] = 0.0;
+    for (int q = 0; q < NC; ++q) isig[q] = hsig[q] = 0.0;
     if (need_red) {
         if (folded) {
             const double *rd = a.red + (long long)tl.inst * NSTAT;
 #pragma unroll
             for (int q = 0; q < NC; ++q) isig[q] = rd[stat_index(c.mesh, q, 1)];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) hsig[q] = rd[stat_index(hc.mesh, q, 1)];
 #pragma unroll
             for (int j = 0; j < 2; ++j) beta[j] = rd[ST_BETA + j];
         } else {
@@ -588,14 +634,9 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
     // the undamped image (a wall ghost: the mirror image of its end cell), for
     // the overlapping cells of every damped cell; the barrier of the
     // reduction below covers it
-    if (c.has) {
-        double g[NC][K1];
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-#pragma unroll
-            for (int m = 0; m < K1; ++m) g[q][m] = ci.mirror ? mirror_sign(q, m) * ci.own[q][m] : ci.own[q][m];
-        lds_put<K, NC, W>(smem + (2 + c.mesh) * PER, c.col, g);
-    }
+    put_undamped<K, FLUX, T>(c, ci, smem);
+    if constexpr (FOLDED)
+        if (tid < WAVE) put_undamped<K, FLUX, T>(hc, hi, smem);
     if (need_red && !folded) {
         finish_partials<NT, NC>(pv, a.part[sp ^ 1], I.tile0, I.npart, need_beta, scratch);
         if (damp) {
@@ -643,11 +684,10 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
         f->nexec = ld_ll(&f->nexec, coh) + 1;
     }
 
-    if (damp) {
-        if (c.damps && (ci.real || ci.mirror)) lds_overlaps<K, FLUX, W>(c, smem + (3 - c.mesh) * PER, ci);
-    }
-    damp_cell<K, FLUX>(I, c, ci, isig, (l == 0) ? prev.tau : tau, damp);
-    if (c.damps) lds_put<K, NC, W>(smem + c.mesh * PER, c.col, ci.own);
+    const double dtau = (l == 0) ? prev.tau : tau;
+    if constexpr (FOLDED)
+        if (tid < WAVE) damp_and_put<K, FLUX, T>(I, hc, hi, hsig, dtau, damp, smem);
+    damp_and_put<K, FLUX, T>(I, c, ci, isig, dtau, damp, smem);
     __syncthreads();
 
     double out[NC][K1];
@@ -841,8 +881,16 @@ __global__ __launch_bounds__(nthreads(T)) void k_stage(StageArgs a) {
 // instance's per-tile records.  One tile per workgroup, as in k_stage: a
 // loop over tiles kept the stage's uniform values alive across iterations
 // and spilled them from scalar registers into vector lanes.
+// Bound by the FP64 pipes (1440 vector instructions per wave at K = 2) with too few
+// waves to fill them: k_stage's layout, whose third wave damps the five cells next
+// to the tile and then waits, held 8 (K <= 2) or 4 (K = 3) busy waves per CU.  With
+// as many workgroups as a launch with folded statistics has, the same damping in
+// the first wave, one pass more, costs nothing next to 12 (8) busy waves: 138 -> 126
+// us at N = 1000003, P2, and 172 -> 144, 93 -> 85, 72 -> 67 us for the P3, P2 and P1
+// instances of a batch of 512.  (Where every CU has one workgroup, k_stage, the
+// pass would be in the chain of waits.)
 template <int K, int FLUX, int T>
-__global__ __launch_bounds__(nthreads(T), T == 64 && K <= 2 ? 3 : 1) void k_stage_folded(StageArgs a) {
+__global__ __launch_bounds__(2 * T, T == 128 ? 1 : (K <= 2 ? 3 : 2)) void k_stage_folded(StageArgs a) {
     __shared__ double smem[lds_doubles(K, FluxT<FLUX>::NC, T) + scratch_doubles(T)];
     const int tile = a.tbeg + xcd_tile(blockIdx.x, a.tend - a.tbeg);     // one tile per workgroup
     if (tile < a.tend) stage_tile<K, FLUX, T, true>(a, a.l, a.par, a.first, tile, smem, false);
@@ -1110,10 +1158,10 @@ static void *pick(int k, int flux, int ti) {   // batches of mixed degree launch
     }
 }
 
-static hipError_t launch(void *fn, int grid, int tile, const StageArgs &a, hipStream_t s) {
+static hipError_t launch(void *fn, int grid, int threads, const StageArgs &a, hipStream_t s) {
     StageArgs copy = a;
     void *args[] = {&copy};
-    return hipLaunchKernel(fn, dim3(grid), dim3(nthreads(tile)), args, 0, s);
+    return hipLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, s);
 }
 
 hipError_t launch_init_1d(const StageArgs &a, int ninst, hipStream_t s) {
@@ -1124,7 +1172,7 @@ hipError_t launch_init_1d(const StageArgs &a, int ninst, hipStream_t s) {
 hipError_t launch_stats_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s) {
     int ti = kernel_index(tile, a.tailwave);
     if (ti < 0) return hipErrorInvalidValue;
-    return launch(pick<1>(kmax, flux, ti), a.tend - a.tbeg, tile, a, s);
+    return launch(pick<1>(kmax, flux, ti), a.tend - a.tbeg, nthreads(tile), a, s);
 }
 
 hipError_t launch_stage_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s) {
@@ -1134,9 +1182,9 @@ hipError_t launch_stage_1d(const StageArgs &a, int kmax, int flux, int tile, hip
     b.rs = rk_stage(a.rk, a.l);              // the stage's coefficients, ready in the kernel arguments
     if (a.red) {                             // statistics folded by launch_fold_1d
         if (a.tailwave) return hipErrorInvalidValue;
-        return launch(pick<4>(kmax, flux, ti), b.tend - b.tbeg, tile, b, s);   // one workgroup per tile
+        return launch(pick<4>(kmax, flux, ti), b.tend - b.tbeg, 2 * tile, b, s);   // one workgroup per tile
     }
-    return launch(pick<0>(kmax, flux, ti), b.tend - b.tbeg, tile, b, s);   // one workgroup per tile
+    return launch(pick<0>(kmax, flux, ti), b.tend - b.tbeg, nthreads(tile), b, s);   // one workgroup per tile
 }
 
 // Instances of more tiles than this are folded by k_fold_rows: up to it, k_fold has
@@ -1177,7 +1225,7 @@ hipError_t launch_fold_final_1d(const StageArgs &a, int flux, int tile, int maxp
 hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s) {
     int ti = kernel_index(tile, a.tailwave);
     if (ti < 0) return hipErrorInvalidValue;
-    return launch(pick<2>(kmax, flux, ti), a.tend - a.tbeg, tile, a, s);
+    return launch(pick<2>(kmax, flux, ti), a.tend - a.tbeg, nthreads(tile), a, s);
 }
 
 int persistent_max_grid_1d(int kmax, int flux, int tile, bool tailwave) {
