@@ -240,21 +240,6 @@ __device__ inline TCell tile_cell(const Inst1D &I, int tile, int i0, bool xwl) {
     return c;
 }
 
-// Indices of the two cells of the other mesh that overlap cell g of `mesh`
-// (left, right): primal g -> dual g, g + 1; dual g -> primal g - 1, g
-// (periodic meshes wrapped; a primal -1 or np is a ghost for cell_pre).
-__device__ inline void overlap_cells(const Inst1D &I, int mesh, int g, int &l, int &r) {
-    if (mesh == 0) {
-        l = g;
-        r = g + 1;
-        if (I.bc == 0 && r >= I.nd) r -= I.nd;
-    } else {
-        l = g - 1;
-        r = g;
-        if (I.bc == 0 && l < 0) l += I.np;
-    }
-}
-
 template <int K, int NC, int W>
 __device__ inline void lds_cell(const double *s, int col, double (&c)[NC][K + 1]) {
 #pragma unroll
@@ -285,26 +270,9 @@ struct CellIn {
     bool mirror;                             // a reflective-wall ghost: damp the end cell, then mirror it
 };
 
-template <int K, int FLUX>
-__device__ inline void load_cell_in(const Inst1D &I, const TCell &c, const double *__restrict__ inC,
-                                    const double *__restrict__ inD, CellIn<K, FLUX> &ci) {
-    const int n = c.mesh == 0 ? I.np : I.nd;
-    ci.real = c.has && c.g >= 0 && c.g < n;
-    ci.mirror = false;
-    if constexpr (FLUX == 3) ci.mirror = c.has && c.mesh == 0 && !ci.real && I.bc == 2;
-    // the cell whose values (and neighbours) are loaded: itself, or the end
-    // cell next to a wall ghost
-    const int sg = ci.mirror ? (c.g < 0 ? 0 : I.np - 1) : c.g;
-    cell_pre<K, FLUX>(I, c.mesh, sg, inC, inD, ci.own);
-    int l, r;
-    overlap_cells(I, c.mesh, ci.real || ci.mirror ? sg : 0, l, r);
-    cell_pre<K, FLUX>(I, 1 - c.mesh, l, inC, inD, ci.nl);
-    cell_pre<K, FLUX>(I, 1 - c.mesh, r, inC, inD, ci.nr);
-}
-
-// The stage kernel's variant: only the thread's own cell from memory (a wall
-// ghost's thread: the end cell); the overlapping cells come from the tile's
-// undamped image in LDS (lds_overlaps).
+// Only the thread's own cell from memory (a damping wall ghost's thread: the end
+// cell); the overlapping cells come from the tile's undamped image in LDS
+// (lds_overlaps).
 template <int K, int FLUX>
 __device__ inline void load_own(const Inst1D &I, const TCell &c, const double *__restrict__ inC,
                                 const double *__restrict__ inD, CellIn<K, FLUX> &ci) {
@@ -802,9 +770,21 @@ __device__ void final_tile(const StageArgs &a, int tile, double *smem, bool xwl)
     const int bp = (int)((a.ns * N) & 1);   // buffer holding the last stage's output (or the input when N = 0)
     double *scratch = smem + lds_doubles(K, NC, T);
     const bool damp = N > 0 && I.oe && K > 0;
-    const TCell c = tile_cell<T>(I, tile, tl.i0, xwl);
+    // the undamped image of the tile and of the cells next to it (without the wave
+    // for these, in a folded launch, by the first wave); a wall ghost comes mirrored
+    TCell c = tile_cell<T>(I, tile, tl.i0, xwl);
+    c.damps = c.owned;
     CellIn<K, FLUX> ci;
-    load_cell_in<K, FLUX>(I, c, a.BC[bp] + I.offC, a.BD[bp] + I.offD, ci);
+    load_own<K, FLUX>(I, c, a.BC[bp] + I.offC, a.BD[bp] + I.offD, ci);
+    if (blockDim.x == 2 * T && threadIdx.x < WAVE) {
+        TCell hc = halo_cell<T>(threadIdx.x, tl.i0);
+        hc.damps = false;
+        hc.g = wrap_cell(I, hc.mesh, hc.g);
+        CellIn<K, FLUX> hi;
+        load_own<K, FLUX>(I, hc, a.BC[bp] + I.offC, a.BD[bp] + I.offD, hi);
+        put_undamped<K, FLUX, T>(hc, hi, smem);
+    }
+    put_undamped<K, FLUX, T>(c, ci, smem);
     double isig[NC];
 #pragma unroll
     for (int q = 0; q < NC; ++q) isig[q] = 0.0;
@@ -819,6 +799,8 @@ __device__ void final_tile(const StageArgs &a, int tile, double *smem, bool xwl)
             for (int q = 0; q < NC; ++q) isig[q] = inv_sigma(own[3 * q], own[3 * q + 1], own[3 * q + 2], ncell);
         }
     }
+    __syncthreads();
+    if (damp && c.owned) lds_overlaps<K, FLUX, lds_width(T)>(c, smem + (3 - c.mesh) * NC * K1 * lds_width(T), ci);
     damp_cell<K, FLUX>(I, c, ci, isig, tau, damp);
     if (c.owned) {
         const int ncell = c.mesh == 0 ? I.np : I.nd;
@@ -1224,8 +1206,8 @@ hipError_t launch_fold_final_1d(const StageArgs &a, int flux, int tile, int maxp
 
 hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s) {
     int ti = kernel_index(tile, a.tailwave);
-    if (ti < 0) return hipErrorInvalidValue;
-    return launch(pick<2>(kmax, flux, ti), a.tend - a.tbeg, nthreads(tile), a, s);
+    if (ti < 0 || (a.red && a.tailwave)) return hipErrorInvalidValue;
+    return launch(pick<2>(kmax, flux, ti), a.tend - a.tbeg, a.red ? 2 * tile : nthreads(tile), a, s);
 }
 
 int persistent_max_grid_1d(int kmax, int flux, int tile, bool tailwave) {
