@@ -913,73 +913,90 @@ __global__ __launch_bounds__(nthreads(T)) void k_fold(StageArgs a, int src) {
 // instances x groups x FOLD_WG blocks).  The last workgroup of a group to arrive
 // combines its blocks in order.  Blocks, order and tree are k_fold's, so the bits
 // are too.  The groups' arrival counts are a line apart: in one line the arrivals of
-// all groups wait for each other.
+// all groups wait for each other (17.4 -> 16.7 us at 15626 tiles).  Bound by its
+// waits (records, block results, arrival): 10.8 us at 15626 tiles, of 16.7 with the
+// kind of a row (sum, max, min) chosen at run time.
 constexpr int FOLD_WG = 4;                   // blocks (waves) per workgroup
 
-template <int NC, int PRE>
-__global__ __launch_bounds__(FOLD_WG * WAVE) void k_fold_rows(StageArgs a, int src) {
+template <int NC, int PRE, bool SPEEDS>
+__device__ inline void fold_rows(const StageArgs &a, int src, int *last) {
+    // (known at compile time: chosen at run time, every operation of the trees and of
+    // the chain over the blocks was all three and two selects)
+    constexpr int KIND[3] = {SPEEDS ? 1 : 0, 1, SPEEDS ? 1 : 2};
+    constexpr int NV = SPEEDS ? 2 : 3;
     const int b = blockIdx.x, g = blockIdx.y, lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
     const Inst1D I = a.ninst == 1 ? a.inst0 : a.inst[b];
     const int nblk = (I.npart + PRE * WAVE - 1) / (PRE * WAVE), nwg = (nblk + FOLD_WG - 1) / FOLD_WG;
     if ((int)blockIdx.z >= nwg) return;
     const int blk = blockIdx.z * FOLD_WG + wave, t0 = blk * PRE * WAVE, n = I.npart - t0;
-    __shared__ int last;
-    const bool speeds = g == 2 * NC;         // (their third value is a duplicate)
-    const int row = speeds ? ST_BETA : triple_row<NC>(g), step = speeds ? 0 : 2;
-    auto kind = [speeds](int j) { return speeds ? 1 : j; };
+    const int row = SPEEDS ? ST_BETA : triple_row<NC>(g);
     double *out = a.foldw + ((long long)b * FOLD_GROUPS + g) * a.foldblk * 3;
     if (blk < nblk) {                        // uniform over the wave
         const double *col = a.part[fold_source(a, src, b)] + (long long)(I.tile0 + t0) * NSTAT + row;
-        double x[PRE][3], acc[3];
+        double x[PRE][NV], acc[NV];
 #pragma unroll
         for (int i = 0; i < PRE; ++i) {
             const double *r = col + (long long)min(lane + i * WAVE, n - 1) * NSTAT;
-            x[i][0] = r[0];
-            x[i][1] = r[1];
-            x[i][2] = r[step];
+#pragma unroll
+            for (int j = 0; j < NV; ++j) x[i][j] = r[j];
         }
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            acc[j] = stat_identity(kind(j));
+        for (int j = 0; j < NV; ++j) {
+            acc[j] = stat_identity(KIND[j]);
 #pragma unroll
             for (int i = 0; i < PRE; ++i)
-                acc[j] = stat_op(kind(j), acc[j], lane + i * WAVE < n ? x[i][j] : stat_identity(kind(j)));
-            acc[j] = wave_reduce(kind(j), acc[j]);
+                acc[j] = stat_op(KIND[j], acc[j], lane + i * WAVE < n ? x[i][j] : stat_identity(KIND[j]));
+            acc[j] = wave_reduce(KIND[j], acc[j]);
         }
         if (lane == WAVE - 1) {
 #pragma unroll
-            for (int j = 0; j < 3; ++j)
+            for (int j = 0; j < NV; ++j)
                 __hip_atomic_store(out + 3 * blk + j, acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned *count = a.foldn + ((long long)b * FOLD_GROUPS + g) * FOLD_PAD;
-        last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nwg - 1;
-        if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nwg - 1;
+        if (*last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (!last || wave > 0) return;
+    if (!*last || wave > 0) return;
     // the blocks in turn: 64 of them at a time in the lanes
-    double v[3];
+    double v[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] = __hip_atomic_load(out + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int k0 = 0; k0 < nblk; k0 += WAVE) {
-        double y[3];
+        double y[NV];
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
+        for (int j = 0; j < NV; ++j)
             y[j] = __hip_atomic_load(out + 3 * min(k0 + lane, nblk - 1) + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int k = 0; k < min(WAVE, nblk - k0); ++k)
+        const int end = min(WAVE, nblk - k0);
+        auto take = [&](int k) {
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const double z = lane_value(y[j], k);
-                v[j] = k0 + k == 0 ? z : stat_op(kind(j), v[j], z);
-            }
+            for (int j = 0; j < NV; ++j) v[j] = stat_op(KIND[j], v[j], lane_value(y[j], k));
+        };
+        int k = k0 == 0 ? 1 : 0;
+        for (; k + 4 <= end; k += 4) take(k), take(k + 1), take(k + 2), take(k + 3);
+        for (; k < end; ++k) take(k);
     }
     if (lane == 0) {
         double *red = a.red + (long long)b * NSTAT + row;
         red[0] = v[0];
-        red[1] = speeds ? v[1] : inv_sigma(v[0], v[1], v[2], (double)(g < NC ? I.np : I.nd));
-        if (!speeds) red[2] = v[2];
+        if constexpr (SPEEDS) {
+            red[1] = v[1];
+        } else {
+            red[1] = inv_sigma(v[0], v[1], v[2], (double)(g < NC ? I.np : I.nd));
+            red[2] = v[2];
+        }
     }
+}
+
+template <int NC, int PRE>
+__global__ __launch_bounds__(FOLD_WG * WAVE) void k_fold_rows(StageArgs a, int src) {
+    __shared__ int last;
+    if (blockIdx.y == 2 * NC) fold_rows<NC, PRE, true>(a, src, &last);
+    else fold_rows<NC, PRE, false>(a, src, &last);
 }
 
 // Step records (both parities), final record of instance i, and with i = 0

@@ -183,9 +183,9 @@ __device__ inline const double *part_tile(const double *part, long long tile) { 
 
 // Reduction of the per-tile partial statistics of tiles [tile0, tile0+ntiles) in a
 // fixed order: in blocks of PRE x 64 tiles, of which lane l of a wave takes tiles
-// l, l + 64, ... in turn, then the wave's tree; the blocks in turn.  A wave of the workgroup reduces the rows of some of the
-// (mesh, component) triples over all tiles (and wave 0 and 1 one of the wave-speed
-// rows): with every wave reducing all 18 rows of a third of the tiles, the trees
+// l, l + 64, ... in turn, then the wave's tree; the blocks in turn.  A wave of the
+// workgroup reduces the rows of some of the (mesh, component) triples over all tiles
+// (and wave 0 and 1 one of the wave-speed rows): with every wave reducing all 18 rows of a third of the tiles, the trees
 // were the longest phase of a stage launch.  Split in two so that the loads of the
 // first PRE tiles per lane are issued together with the kernel's other independent
 // loads (5 x 64 tiles hold the 257 columns of a mesh that fills the chip).

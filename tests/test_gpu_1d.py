@@ -478,13 +478,15 @@ def test_every_tile_count_mod_8(ntiles):
     assert _rel(gC, gD, rC, rD) <= RUN_TOL
 
 
-@pytest.mark.parametrize("tile,n", [(32, 32 * 256 - 1), (32, 32 * 257 - 1), (32, 32 * 1024), (64, 64 * 384 - 2),
-                                    (64, 64 * 385 - 1), (128, 128 * 641 - 1)])
+@pytest.mark.parametrize("tile,n", [(32, 32 * 192 - 1), (32, 32 * 193 - 1), (32, 32 * 320 - 1), (32, 32 * 385 - 1),
+                                    (32, 32 * 64 * 192 + 40), (64, 64 * 320 - 2), (64, 64 * 321 - 1), (64, 64 * 641 - 1),
+                                    (128, 128 * 321 - 1)])
 @pytest.mark.parametrize("euler", [True, False])
 def test_folded_rows_give_the_bits_of_the_in_kernel_reduction(tile, n, euler):
-    """The fold with a workgroup per row takes over beyond two tiles per thread
-    (256, 384, 640 tiles at tiles of 32, 64, 128): the same bits on both sides
-    of each line, in whole runs and (their final OE) in single stages."""
+    """The statistics are summed in blocks of 192 tiles of 32, or of 320 larger
+    ones, and beyond 320 tiles a fold takes a wave per block (64 blocks at a
+    time): the bits of the reduction in the stage kernels on both sides of each
+    line, in whole runs and (their final OE) in single stages."""
     if euler:
         prob, uC, uD = inputs.euler_riemann(n, 1, inputs.riemann_states(3))
     else:
