@@ -496,6 +496,34 @@ __device__ inline void damp_and_put(const Inst1D &I, const TCell &c, CellIn<K, F
     if (c.damps) lds_put<K, NC, W>(smem + c.mesh * PER, c.col, ci.own);
 }
 
+// eq:RKCDG: out = c_{l0} u^n [+ accumulated earlier stages] + c_{ll} u^l + tau d_{ll} L(u^l),
+// from the rates of the two halves of the cell; whether every coefficient is finite.
+template <int K, int NC>
+__device__ inline bool rk_update(const RKStage &rs, int l, double tau, double taumax, const double (&own)[NC][K + 1],
+                                 const double (&un)[NC][K + 1], const double (&acc)[NC][K + 1],
+                                 const double (&rl)[NC][K + 1], const double (&rr)[NC][K + 1], double (&out)[NC][K + 1]) {
+    const double inv_tm = div_nr(1.0, taumax);
+    const double td = tau * rs.d;
+    bool finite = true;
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+        for (int m = 0; m <= K; ++m) {
+            const double both = rl[q][m] + rr[q][m];
+            const double rate = inv_tm * (both - own[q][m]);
+            const double v = fma(td, rate, rs.cw * own[q][m]);
+            double o = v;
+            if (l > 0) {                     // (u^n at stage 0 is the input itself)
+                double base = rs.cn * un[q][m];
+                if (rs.acc_read) base += acc[q][m];
+                o = base + v;
+            }
+            out[q][m] = o;
+            finite = finite && isfinite(o);
+        }
+    return finite;
+}
+
 // ---------------------------------------------------------- stage tile ---
 
 // FOLDED: the instance's statistics were reduced by k_fold into a.red (batched
@@ -686,26 +714,7 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
         lds_cell<K, NC, W>(smem + (1 - c.mesh) * PER, c.mesh == 0 ? c.col + 1 : c.col, nb);
         cdg_rate_half<K, FLUX>(nb, 1, I.p0, ft, rr);
 
-        // eq:RKCDG: out = c_{l0} u^n [+ accumulated earlier stages] + c_{ll} u^l + tau d_{ll} L(u^l)
-        const double inv_tm = div_nr(1.0, taumax);
-        const double td = tau * rs.d;
-        bool finite = true;
-#pragma unroll
-        for (int q = 0; q < NC; ++q)
-#pragma unroll
-            for (int m = 0; m < K1; ++m) {
-                const double both = rl[q][m] + rr[q][m];      // the two halves of the cell
-                const double rate = inv_tm * (both - own[q][m]);
-                const double v = fma(td, rate, rs.cw * own[q][m]);
-                double o = v;
-                if (l > 0) {                 // (u^n at stage 0 is the input itself)
-                    double base = rs.cn * un[q][m];
-                    if (rs.acc_read) base += acc[q][m];
-                    o = base + v;
-                }
-                out[q][m] = o;
-                finite = finite && isfinite(o);
-            }
+        bool finite = rk_update<K, NC>(rs, l, tau, taumax, own, un, acc, rl, rr, out);
         if (rs.ca != 0.0) {                  // classical RK4: this stage's damped input joins the sum
 #pragma unroll
             for (int q = 0; q < NC; ++q)
@@ -1092,6 +1101,215 @@ __global__ __launch_bounds__(nthreads(T)) void k_persistent(StageArgs a, long lo
     }
 }
 
+// ------------------------------------------------------- small meshes ---
+
+// Steps n0 .. n0 + count - 1 of one small scalar instance in one workgroup, a wave
+// per tile of 32 primal and 32 dual cells, the state in registers and LDS from the
+// first stage to the last.  The records in memory (step records, partial
+// statistics, stage buffer) are read at the start and written at the end as the
+// launches of the same stages would leave them, and the bits are theirs: the same
+// cell functions, a record per tile, the same tree (an instance of at most 32 tiles
+// is one round of lanes 0 .. 31; here lanes 32 .. 63 take the dual mesh's).  Each
+// cell is damped by its own thread only; two barriers per stage: the undamped image
+// and the records before the first, the damped image before the second.
+// Of a stage launch of such a mesh 1.6 us are the launch and about as much the waits
+// for its records and cells; here a stage is its chain of arithmetic, and from 8
+// waves on (two per SIMD) its issue.  Per stage, P2 advection (a launch per stage ->
+// here): 4.5 -> 1.7 us at 64 cells, 4.6 -> 2.3 at 256, 4.6 -> 3.5 at 512, where the
+// waves of a workgroup end; P3 4.9 -> 2.2, 5.1 -> 3.1, 5.0 -> 4.8.
+constexpr int SOLO_TILES = 16;
+
+template <int K, int FLUX>
+__global__ __launch_bounds__(SOLO_TILES * WAVE) void k_solo(StageArgs a, long long n0, int count) {
+    using F = FluxT<FLUX>;
+    constexpr int NC = F::NC, K1 = K + 1, NV = 3 * NC + 1, W = SOLO_TILES * 32 + 3, PER = NC * K1 * W;
+    static_assert(NC == 1, "scalar fluxes");
+    // images [damped C, damped D, undamped C, undamped D], column g + 1 of cell g
+    __shared__ double img[4 * PER], rec[2][NV][32];
+    const Inst1D I = a.inst0;
+    const int tid = threadIdx.x, lane = tid % WAVE, tile = tid / WAVE, ntile = blockDim.x / WAVE;
+    TCell c;
+    c.mesh = lane / 32;
+    c.g = tile * 32 + lane % 32;
+    c.col = c.g + 1;
+    const int ncell = c.mesh == 0 ? I.np : I.nd;
+    c.owned = c.has = c.damps = c.g < ncell;
+    // columns of the overlapping cells of the other mesh, left and right
+    int lc = c.mesh == 0 ? c.g : c.g - 1, rc = lc + 1;
+    if (I.bc == 0) {
+        lc = lc < 0 ? I.np - 1 : lc;
+        rc = c.mesh == 0 && rc >= I.nd ? 0 : rc;
+    }
+    ++lc, ++rc;
+    if (!c.owned) lc = rc = 1;
+    // the ghost column that this thread's cell fills (outflow: the mean of the end cell)
+    const bool gl = I.bc != 0 && c.mesh == 0 && c.g == 0, gr = I.bc != 0 && c.mesh == 0 && c.g == I.np - 1;
+    double *damped = img + c.mesh * PER, *undamped = img + (2 + c.mesh) * PER;
+    const double *odamped = img + (1 - c.mesh) * PER, *oundamped = img + (3 - c.mesh) * PER;
+
+    const int sp0 = (a.ns & 1) ? (int)(n0 & 1) : 0;
+    Slot *S = a.slots;
+    double t = S[n0 & 1].t, ptau = S[(n0 & 1) ^ 1].tau, taumax = 0.0;
+    long long nexec = a.fin->nexec;
+    CellIn<K, FLUX> ci;
+    ci.real = c.owned;
+    ci.mirror = false;
+    {
+        const double *src = c.mesh == 0 ? (a.srcC ? a.srcC : a.BC[sp0]) : (a.srcD ? a.srcD : a.BD[sp0]);
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int m = 0; m < K1; ++m) ci.own[q][m] = c.owned ? src[(long long)(q * K1 + m) * ncell + c.g] : 0.0;
+    }
+    const double *part0 = a.part[sp0 ^ 1];
+    for (int i = tid; i < 2 * NV * ntile; i += blockDim.x) {
+        const int j = i % ntile, v = i / ntile % NV, mesh = i / ntile / NV;
+        rec[mesh][v][j] = part0[(long long)j * NSTAT + (v == 3 * NC ? ST_BETA + mesh : stat_index(mesh, v / 3, v % 3))];
+    }
+    auto put = [&](double *image, bool zero) {
+        if (c.owned) lds_put<K, NC, W>(image, c.col, ci.own);
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int m = 0; m < K1; ++m)
+                if (m == 0 || zero) {
+                    if (gl) image[(q * K1 + m) * W] = m == 0 ? ci.own[q][0] : 0.0;
+                    if (gr) image[(q * K1 + m) * W + I.np + 1] = m == 0 ? ci.own[q][0] : 0.0;
+                }
+    };
+    put(undamped, true);
+    put(damped, true);
+
+    double un[NC][K1], acc[NC][K1], tau = 0.0;
+    int done = 0, last = 0, steps = 0;
+    for (; steps < count; ++steps) {
+        if (t >= a.t_end) {                  // uniform: every wave holds the same t
+            done = 1;
+            break;
+        }
+        for (int l = 0; l < a.ns; ++l) {
+            const RKStage rs = rk_stage(a.rk, l);
+            const bool damp = I.oe && K > 0 && (l > 0 || n0 + steps > 0);
+            __syncthreads();
+            double isig[NC];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) isig[q] = 0.0;
+            const int j = min(lane % 32, ntile - 1);
+            const bool in = lane % 32 < ntile;
+            if (damp) {
+#pragma unroll
+                for (int q = 0; q < NC; ++q) {
+                    double v[3];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        v[k] = in ? rec[c.mesh][3 * q + k][j] : stat_identity(k);
+                        v[k] = half_wave_reduce(k, v[k]);
+                        v[k] = lane < 32 ? lane_value(v[k], 31) : lane_value(v[k], 63);
+                    }
+                    isig[q] = inv_sigma(v[0], v[1], v[2], (double)ncell);
+                }
+            }
+            if (l == 0) {
+                if (a.dt_fixed > 0.0) {
+                    taumax = a.dt_fixed;
+                } else {
+                    const double b = half_wave_reduce(1, in ? rec[c.mesh][3 * NC][j] : -INFINITY);
+                    taumax = I.cfl * I.h / fmax(lane_value(b, 31), lane_value(b, 63));
+                }
+                tau = taumax;
+                last = 0;
+                if (t + tau >= a.t_end) {
+                    tau = a.t_end - t;
+                    last = 1;
+                }
+            }
+            if (damp) {
+                lds_cell<K, NC, W>(oundamped, lc, ci.nl);
+                lds_cell<K, NC, W>(oundamped, rc, ci.nr);
+            }
+            damp_cell<K, FLUX>(I, c, ci, isig, l == 0 ? ptau : tau, damp);
+            put(damped, false);
+            __syncthreads();
+            double out[NC][K1];
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+#pragma unroll
+                for (int m = 0; m < K1; ++m) out[q][m] = 0.0;
+            if (c.owned) {
+                if (l == 0) {
+#pragma unroll
+                    for (int q = 0; q < NC; ++q)
+#pragma unroll
+                        for (int m = 0; m < K1; ++m) un[q][m] = ci.own[q][m];
+                }
+                double nb[NC][K1], rl[NC][K1], rr[NC][K1];
+                const double ft = taumax * I.hinv;
+                lds_cell<K, NC, W>(odamped, lc, nb);
+                cdg_rate_half<K, FLUX>(nb, 0, I.p0, ft, rl);
+                lds_cell<K, NC, W>(odamped, rc, nb);
+                cdg_rate_half<K, FLUX>(nb, 1, I.p0, ft, rr);
+                if (!rk_update<K, NC>(rs, l, tau, taumax, ci.own, un, acc, rl, rr, out)) {
+                    a.err[0] = 1;
+                    a.err[3] = (int)(nexec + 1);
+                }
+                if (rs.ca != 0.0) {
+#pragma unroll
+                    for (int q = 0; q < NC; ++q)
+#pragma unroll
+                        for (int m = 0; m < K1; ++m)
+                            acc[q][m] = rs.acc_first ? rs.ca * ci.own[q][m] : fma(rs.ca, ci.own[q][m], acc[q][m]);
+                }
+            }
+            double v[NV];
+            cell_stats<K, FLUX>(I, c.owned, out, v, l == a.ns - 1);
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                const double x = half_wave_reduce(cell_stat_kind<NC>(k), v[k]);
+                if (lane % 32 == 31) rec[c.mesh][k][tile] = x;
+            }
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+#pragma unroll
+                for (int m = 0; m < K1; ++m) ci.own[q][m] = out[q][m];
+            put(undamped, false);
+        }
+        t = last ? a.t_end : t + tau;
+        ptau = tau;
+        ++nexec;
+    }
+    if (tid == 0) {
+        for (int p = 0; p < 2; ++p) {        // both parities: the next step of either reads this
+            S[p].t = t;
+            S[p].done = done;
+            if (steps > 0) {
+                S[p].tau = ptau;
+                S[p].tau_max = taumax;
+                S[p].last = last;
+            }
+        }
+    }
+    if (steps == 0) return;                  // uniform
+    if (tid == 0) {
+        a.fin->t = t;
+        a.fin->tau = ptau;
+        a.fin->nexec = nexec;
+    }
+    const int sp = (((a.ns & 1) ? (int)((n0 + steps - 1) & 1) : 0) + a.ns - 1) & 1;   // of the last stage
+    double *dst = c.mesh == 0 ? a.BC[sp ^ 1] : a.BD[sp ^ 1];
+    if (c.owned) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+#pragma unroll
+            for (int m = 0; m < K1; ++m) dst[(long long)(q * K1 + m) * ncell + c.g] = ci.own[q][m];
+    }
+    __syncthreads();
+    double *part = a.part[sp];
+    for (int i = tid; i < 2 * NV * ntile; i += blockDim.x) {
+        const int j = i % ntile, v = i / ntile % NV, mesh = i / ntile / NV;
+        part[(long long)j * NSTAT + (v == 3 * NC ? ST_BETA + mesh : stat_index(mesh, v / 3, v % 3))] = rec[mesh][v][j];
+    }
+}
+
 __global__ void k_init(StageArgs a, int ninst) {
     clear_records(a, blockIdx.x * blockDim.x + threadIdx.x, ninst);
 }
@@ -1225,6 +1443,21 @@ hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hip
     int ti = kernel_index(tile, a.tailwave);
     if (ti < 0 || (a.red && a.tailwave)) return hipErrorInvalidValue;
     return launch(pick<2>(kmax, flux, ti), a.tend - a.tbeg, a.red ? 2 * tile : nthreads(tile), a, s);
+}
+
+// Steps of a single small instance in one launch (k_solo): scalar fluxes without
+// wall or inflow ghosts, tiles of 32.
+bool solo_1d(const StageArgs &a, int flux, int tile) {
+    return a.ninst == 1 && flux <= 1 && tile == 32 && !a.red && a.inst0.npart <= SOLO_TILES;
+}
+
+hipError_t launch_solo_1d(const StageArgs &a, int k, int flux, long long n0, int count, hipStream_t s) {
+    if (!solo_1d(a, flux, 32)) return hipErrorInvalidValue;
+    static void *const fn[2][4] = {{(void *)k_solo<0, 0>, (void *)k_solo<1, 0>, (void *)k_solo<2, 0>, (void *)k_solo<3, 0>},
+                                   {(void *)k_solo<0, 1>, (void *)k_solo<1, 1>, (void *)k_solo<2, 1>, (void *)k_solo<3, 1>}};
+    StageArgs copy = a;
+    void *args[] = {&copy, &n0, &count};
+    return hipLaunchKernel(fn[flux][k], dim3(1), dim3(WAVE * a.inst0.npart), args, 0, s);
 }
 
 int persistent_max_grid_1d(int kmax, int flux, int tile, bool tailwave) {

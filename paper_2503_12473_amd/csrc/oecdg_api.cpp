@@ -354,11 +354,24 @@ int final_all(oecdg_handle *h, const StageArgs &a) {
     return OECDG_OK;
 }
 
+// Small scalar meshes take all steps of a launch_steps call in one launch, unless
+// the caller asked for a mode of stage launches.
+bool solo_on(const oecdg_handle *h, const StageArgs &a) {
+    return h->mode == OECDG_MODE_AUTO && solo_1d(a, h->flux, h->tile);
+}
+
 // Launch the stage kernels of steps n0 .. n0 + count - 1.  inC/inD (optional):
 // the arrays that the first stage of step 0 reads instead of the stage buffer
 // of index 0 (the caller's initial data, read in place).
 int launch_steps(oecdg_handle *h, const StageArgs &base, long long n0, long long count,
                  const double *inC = nullptr, const double *inD = nullptr) {
+    if (solo_on(h, base)) {
+        StageArgs a = base;
+        a.srcC = inC;
+        a.srcD = inD;
+        HIPCHK(h, launch_solo_1d(a, h->groups[0].k, h->flux, n0, (int)count, h->stream));
+        return OECDG_OK;
+    }
     for (long long n = n0; n < n0 + count; ++n)
         for (int l = 0; l < base.ns; ++l) {
             StageArgs a = base;
@@ -397,9 +410,9 @@ int capture(oecdg_handle *h, F &&body, hipGraphExec_t *out) {
     return OECDG_OK;
 }
 
-// Graphs depend on (t_end, dt_fixed, tile, graph_steps, fold): drop them when these change.
+// Graphs depend on (t_end, dt_fixed, tile, graph_steps, kernels): drop them when these change.
 void key_graphs(oecdg_handle *h, const StageArgs &base) {
-    const int fold = base.red ? 1 : 0;
+    const int fold = base.red ? 1 : (solo_on(h, base) ? 2 : 0);
     if (h->g_tend == base.t_end && h->g_dt == base.dt_fixed && h->g_tile == h->tile &&
         h->g_steps == h->graph_steps && h->g_fold == fold)
         return;

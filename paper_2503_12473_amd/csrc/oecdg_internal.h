@@ -127,7 +127,7 @@ struct StageArgs {
     int damp_input;          // 0: the stage input is used as is (single-stage call)
     int ninst;               // instances in the batch
     // final / statistics kernels
-    const double *srcC, *srcD;
+    const double *srcC, *srcD;   // (k_solo: the input of step 0 when read in place, else null)
     double *dstC, *dstD;
     int init_records;        // statistics kernel: also clear the step records and error flags (a run's start)
     Final *fin_host;         // final kernel, when set: the step records and error flags copied to these
@@ -173,6 +173,8 @@ hipError_t launch_fold_final_1d(const StageArgs &a, int flux, int tile, int maxp
 hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hipStream_t s);
 hipError_t launch_persistent_1d(const StageArgs &a, int kmax, int flux, int tile, int grid,
                                 long long nsteps, hipStream_t s);
+bool solo_1d(const StageArgs &a, int flux, int tile);            // may launch_solo_1d take the run's steps?
+hipError_t launch_solo_1d(const StageArgs &a, int k, int flux, long long n0, int count, hipStream_t s);
 int persistent_max_grid_1d(int kmax, int flux, int tile, bool tailwave);
 
 }  // namespace oecdg

@@ -504,3 +504,28 @@ def test_folded_rows_give_the_bits_of_the_in_kernel_reduction(tile, n, euler):
             outs.append((a, b, one[0], one[1], t, ns))
     for x, y in zip(*outs):
         assert np.array_equal(x.cpu().numpy(), y.cpu().numpy()) if hasattr(x, "cpu") else x == y
+
+
+@pytest.mark.parametrize("n", [2, 3, 31, 32, 33, 255, 256, 480, 511, 512])
+@pytest.mark.parametrize("flux,bc,k,rk", [(FLUX_ADVECTION, BC_PERIODIC, 2, 3), (FLUX_ADVECTION, BC_OUTFLOW, 3, 4),
+                                          (FLUX_BURGERS, BC_PERIODIC, 1, 2), (FLUX_BURGERS, BC_OUTFLOW, 2, 3),
+                                          (FLUX_BURGERS, BC_PERIODIC, 0, 1)])
+def test_small_scalar_runs_give_the_bits_of_stage_launches(n, flux, bc, k, rk):
+    """The library's choice for scalar meshes of at most 16 tiles of 32 is all
+    steps in one workgroup: the bits of one launch per stage, for a number of
+    steps, to a final time (over several launches) and with a fixed step."""
+    prob = Problem1D(k=k, nc=1, flux=flux, bc=bc, n=n, xlo=0.0, xhi=1.0, a=0.75)
+    uC, uD = _state(prob, np.random.default_rng(n))
+    outs = []
+    for mode in (_lib.MODE_AUTO, _lib.MODE_EAGER):
+        print(f"[small] n={n} flux={flux} bc={bc} k={k} rk={rk} mode={mode}", flush=True)
+        with OECDG(prob, 0.1, rk=rk) as s:
+            s.set_option(_lib.OPT_MODE, mode)
+            s.set_option(_lib.OPT_GRAPH_STEPS, 8)
+            res = []
+            for kw in ({"nsteps": 7}, {"t_end": 20.5 * 0.1 * prob.h}, {"nsteps": 300, "dt_fixed": 0.01 * prob.h}):
+                a, b = to_device(uC), to_device(uD)
+                res += [s.run(a, b, **kw), a.cpu().numpy(), b.cpu().numpy()]
+            outs.append(res)
+    for x, y in zip(*outs):
+        assert x == y if isinstance(x, tuple) else np.array_equal(x, y)
