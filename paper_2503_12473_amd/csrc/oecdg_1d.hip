@@ -1108,16 +1108,28 @@ __global__ __launch_bounds__(nthreads(T)) void k_persistent(StageArgs a, long lo
 // first stage to the last.  The records in memory (step records, partial
 // statistics, stage buffer) are read at the start and written at the end as the
 // launches of the same stages would leave them, and the bits are theirs: the same
-// cell functions, a record per tile, the same tree (an instance of at most 32 tiles
-// is one round of lanes 0 .. 31; here lanes 32 .. 63 take the dual mesh's).  Each
+// cell functions, a record per tile, the same tree (an instance of at most 16 tiles
+// is one round of lanes 0 .. 15; here every group of 16 lanes takes the records of its
+// half's mesh, so that no lane has to be read by the others).  Each
 // cell is damped by its own thread only; two barriers per stage: the undamped image
 // and the records before the first, the damped image before the second.
 // Of a stage launch of such a mesh 1.6 us are the launch and about as much the waits
 // for its records and cells; here a stage is its chain of arithmetic, and from 8
 // waves on (two per SIMD) its issue.  Per stage, P2 advection (a launch per stage ->
-// here): 4.5 -> 1.7 us at 64 cells, 4.6 -> 2.3 at 256, 4.6 -> 3.5 at 512, where the
-// waves of a workgroup end; P3 4.9 -> 2.2, 5.1 -> 3.1, 5.0 -> 4.8.
+// here): 4.5 -> 1.6 us at 64 cells, 4.6 -> 2.1 at 256, 4.6 -> 3.3 at 512, where the
+// waves of a workgroup end; P3 4.9 -> 2.0, 5.1 -> 2.9, 5.1 -> 4.5.  (Not Euler: 5.5
+// for 7.4 us at 255 cells, but the compiler contracts its products into other
+// multiply-adds here than in k_stage, and the bits are to be the same.)
 constexpr int SOLO_TILES = 16;
+
+// Reduction over each group of 16 lanes, the result in all of them: the first levels
+// of wave_reduce.
+__device__ inline double group_reduce(int kind, double v) {
+    v = stat_op(kind, v, dpp_all<0xB1>(v));
+    v = stat_op(kind, v, dpp_all<0x4E>(v));
+    v = stat_op(kind, v, dpp_all<0x141>(v));
+    return stat_op(kind, v, dpp_all<0x140>(v));
+}
 
 template <int K, int FLUX>
 __global__ __launch_bounds__(SOLO_TILES * WAVE) void k_solo(StageArgs a, long long n0, int count) {
@@ -1194,8 +1206,8 @@ __global__ __launch_bounds__(SOLO_TILES * WAVE) void k_solo(StageArgs a, long lo
             double isig[NC];
 #pragma unroll
             for (int q = 0; q < NC; ++q) isig[q] = 0.0;
-            const int j = min(lane % 32, ntile - 1);
-            const bool in = lane % 32 < ntile;
+            const int j = min(lane % SOLO_TILES, ntile - 1);
+            const bool in = lane % SOLO_TILES < ntile;
             if (damp) {
 #pragma unroll
                 for (int q = 0; q < NC; ++q) {
@@ -1203,8 +1215,7 @@ __global__ __launch_bounds__(SOLO_TILES * WAVE) void k_solo(StageArgs a, long lo
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
                         v[k] = in ? rec[c.mesh][3 * q + k][j] : stat_identity(k);
-                        v[k] = half_wave_reduce(k, v[k]);
-                        v[k] = lane < 32 ? lane_value(v[k], 31) : lane_value(v[k], 63);
+                        v[k] = group_reduce(k, v[k]);
                     }
                     isig[q] = inv_sigma(v[0], v[1], v[2], (double)ncell);
                 }
@@ -1213,8 +1224,8 @@ __global__ __launch_bounds__(SOLO_TILES * WAVE) void k_solo(StageArgs a, long lo
                 if (a.dt_fixed > 0.0) {
                     taumax = a.dt_fixed;
                 } else {
-                    const double b = half_wave_reduce(1, in ? rec[c.mesh][3 * NC][j] : -INFINITY);
-                    taumax = I.cfl * I.h / fmax(lane_value(b, 31), lane_value(b, 63));
+                    const double b = group_reduce(1, in ? rec[c.mesh][3 * NC][j] : -INFINITY);
+                    taumax = I.cfl * I.h / fmax(lane_value(b, 0), lane_value(b, 32));
                 }
                 tau = taumax;
                 last = 0;
