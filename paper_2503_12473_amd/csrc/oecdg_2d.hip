@@ -3,11 +3,6 @@
 // linear advection or Euler.
 //
 // Per RK stage (eq:RKCDG):
-//   k_reduce2d  folds the per-tile partial statistics of the stage input into
-//               the global scalars: per mesh and component the domain average
-//               and sigma (Sec. 2.2), the largest x and y wave speeds, and at a
-//               step start tau and tau_max (tau_max = C_CFL / (beta_x/h_x +
-//               beta_y/h_y), Sec. 2.1);
 //   k_stage2d   one workgroup per tile of TX x TY primal cells and the dual
 //               cells with the same indices, one thread per cell.  Its threads
 //               load the cells that the tile's operator reads, apply the OE
@@ -16,10 +11,16 @@
 //               put them in LDS; each thread then evaluates the operator of
 //               eq:2D_H on its cell, takes the RK combination (the c/d table of
 //               eq:RKCDG: SSP-RK3 by default, forward Euler, SSP-RK2 or
-//               classical RK4) and writes the undamped stage output;
-//   k_delta2d   the damping numerators (the edge integrals of Sec. 2.2) and the
-//               tile's partial statistics of that output, one workgroup per
-//               tile and component.
+//               classical RK4) and writes the undamped stage output and, per
+//               wave, its partial statistics;
+//   k_delta2d   the damping numerators of that output (the edge integrals of
+//               Sec. 2.2), one component and mesh of a tile of cells per
+//               workgroup; its first workgroups reduce the partial statistics to
+//               the global scalars (per mesh and component the domain average and
+//               sigma of Sec. 2.2, the largest x and y wave speeds, and at a step
+//               start tau and tau_max, tau_max = C_CFL / (beta_x/h_x +
+//               beta_y/h_y), Sec. 2.1).
+// k_stats2d and k_reduce2d give the statistics of a run's initial data;
 // k_damp2d damps a state without a stage (the end of a run or of a single stage).
 //
 // Layout (global): u[(((q*(k+1) + a)*(k+1) + b)*ny + iy)*nx + ix]; dual cell
