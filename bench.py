@@ -264,7 +264,7 @@ def euler2d_bench(repeats: int = 5, steps: int = E2D_STEPS):
             torch.cuda.synchronize()
             times.append(e0.elapsed_time(e1) / 1e3)
     wall = sorted(times)[len(times) // 2]
-    launch_s = wall / (3 * n)                    # one RK stage: fold + reduce + k_stage2d + k_delta2d
+    launch_s = wall / (3 * n)                    # one RK stage: k_stage2d + k_delta2d
     bytes_per_launch = BYTES_PER_DOF_UPDATE / 3.0 * dofs
     achieved = bytes_per_launch / launch_s / 1e9
     prof = profile_2d()
@@ -288,7 +288,7 @@ def euler2d_bench(repeats: int = 5, steps: int = E2D_STEPS):
                          "hbm": {"achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                  "frac": achieved / HBM_PEAK_GBS, "traffic": prof.get("traffic_bytes_per_stage")},
                          "kernel": "per RK stage: k_stage2d (OE of the previous stage + operator + SSP-RK3) "
-                                   "+ k_delta2d (damping numerators, statistics) + statistics folds",
+                                   "+ k_delta2d (damping numerators, reduction of the statistics)",
                          "launch_us": 1e6 * launch_s}}
 
 

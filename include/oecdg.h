@@ -100,7 +100,8 @@ enum {
     OECDG_OPT_FOLD = 5          /* where the global statistics of Sec. 2.2 (avg, sigma) and the wave
                                  * speed are reduced before each 1D stage: 0 library choice (a
                                  * per-instance fold kernel for batches and for meshes of more
-                                 * than 1024 tiles, inside every stage workgroup otherwise),
+                                 * than 512 tiles, scalar 800, tiles of 32 1024; inside every
+                                 * stage workgroup otherwise),
                                  * 1 inside the stage kernel, 2 the fold kernel (not when the
                                  * last tile carries the dual cell np, which then reduces
                                  * inside).  The same bits either way. */

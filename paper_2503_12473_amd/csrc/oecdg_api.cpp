@@ -246,11 +246,17 @@ int build_tiles(oecdg_handle *h) {
 
 // Statistics folded by a separate per-instance kernel (k_fold) before each
 // stage launch, instead of every workgroup reducing its instance's partials:
-// the default for batches and for meshes of more than 1024 tiles (whose
-// in-kernel reduction would read every tile's record in every workgroup);
-// other single instances reduce in-kernel unless asked.
+// the default for batches and for meshes of so many tiles that reading every
+// tile's record in every workgroup takes longer than the fold's launch.  With
+// Euler's registers two workgroups of k_stage share a CU, so beyond 512 tiles of
+// 64 the reduction comes in rounds too: 12.7 us per stage against 14.7 with the
+// fold at 501 tiles, 16.4 against 15.0 at 513, 29.1 against 18.0 at 1016 (P2).
+// Scalar stages hold six per CU; there the lines cross at 800 tiles (11.4 against
+// 11.1 us at 801, 10.2 against 10.9 at 769, 14.7 against 11.6 at 1016, P2).
+// Tiles of 32 (two waves, half the cells) cross later.
 bool fold_on(const oecdg_handle *h) {
-    return !h->tailwave && (h->fold == 2 || (h->fold == 0 && (h->nbatch > 1 || h->ncol > 1024)));
+    const int line = h->tile == 32 ? 1024 : (h->flux <= 1 ? 800 : 512);
+    return !h->tailwave && (h->fold == 2 || (h->fold == 0 && (h->nbatch > 1 || h->ncol > line)));
 }
 
 StageArgs base_args(oecdg_handle *h) {
