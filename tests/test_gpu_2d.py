@@ -182,11 +182,11 @@ def test_nonfinite_input_is_reported():
 
 @pytest.mark.parametrize("flux,k,space", [(FLUX_EULER, 1, 0), (FLUX_EULER, 2, 0), (FLUX_EULER, 2, 1), (FLUX_EULER, 3, 1),
                                           (FLUX_ADVECTION, 2, 0), (FLUX_ADVECTION, 3, 1)])
-@pytest.mark.parametrize("nx,ny", [(16, 4), (17, 5), (15, 3), (2, 33), (33, 2), (31, 18)])
+@pytest.mark.parametrize("nx,ny", [(16, 4), (17, 5), (15, 3), (16, 7), (17, 8), (15, 9), (8, 7), (2, 33), (33, 2), (31, 18)])
 def test_mesh_sizes_at_the_edges_of_the_tiles(nx, ny, flux, k, space):
-    """Meshes of one tile (16 x 4 of the stage kernel, 16 x 16 of the damping
-    numerators), one cell more and less, and thinner than a tile with its
-    halo, against the oracle."""
+    """Meshes of one tile (16 x 4, 16 x 7, 16 x 8, 8 x 7 of the stage kernels,
+    16 x 16 of the damping numerators), one cell more and less, and thinner
+    than a tile with its halo, against the oracle."""
     nc = 4 if flux == FLUX_EULER else 1
     prob = Problem2D(k=k, nc=nc, flux=flux, nx=nx, ny=ny, xlo=0.0, xhi=1.2, ylo=0.0, yhi=0.7, a=1.0, b=-0.6, space=space)
 
