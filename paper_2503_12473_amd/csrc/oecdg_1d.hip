@@ -963,6 +963,9 @@ __device__ inline void fold_rows(const StageArgs &a, int src, int *last) {
                 __hip_atomic_store(out + 3 * blk + j, acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
+    // Every wave waits for its own stores to be visible to the other XCDs: the barrier
+    // does not, and the arrival below waits for those of the first wave only.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned *count = a.foldn + ((long long)b * FOLD_GROUPS + g) * FOLD_PAD;
