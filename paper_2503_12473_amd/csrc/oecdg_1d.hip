@@ -1060,6 +1060,7 @@ __global__ __launch_bounds__(nthreads(T)) void k_final(StageArgs a) {
 // cooperative launch).  Sense by generation counter; bounded spin so that every
 // workgroup always terminates (a timeout is reported through err[2]).
 __device__ inline void grid_barrier(const StageArgs &a) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // every wave's stores, not only the arriving one's
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned *count = a.bar, *gen = a.bar + 1;

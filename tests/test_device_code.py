@@ -63,3 +63,13 @@ def test_fold_workgroups_arrive_after_the_stores_of_all_their_waves(code_objects
     for name, ins in kernels.items():
         arrivals, bad = _unwaited_arrivals(ins)
         assert arrivals == 2 and bad == 0, name
+
+
+def test_the_grid_barrier_is_reached_after_the_stores_of_all_waves(code_objects):
+    """The persistent launch's grid barrier: every wave's stores (the stage's output and
+    statistics, which other workgroups read after it) before the workgroup's arrival."""
+    kernels = _kernels(code_objects, "k_persistent")
+    assert kernels
+    for name, ins in kernels.items():
+        arrivals, bad = _unwaited_arrivals(ins)
+        assert arrivals >= 1 and bad == 0, name
