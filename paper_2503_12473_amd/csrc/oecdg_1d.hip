@@ -963,9 +963,9 @@ __device__ inline void fold_rows(const StageArgs &a, int src, int *last) {
                 __hip_atomic_store(out + 3 * blk + j, acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    // Every wave waits for its own stores to be visible to the other XCDs: the barrier
-    // does not, and the arrival below waits for those of the first wave only.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    // the barrier does not wait for them, and the arrival's release only for those of its
+    // own wave (a release fence in every wave cost 5 us per fold more)
+    wait_stores();
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned *count = a.foldn + ((long long)b * FOLD_GROUPS + g) * FOLD_PAD;
@@ -1060,13 +1060,14 @@ __global__ __launch_bounds__(nthreads(T)) void k_final(StageArgs a) {
 // cooperative launch).  Sense by generation counter; bounded spin so that every
 // workgroup always terminates (a timeout is reported through err[2]).
 __device__ inline void grid_barrier(const StageArgs &a) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // every wave's stores, not only the arriving one's
+    wait_stores();                           // of every wave: in this XCD's L2 before the write-back below
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned *count = a.bar, *gen = a.bar + 1;
         const unsigned g = __hip_atomic_load(gen, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();
-        const unsigned arrived = __hip_atomic_fetch_add(count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        wait_stores();                       // the write-back itself (the compiler counts no access to wait for)
+        const unsigned arrived = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (arrived == gridDim.x - 1) {
             __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_fetch_add(gen, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);

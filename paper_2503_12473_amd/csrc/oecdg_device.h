@@ -92,6 +92,12 @@ __device__ inline Slot ld_slot(const Slot *p, bool coherent) {
     return s;
 }
 
+// Waits until the wave's stores are acknowledged (agent-scope atomic ones: by the memory
+// that all XCDs share; plain ones: by the XCD's L2).  A workgroup barrier waits for no
+// store, and a release in one thread only for those of its own wave: before other
+// workgroups are told of stores of several waves, each wave waits here.
+__device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ------------------------------------------------------ tiles and XCDs ---
 // Workgroup b of a launch over n tiles -> its tile (offset from the first).
 // Workgroups are dealt to the 8 XCDs in turn (XCD b mod 8), so XCD x gets
