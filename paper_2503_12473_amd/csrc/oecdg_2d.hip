@@ -304,9 +304,9 @@ __device__ inline void damp_factors(const double (&nv)[(K + 1) * NC], const doub
     double S = 0.0;
 #pragma unroll
     for (int m = 0; m <= K; ++m) {
-        double dm = nv[m * NC] * isig[0];
+        double dm = 0.0;                         // (drops a NaN: the wave speed of a cell of negative pressure)
 #pragma unroll
-        for (int q = 1; q < NC; ++q) dm = max_d(dm, nv[m * NC + q] * isig[q]);
+        for (int q = 0; q < NC; ++q) dm = max_d(dm, nv[m * NC + q] * isig[q]);
         S += dm;
         if (m >= 1) f[m - 1] = exp(-tau * S);
     }

@@ -202,3 +202,27 @@ def test_mesh_sizes_at_the_edges_of_the_tiles(nx, ny, flux, k, space):
     g, _, _ = _gpu_run(prob, uC, uD, 0.2, nsteps=3)
     rC, rD, _, _ = ora.run2d(prob, uC, uD, nsteps=3, cfl=0.2)
     assert _rel(g, (rC, rD)) <= TOL
+
+
+@pytest.mark.parametrize("k,space", [(2, 0), (2, 1), (3, 1)])
+def test_negative_pressure_is_reported_and_the_arrays_stay_finite(k, space):
+    """A cell average of negative pressure, in the data and in the stage's output: a
+    stage and runs return ENONPHYSICAL, as the oracle does, and write finite arrays
+    (the NaN wave speed of such a cell takes no part in the damping)."""
+    from paper_2503_12473_amd import _lib
+    prob, uC, uD, _ = inputs.euler2d_quadrants(16, k, seed=0, space=space)
+    with OECDG(prob, 0.3) as s:
+        dt = s.dt(to_device(uC), to_device(uD))
+        uC = uC.copy()
+        uC[3, 0, 0, 5, 7] = -50.0
+        for nsteps in (0, 1, 3):
+            print(f"[2d] negative pressure k={k} space={space} nsteps={nsteps}", flush=True)
+            a, b = to_device(uC), to_device(uD)
+            out = (a, b) if nsteps else (torch.zeros_like(a), torch.zeros_like(b))
+            with pytest.raises(_lib.OECDGError) as e:
+                s.run(a, b, nsteps=nsteps) if nsteps else s.stage(0, dt, dt, a, b, out=out)
+            assert e.value.code == _lib.ENONPHYSICAL
+            assert all(torch.isfinite(o).all() for o in out)
+            if nsteps:
+                with pytest.raises(ora.OracleError, match="ENONPHYSICAL"):
+                    ora.run2d(prob, uC, uD, nsteps=nsteps, cfl=0.3)
