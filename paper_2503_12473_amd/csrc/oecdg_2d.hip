@@ -242,12 +242,15 @@ template <int NC> struct Rec2 {
 // Tile of a workgroup; a band of consecutive tiles per XCD (xcd_tile).
 __device__ inline int tile_of_block(int nt) { return xcd_tile(blockIdx.x, nt); }
 
-// sqrt(x) for x >= SQRT_TINY from the hardware estimate r of 1/sqrt (relative
-// error below 2^-22) and one third-order step: with t = x r and e = 1 - t r,
-// sqrt(x) = t (1 - e)^(-1/2) = t + t e (1/2 + 3/8 e + O(e^2)), within an ulp of the
-// correctly rounded root up to 1e300.  The IEEE sequence (range scaling, three
-// steps, class checks) was 40 % of k_delta2d.
-constexpr double SQRT_TINY = 1e-300;
+// sqrt(x) for finite x > 0 from the hardware estimate r of 1/sqrt (relative error
+// below 2^-22, of subnormal x too) and one third-order step: with t = x r and
+// e = 1 - t r, sqrt(x) = t (1 - e)^(-1/2) = t + t e (1/2 + 3/8 e + O(e^2)), within an ulp
+// of the correctly rounded root.  The IEEE sequence (range scaling, three steps,
+// class checks) was 40 % of k_delta2d.  0 and infinity give NaN: a sum under the root
+// begins with SQRT_TINY, the smallest double, whose root is 2^-537 exactly, and
+// edge_norms takes the roots of sums that were 0, and the NaN of infinite ones, out of
+// its results.
+constexpr double SQRT_TINY = 0x1p-1074;
 __device__ inline double sqrt_nr(double x) {
     const double r = __builtin_amdgcn_rsq(x);
     const double t = x * r;
@@ -1070,6 +1073,15 @@ __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double 
     }
 #pragma unroll
     for (int m = 0; m < K1; ++m) acc[m] = 0.0;
+    // what the sums of the roots come to where every sum of squares is 0 (exactly: the
+    // additions below, scaled by 2^537); a sum of larger ones does not change by it
+    constexpr double none = [] {
+        constexpr Tab2<K> t = make_tab2<K>();
+        double x = 0.0;
+        for (int i = 0; i < 4; ++i)
+            for (int g = 0; g < Q; ++g) x += t.w[g];
+        return x * 0x1p-537;
+    }();
     double tiny = SQRT_TINY;                     // in a register: as a constant it is moved there for every sum
     asm volatile("" : "+v"(tiny));
 #pragma unroll 1
@@ -1148,7 +1160,7 @@ __device__ inline void edge_norms(const double (&u)[K + 1][K + 1], const double 
         }
     }
 #pragma unroll
-    for (int m = 1; m < K1; ++m) acc[m] *= sct[m];
+    for (int m = 1; m < K1; ++m) acc[m] = min_d(acc[m] - none, INFINITY) * sct[m];
 }
 
 // A workgroup takes one mesh of one component of a tile, a cell per thread: only

@@ -226,3 +226,44 @@ def test_negative_pressure_is_reported_and_the_arrays_stay_finite(k, space):
             if nsteps:
                 with pytest.raises(ora.OracleError, match="ENONPHYSICAL"):
                     ora.run2d(prob, uC, uD, nsteps=nsteps, cfl=0.3)
+
+
+def _wave_and_step(k, space):
+    prob = Problem2D(k=k, nc=1, flux=FLUX_ADVECTION, nx=24, ny=17, xlo=0.0, xhi=1.2, ylo=0.0, yhi=0.7, a=1.0, b=-0.6,
+                     space=space)
+
+    def f(X, Y):
+        return (0.3 * np.sin(2 * math.pi * X / 1.2) * np.cos(2 * math.pi * Y / 0.7) + (np.mod(X, 1.2) > 0.5))[None]
+    return (prob,) + tuple(inputs.project_2d(f, prob))
+
+
+@pytest.mark.parametrize("k,space", [(1, 0), (2, 0), (2, 1), (3, 0), (3, 1)])
+@pytest.mark.parametrize("e", [-480, -500, 480])
+def test_damping_does_not_depend_on_the_scale_of_the_data(k, space, e):
+    """Advection of data scaled by 2^e: the scaled result.  The smallest squares
+    under the roots are subnormal there, to 2^-1075 of them: 2^-37 of sigma
+    in a root at e = -500, 4e-10 of a result after nine stages."""
+    prob, uC, uD = _wave_and_step(k, space)
+    g, _, _ = _gpu_run(prob, uC, uD, 0.3, nsteps=3)
+    s, _, _ = _gpu_run(prob, np.ldexp(uC, e), np.ldexp(uD, e), 0.3, nsteps=3)
+    assert _rel([np.ldexp(x, -e) for x in s], g) <= 1e-9
+
+
+@pytest.mark.parametrize("k,space", [(1, 1), (2, 0), (3, 1)])
+def test_damping_where_the_squares_overflow(k, space):
+    """Advection of data of 2^700: infinite roots, of which the factor is 0, as in the oracle."""
+    prob, uC, uD = _wave_and_step(k, space)
+    uC, uD = np.ldexp(uC, 700), np.ldexp(uD, 700)
+    g, _, _ = _gpu_run(prob, uC, uD, 0.3, nsteps=1)
+    r = ora.run2d(prob, uC, uD, nsteps=1, cfl=0.3)
+    assert _rel(g, r) <= TOL
+
+
+@pytest.mark.parametrize("k,space", [(1, 1), (2, 0), (3, 1)])
+def test_damping_where_the_squares_vanish(k, space):
+    """Of 2^-560 and of 2^-700: every root is exactly 0, and the jumps of order 0, which
+    are not squared, give the damping of both."""
+    prob, uC, uD = _wave_and_step(k, space)
+    g, r = (_gpu_run(prob, np.ldexp(uC, e), np.ldexp(uD, e), 0.3, nsteps=1)[0] for e in (-560, -700))
+    assert _rel([np.ldexp(x, 140) for x in r], g) <= TOL
+    assert all(np.abs(x[0, 1, 0]).max() > 0.0 for x in (*g, *r))
