@@ -47,9 +47,9 @@ __host__ __device__ constexpr int nthreads(int T) { return 2 * T + WAVE; }
 // Damping factors of one cell: fac[j] = exp(-tau * sum_{m<=j} delta^m), j >= 1,
 // delta^m = (2m+1) 2^m / ((2k-1) m! h) * max_q beta (|dR_q| + |dL_q|) / sigma_q
 // with dR, dL the xi-derivatives of order m of (own trace - other mesh at its
-// centre) at the right and left edge.  isig: 1 / sigma_q, 0 where sigma_q = 0 (the
-// component then contributes 0): one product per order and component instead of a
-// division and a branch.
+// centre) at the right and left edge.  isig, tau: of scale_small (isig = 0 where
+// sigma_q = 0: the component then contributes 0): one product per order and component
+// instead of a division and a branch.
 template <int K, int NC>
 __device__ inline void oe_factors(const double (&own)[NC][K + 1], const double (&nl)[NC][K + 1],
                                   const double (&nr)[NC][K + 1], double beta, const double *isig, double hinv,
@@ -71,7 +71,7 @@ __device__ inline void oe_factors(const double (&own)[NC][K + 1], const double (
                 vr += nr[q][n] * tb.D0[m][n];
                 vl += nl[q][n] * tb.D0[m][n];
             }
-            dm = max_d(dm, beta * (fabs(ur - vr) + fabs(ul - vl)) * isig[q]);
+            dm = max_d(dm, beta * (fabs(ur - vr) + fabs(ul - vl)) * fabs(isig[q]));
         }
         S += tb.C[m] * hinv * dm;
         if (m >= 1) fac[m] = exp(-tau * S);
@@ -300,7 +300,7 @@ __device__ inline void lds_overlaps(const TCell &c, const double *uo, CellIn<K, 
 
 template <int K, int FLUX>
 __device__ inline void damp_cell(const Inst1D &I, const TCell &c, CellIn<K, FLUX> &ci,
-                                 const double (&isig)[FluxT<FLUX>::NC], double tau, bool damp) {
+                                 double (&isig)[FluxT<FLUX>::NC], bool small, double tau, bool damp) {
     using F = FluxT<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1;
     if (damp && c.damps && (ci.real || ci.mirror)) {
@@ -309,6 +309,7 @@ __device__ inline void damp_cell(const Inst1D &I, const TCell &c, CellIn<K, FLUX
         for (int q = 0; q < NC; ++q) ubar[q] = ci.own[q][0];
         const double beta = F::speed(ubar, I.p0);
         double fac[K1];
+        if (small) scale_small(isig, tau);
         oe_factors<K, NC>(ci.own, ci.nl, ci.nr, beta, isig, I.hinv, tau, fac);
 #pragma unroll
         for (int q = 0; q < NC; ++q)
@@ -457,12 +458,17 @@ __device__ inline void tile_partials(const Inst1D &I, const TCell &c, const doub
     }
 }
 
-// 1 / sigma of a component (0 where sigma = 0) from its reduced statistics of a
-// mesh of ncell cells.  (Clamped, so that a subnormal sigma gives no infinity.)
-__device__ inline double inv_sigma(double sum, double mx, double mn, double ncell) {
-    const double avg = div_nr(sum, ncell);
-    const double sig = fmax(mx - avg, avg - mn);
-    return sig != 0.0 ? fmin(1.0 / sig, 1.7976931348623157e308) : 0.0;
+// recip_sigma of NC components from their reduced statistics of a mesh of ncell cells
+// (sum, max and min of each in turn).
+template <int NC>
+__device__ inline bool inv_sigma(const double *stats, double ncell, double (&isig)[NC]) {
+    double sig[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+        const double avg = div_nr(stats[3 * q], ncell);
+        sig[q] = fmax(stats[3 * q + 1] - avg, avg - stats[3 * q + 2]);
+    }
+    return recip_sigma(sig, isig);
 }
 
 // LDS of a tile: the damped and the undamped image of both meshes, columns
@@ -489,10 +495,11 @@ __device__ inline void put_undamped(const TCell &c, const CellIn<K, FLUX> &ci, d
 // ci.own and in the damped image.
 template <int K, int FLUX, int T>
 __device__ inline void damp_and_put(const Inst1D &I, const TCell &c, CellIn<K, FLUX> &ci,
-                                    const double (&isig)[FluxT<FLUX>::NC], double tau, bool damp, double *smem) {
+                                    double (&isig)[FluxT<FLUX>::NC], bool small, double tau, bool damp,
+                                    double *smem) {
     constexpr int NC = FluxT<FLUX>::NC, W = lds_width(T), PER = NC * (K + 1) * W;
     if (damp && c.damps && (ci.real || ci.mirror)) lds_overlaps<K, FLUX, W>(c, smem + (3 - c.mesh) * PER, ci);
-    damp_cell<K, FLUX>(I, c, ci, isig, tau, damp);
+    damp_cell<K, FLUX>(I, c, ci, isig, small, tau, damp);
     if (c.damps) lds_put<K, NC, W>(smem + c.mesh * PER, c.col, ci.own);
 }
 
@@ -605,6 +612,7 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
     double isig[NC], hsig[NC], beta[2] = {0.0, 0.0};   // of this thread's mesh; the wave speeds of both
 #pragma unroll
     for (int q = 0; q < NC; ++q) isig[q] = hsig[q] = 0.0;
+    bool small = false;                      // a subnormal sigma (recip_sigma; FOLDED: by its sign)
     if (need_red) {
         if (folded) {
             const double *rd = a.red + (long long)tl.inst * NSTAT;
@@ -636,9 +644,7 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
     if (need_red && !folded) {
         finish_partials<NT, NC>(pv, a.part[sp ^ 1], I.tile0, I.npart, need_beta, scratch);
         if (damp) {
-            const double *own = scratch + 3 * NC * c.mesh;
-#pragma unroll
-            for (int q = 0; q < NC; ++q) isig[q] = inv_sigma(own[3 * q], own[3 * q + 1], own[3 * q + 2], (double)ncell);
+            small = inv_sigma(scratch + 3 * NC * c.mesh, (double)ncell, isig);
         }
         if (need_beta) {
 #pragma unroll
@@ -682,8 +688,8 @@ __device__ void stage_tile(const StageArgs &a, int l, int par, int first, int ti
 
     const double dtau = (l == 0) ? prev.tau : tau;
     if constexpr (FOLDED)
-        if (tid < WAVE) damp_and_put<K, FLUX, T>(I, hc, hi, hsig, dtau, damp, smem);
-    damp_and_put<K, FLUX, T>(I, c, ci, isig, dtau, damp, smem);
+        if (tid < WAVE) damp_and_put<K, FLUX, T>(I, hc, hi, hsig, any_small(hsig), dtau, damp, smem);
+    damp_and_put<K, FLUX, T>(I, c, ci, isig, FOLDED ? any_small(isig) : small, dtau, damp, smem);
     __syncthreads();
 
     double out[NC][K1];
@@ -795,22 +801,22 @@ __device__ void final_tile(const StageArgs &a, int tile, double *smem, bool xwl)
     }
     put_undamped<K, FLUX, T>(c, ci, smem);
     double isig[NC];
+    bool small = false;
 #pragma unroll
     for (int q = 0; q < NC; ++q) isig[q] = 0.0;
     if (damp) {
         if (a.red) {                         // folded (launch_fold_final_1d)
 #pragma unroll
             for (int q = 0; q < NC; ++q) isig[q] = a.red[(long long)tl.inst * NSTAT + stat_index(c.mesh, q, 1)];
+            small = any_small(isig);
         } else {
             reduce_instance<nthreads(T), NC>(a.part[(int)((a.ns * N - 1) & 1)], I.tile0, I.npart, false, scratch);
-            const double ncell = (double)(c.mesh == 0 ? I.np : I.nd), *own = scratch + 3 * NC * c.mesh;
-#pragma unroll
-            for (int q = 0; q < NC; ++q) isig[q] = inv_sigma(own[3 * q], own[3 * q + 1], own[3 * q + 2], ncell);
+            small = inv_sigma(scratch + 3 * NC * c.mesh, (double)(c.mesh == 0 ? I.np : I.nd), isig);
         }
     }
     __syncthreads();
     if (damp && c.owned) lds_overlaps<K, FLUX, lds_width(T)>(c, smem + (3 - c.mesh) * NC * K1 * lds_width(T), ci);
-    damp_cell<K, FLUX>(I, c, ci, isig, tau, damp);
+    damp_cell<K, FLUX>(I, c, ci, isig, small, tau, damp);
     if (c.owned) {
         const int ncell = c.mesh == 0 ? I.np : I.nd;
         double *dst = c.mesh == 0 ? a.dstC + I.offC : a.dstD + I.offD;
@@ -907,9 +913,10 @@ __global__ __launch_bounds__(nthreads(T)) void k_fold(StageArgs a, int src) {
     double *red = a.red + (long long)b * NSTAT;
     if (tid < 2 * NC) {
         const double *t = out + 3 * tid;
-        double *r = red + triple_row<NC>(tid);
+        double *r = red + triple_row<NC>(tid), isig[1];
+        inv_sigma(t, (double)(tid < NC ? I.np : I.nd), isig);
         r[0] = t[0];
-        r[1] = inv_sigma(t[0], t[1], t[2], (double)(tid < NC ? I.np : I.nd));
+        r[1] = isig[0];
         r[2] = t[2];
     } else if (tid < 2 * NC + 2) {
         red[ST_BETA + tid - 2 * NC] = out[6 * NC + tid - 2 * NC];
@@ -998,7 +1005,9 @@ __device__ inline void fold_rows(const StageArgs &a, int src, int *last) {
         if constexpr (SPEEDS) {
             red[1] = v[1];
         } else {
-            red[1] = inv_sigma(v[0], v[1], v[2], (double)(g < NC ? I.np : I.nd));
+            double isig[1];
+            inv_sigma(v, (double)(g < NC ? I.np : I.nd), isig);
+            red[1] = isig[0];
             red[2] = v[2];
         }
     }
@@ -1209,21 +1218,17 @@ __global__ __launch_bounds__(SOLO_TILES * WAVE) void k_solo(StageArgs a, long lo
             const bool damp = I.oe && K > 0 && (l > 0 || n0 + steps > 0);
             __syncthreads();
             double isig[NC];
+            bool small = false;
 #pragma unroll
             for (int q = 0; q < NC; ++q) isig[q] = 0.0;
             const int j = min(lane % SOLO_TILES, ntile - 1);
             const bool in = lane % SOLO_TILES < ntile;
             if (damp) {
+                double v[3 * NC];
 #pragma unroll
-                for (int q = 0; q < NC; ++q) {
-                    double v[3];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        v[k] = in ? rec[c.mesh][3 * q + k][j] : stat_identity(k);
-                        v[k] = group_reduce(k, v[k]);
-                    }
-                    isig[q] = inv_sigma(v[0], v[1], v[2], (double)ncell);
-                }
+                for (int k = 0; k < 3 * NC; ++k)
+                    v[k] = group_reduce(k % 3, in ? rec[c.mesh][k][j] : stat_identity(k % 3));
+                small = inv_sigma(v, (double)ncell, isig);
             }
             if (l == 0) {
                 if (a.dt_fixed > 0.0) {
@@ -1243,7 +1248,7 @@ __global__ __launch_bounds__(SOLO_TILES * WAVE) void k_solo(StageArgs a, long lo
                 lds_cell<K, NC, W>(oundamped, lc, ci.nl);
                 lds_cell<K, NC, W>(oundamped, rc, ci.nr);
             }
-            damp_cell<K, FLUX>(I, c, ci, isig, l == 0 ? ptau : tau, damp);
+            damp_cell<K, FLUX>(I, c, ci, isig, small, l == 0 ? ptau : tau, damp);
             put(damped, false);
             __syncthreads();
             double out[NC][K1];

@@ -32,7 +32,6 @@
 #include "oecdg_tables.h"
 
 #include <algorithm>
-#include <cfloat>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -182,7 +181,8 @@ constexpr Tab2<K> make_tab2() {
 // Global scalars of the current stage (written by k_reduce2d).
 struct Stats2 {
     double avg[2][4], sig[2][4];  // per mesh and component
-    double isig[2][4];            // 1 / sigma, 0 where sigma is 0 (the component takes no part in the damping)
+    double isig[2][4];            // recip_sigma of sigma
+    int small;                    // whether one of them is of a subnormal sigma
     double bx, by;                // largest x / y wave speeds at cell averages (both meshes)
     double t;                     // start time of the current step
     double tau, tau_max;          // the current step
@@ -299,17 +299,21 @@ __device__ inline void load_numerators(const double *__restrict__ N, long long p
     for (int e = 0; e < (K + 1) * NC; ++e, p += plane) nv[e] = *p;
 }
 
-// Damping factors exp(-tau sum_{m<=j} delta^m), j = 1..K, of a cell,
-// delta^m = max_q N^m_q / sigma_q (isig: 1 / sigma_q, 0 where sigma_q is 0).
+// Damping factors exp(-tau sum_{m<=j} delta^m), j = 1..K, of a cell of a mesh,
+// delta^m = max_q N^m_q / sigma_q.
 template <int K, int NC>
-__device__ inline void damp_factors(const double (&nv)[(K + 1) * NC], const double *__restrict__ isig, double tau,
+__device__ inline void damp_factors(const double (&nv)[(K + 1) * NC], const Stats2 *__restrict__ st, int mesh,
                                     double (&f)[K]) {
+    double isig[NC], tau = st->tau_damp;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) isig[q] = st->isig[mesh][q];
+    if (st->small) scale_small(isig, tau);
     double S = 0.0;
 #pragma unroll
     for (int m = 0; m <= K; ++m) {
         double dm = 0.0;                         // (drops a NaN: the wave speed of a cell of negative pressure)
 #pragma unroll
-        for (int q = 0; q < NC; ++q) dm = max_d(dm, nv[m * NC + q] * isig[q]);
+        for (int q = 0; q < NC; ++q) dm = max_d(dm, nv[m * NC + q] * fabs(isig[q]));
         S += dm;
         if (m >= 1) f[m - 1] = exp(-tau * S);
     }
@@ -713,7 +717,7 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
     {
         double f[K];
         if (a.damp) {
-            damp_factors<K, NC>(n0, st->isig[c0.mesh], st->tau_damp, f);
+            damp_factors<K, NC>(n0, st, c0.mesh, f);
 #pragma unroll
             for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -730,7 +734,7 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
     if (more) {
         double f[K];
         if (a.damp) {
-            damp_factors<K, NC>(n1, st->isig[c1.mesh], st->tau_damp, f);
+            damp_factors<K, NC>(n1, st, c1.mesh, f);
 #pragma unroll
             for (int q = 0; q < NC / PARTS; ++q)
 #pragma unroll
@@ -848,7 +852,7 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
     if (valid && FM && a.l == 0) {               // the factors of the step's input, for its later stages
         double nv[K1 * NC];
         load_numerators<K, NC>(mesh ? a.numD : a.numC, a.plane, gofs, nv);
-        damp_factors<K, NC>(nv, st->isig[mesh], st->tau_damp, fn);
+        damp_factors<K, NC>(nv, st, mesh, fn);
 #pragma unroll
         for (int j = 0; j < K; ++j) FM[j * a.plane] = fn[j];
     }
@@ -894,7 +898,7 @@ __global__ __launch_bounds__(256) void k_damp2d(Stage2Args a) {
     if (a.damp) {
         double nv[K1 * NC];
         load_numerators<K, NC>(mesh ? a.numD : a.numC, a.plane, g, nv);
-        damp_factors<K, NC>(nv, a.st->isig[mesh], a.st->tau_damp, f);
+        damp_factors<K, NC>(nv, a.st, mesh, f);
     }
     const double *in = (mesh ? a.inD : a.inC) + g;
     double *out = (mesh ? a.outD : a.outC) + g;
@@ -988,7 +992,11 @@ __device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
         const double sig = fmax(t[1] - avg, avg - t[2]);
         st->avg[mesh][q] = avg;
         st->sig[mesh][q] = sig;
-        st->isig[mesh][q] = sig != 0.0 ? fmin(1.0 / sig, DBL_MAX) : 0.0;
+        const double s[1] = {sig};
+        double is[1];
+        const bool any = __any(recip_sigma(s, is));   // (all in one wave)
+        st->isig[mesh][q] = is[0];
+        if (tid == 0) st->small = any;
     }
     if (tid != 0) return;
     const double bx = max_d(lds[3 * NC], lds[NM + 3 * NC]), by = max_d(lds[3 * NC + 1], lds[NM + 3 * NC + 1]);

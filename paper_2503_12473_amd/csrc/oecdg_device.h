@@ -23,6 +23,47 @@ __device__ inline double div_nr(double a, double b) {
     return fma(fma(-b, q, a), r, q);
 }
 
+// 1 / sigma of components as the damping takes it: 0 where sigma is 0 (the component takes
+// no part), and -1 / (SMALL_SCALE sigma) of a subnormal sigma, whose reciprocal may
+// overflow; whether there is one.  scale_small then brings the others of the cell to that
+// scale and takes it out of the exponents through tau; the damping reads the magnitudes.
+constexpr double SMALL_SCALE = 0x1p64;
+template <int NC>
+__device__ inline bool recip_sigma(const double (&sig)[NC], double (&isig)[NC]) {
+    double least = sig[0];
+    bool small = false;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+        isig[q] = 1.0 / sig[q];
+        if (q > 0) least = fmin(least, sig[q]);
+    }
+    if (least < 0x1p-1022) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+            if (sig[q] == 0.0) isig[q] = 0.0;
+            if (sig[q] > 0.0 && sig[q] < 0x1p-1022) {
+                isig[q] = -1.0 / (SMALL_SCALE * sig[q]);
+                small = true;
+            }
+        }
+    }
+    return small;
+}
+template <int NC>
+__device__ inline bool any_small(const double (&isig)[NC]) {
+    long long any = 0;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) any |= __builtin_bit_cast(long long, isig[q]);
+    return any < 0;
+}
+template <int NC>
+__device__ inline void scale_small(double (&isig)[NC], double &tau) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+        if (isig[q] > 0.0) isig[q] *= 1.0 / SMALL_SCALE;
+    tau *= SMALL_SCALE;
+}
+
 // ---------------------------------------------------------------- fluxes ---
 
 template <int FLUX> struct FluxT;

@@ -531,3 +531,22 @@ def test_small_scalar_runs_give_the_bits_of_stage_launches(n, flux, bc, k, rk):
             outs.append(res)
     for x, y in zip(*outs):
         assert x == y if isinstance(x, tuple) else np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("mode,fold", [(_lib.MODE_AUTO, 0), (_lib.MODE_EAGER, 1), (_lib.MODE_EAGER, 2)])
+@pytest.mark.parametrize("k,n", [(1, 40), (2, 64), (3, 100), (2, 5000)])
+def test_damping_of_subnormal_data(k, n, mode, fold):
+    """Advection of data of 2^-1040, whose 1 / sigma overflows: the scaled result to the
+    rounding of subnormal numbers (2^-34 of the data each, some hundred of them a stage)."""
+    prob = Problem1D(k=k, nc=1, flux=FLUX_ADVECTION, bc=BC_PERIODIC, n=n, xlo=0.0, xhi=1.0, a=0.75)
+    uC, uD = inputs.project_1d(lambda x: (np.sin(2 * np.pi * x) + 2.0 * (np.mod(x, 1.0) > 0.3))[None], prob)
+    outs = []
+    for e in (0, -1040):
+        print(f"[subnormal] k={k} n={n} mode={mode} fold={fold} e={e}", flush=True)
+        with OECDG(prob, 0.1) as s:
+            s.set_option(_lib.OPT_MODE, mode)
+            s.set_option(_lib.OPT_FOLD, fold)
+            a, b = to_device(np.ldexp(uC, e)), to_device(np.ldexp(uD, e))
+            s.run(a, b, nsteps=3)
+            outs.append([np.ldexp(x.cpu().numpy().reshape(uC.shape), -e) for x in (a, b)])
+    assert _rel(*outs[1], *outs[0]) <= 2e-7

@@ -267,3 +267,12 @@ def test_damping_where_the_squares_vanish(k, space):
     g, r = (_gpu_run(prob, np.ldexp(uC, e), np.ldexp(uD, e), 0.3, nsteps=1)[0] for e in (-560, -700))
     assert _rel([np.ldexp(x, 140) for x in r], g) <= TOL
     assert all(np.abs(x[0, 1, 0]).max() > 0.0 for x in (*g, *r))
+
+
+@pytest.mark.parametrize("k,space", [(1, 0), (2, 1), (3, 0)])
+def test_damping_of_subnormal_data(k, space):
+    """Of 2^-1040, whose 1 / sigma overflows: the result of 2^-560 scaled (the squares
+    vanish in both), to the rounding of subnormal numbers."""
+    prob, uC, uD = _wave_and_step(k, space)
+    g, r = (_gpu_run(prob, np.ldexp(uC, e), np.ldexp(uD, e), 0.3, nsteps=3)[0] for e in (-560, -1040))
+    assert _rel([np.ldexp(x, 480) for x in r], g) <= 2e-7
