@@ -14,7 +14,9 @@ constexpr int WAVE = 64;
 // a / b by the steps of the IEEE division without its range scaling and fix-up:
 // the same bits wherever those do nothing (b and the quotient within about
 // 2^+-1000 and neither 0 nor infinite), 8 instructions instead of 11.  b = 0
-// gives NaN instead of an infinity; both make the output non-finite.
+// gives NaN instead of an infinity; both make the output non-finite.  div_nr0 has the
+// fix-up of zeros and infinities: a wave speed has to stay infinite, as a maximum drops
+// a NaN.
 __device__ inline double div_nr(double a, double b) {
     double r = __builtin_amdgcn_rcp(b);
     r = fma(r, fma(-b, r, 1.0), r);
@@ -22,6 +24,7 @@ __device__ inline double div_nr(double a, double b) {
     const double q = a * r;
     return fma(fma(-b, q, a), r, q);
 }
+__device__ inline double div_nr0(double a, double b) { return __builtin_amdgcn_div_fixup(div_nr(a, b), b, a); }
 
 // 1 / sigma of components as the damping takes it: 0 where sigma is 0 (the component takes
 // no part), and -1 / (SMALL_SCALE sigma) of a subnormal sigma, whose reciprocal may
@@ -94,9 +97,9 @@ template <> struct FluxT<2> {          // Euler (rho, m, E), ideal gas
     // |v| + sqrt(gamma |p| / rho): |v| + c for every physical state, finite
     // where a tolerated non-positive pressure sits at a cell average
     __device__ static inline double speed(const double *u, double g) {
-        const double v = div_nr(u[1], u[0]);
+        const double v = div_nr0(u[1], u[0]);
         const double p = (g - 1.0) * (u[2] - 0.5 * u[1] * v);
-        return fabs(v) + sqrt(div_nr(g * fabs(p), u[0]));
+        return fabs(v) + sqrt(div_nr0(g * fabs(p), u[0]));
     }
     __device__ static inline bool physical(const double *u, double g) {
         if (!(u[0] > 0.0)) return false;

@@ -550,3 +550,20 @@ def test_damping_of_subnormal_data(k, n, mode, fold):
             s.run(a, b, nsteps=3)
             outs.append([np.ldexp(x.cpu().numpy().reshape(uC.shape), -e) for x in (a, b)])
     assert _rel(*outs[1], *outs[0]) <= 2e-7
+
+
+@pytest.mark.parametrize("fold", [1, 2])
+@pytest.mark.parametrize("slope", [0.0, 0.2])
+def test_zero_density_gives_no_time_step(slope, fold):
+    """A cell average of zero density and nonzero momentum has no finite wave speed:
+    oecdg_dt and a run report it, whatever the wave speeds of the other cells."""
+    prob, uC, uD = inputs.euler_riemann(64, 1, (1.0, 1.0, 0.5, 0.5))
+    uC = uC.copy()
+    uC[0, :, 10] = 0.0, slope
+    uC[1, 0, 10] = 0.1
+    with OECDG(prob, 0.15) as s:
+        s.set_option(_lib.OPT_FOLD, fold)
+        for call in (s.dt, lambda a, b: s.run(a, b, nsteps=1)):
+            with pytest.raises(_lib.OECDGError) as e:
+                call(to_device(uC), to_device(uD))
+            assert e.value.code == _lib.ENONFINITE
