@@ -617,8 +617,10 @@ int oecdg::adjoint_1d(oecdg_handle *h, const double *uC0, const double *uD0, int
     const size_t segsz = (size_t)ckpt * 6 * S2 + (size_t)ckpt * 3 * psz;
     const size_t slotsz = (2 * sizeof(Slot) + sizeof(Final) + sizeof(double) - 1) / sizeof(double);
     // workspace: checkpoints | 2 x segment (states, 6 per step | partials, 3 per step) |
-    //            2 adjoints | acc | 2 x (lp, cR, cL) | 2 x block partials | step slots of the second stream
-    const size_t need = (size_t)std::max<long long>(nseg, 1) * S2 + 2 * segsz + 9 * S2 + 2 * bpsz + slotsz;
+    //            2 adjoints | acc | 2 x (lp, cR, cL) | 2 x block partials | the second stream's step slots and,
+    //            where the statistics are folded, its fold
+    const size_t foldsz = fold_on(h) ? NSTAT + (size_t)3 * FOLD_GROUPS * h->foldblk : 0;
+    const size_t need = (size_t)std::max<long long>(nseg, 1) * S2 + 2 * segsz + 9 * S2 + 2 * bpsz + slotsz + foldsz;
     if (!h->aux) HIPCHK(h, hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
     for (hipEvent_t &e : h->adj_ev)
         if (!e) HIPCHK(h, hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -649,10 +651,14 @@ int oecdg::adjoint_1d(oecdg_handle *h, const double *uC0, const double *uD0, int
     StageArgs base = base_args(h);
     base.dt_fixed = dt;
     base.t_end = INFINITY;
-    base.red = nullptr;                                      // the recomputation reduces in-kernel
-    StageArgs baux = base;                                   // the second stream keeps its own step slots
+    StageArgs baux = base;                                   // the second stream keeps its own step slots and fold
     baux.slots = (Slot *)slotmem;
     baux.fin = (Final *)((Slot *)slotmem + 2);
+    if (base.red) {
+        baux.red = slotmem + slotsz;
+        baux.foldw = baux.red + NSTAT;
+        baux.foldn = h->foldn + (size_t)FOLD_PAD * FOLD_GROUPS * h->nbatch;
+    }
     int rc;
     // Stage l of step nn (step j of the segment in buffer b), keeping every
     // stage state and its partial statistics; (inC, inD, inP) is the undamped
@@ -675,6 +681,7 @@ int oecdg::adjoint_1d(oecdg_handle *h, const double *uC0, const double *uD0, int
         a.DD = nullptr;
         a.part[sp] = pp(b, j, l);
         a.part[sp ^ 1] = inP;
+        if (a.red) HIPCHK(h, launch_fold_1d(a, h->flux, h->tile, h->maxpart, s));
         for (const auto &g : h->groups) {
             StageArgs c = a;
             c.tbeg = g.tbeg;
@@ -928,9 +935,9 @@ int oecdg_init(const oecdg_desc *d, int32_t nbatch, void *stream, oecdg_handle *
     if (h->rk == 4) ALLOC(h->A, sizeof(double) * (h->totC + h->totD));
     ALLOC(h->bar, sizeof(unsigned) * 2);
     ALLOC(h->red, sizeof(double) * NSTAT * nbatch);
-    ALLOC(h->foldn, sizeof(unsigned) * FOLD_PAD * FOLD_GROUPS * nbatch);
+    const std::vector<unsigned> none((size_t)FOLD_PAD * FOLD_GROUPS * (nbatch + 1), 0u);   // (one more: adjoint_1d)
+    ALLOC(h->foldn, sizeof(unsigned) * none.size());
 #undef ALLOC
-    const std::vector<unsigned> none((size_t)FOLD_PAD * FOLD_GROUPS * nbatch, 0u);
     if (hipMemcpy(h->foldn, none.data(), sizeof(unsigned) * none.size(), hipMemcpyHostToDevice) != hipSuccess) {
         oecdg_destroy(h);
         return OECDG_EHIP;

@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from oracle import adjoint_torch as adj
-from paper_2503_12473_amd import inputs
+from paper_2503_12473_amd import _lib, inputs
 from paper_2503_12473_amd.api import OECDG, to_device
 from paper_2503_12473_amd.autograd import run_differentiable
 
@@ -179,3 +179,20 @@ def test_full_size_adjoint():
     e = _rel(g[0], g[1], r[0], r[1])
     print(f"[adjoint] full size rel err {e:.3e}", flush=True)
     assert e <= ADJ_TOL
+
+
+@pytest.mark.parametrize("k,n,ckpt", [(1, 96, 2), (2, 160, 3), (3, 161, 2), (2, 64 * 321 - 1, 2)])
+def test_folded_statistics_give_the_bits_of_the_in_kernel_reduction(k, n, ckpt):
+    """The forward steps of both streams with the statistics folded, and reduced in
+    the stage kernels, over several segments."""
+    prob, uC, uD, tC, tD, tau, steps = _setup(n, k, 4 * ckpt + 1)
+    outs = []
+    for fold in (1, 2):
+        print(f"[adjoint] k={k} n={n} ckpt={ckpt} fold={fold}", flush=True)
+        with OECDG(prob, 0.3) as s:
+            s.set_option(_lib.OPT_FOLD, fold)
+            for _ in range(2):
+                g = s.adjoint(to_device(uC), to_device(uD), steps, tau, to_device(tC), to_device(tD), ckpt)
+                outs.append([x.cpu().numpy() for x in g])
+    for o in outs[1:]:
+        assert all(np.array_equal(x, y) for x, y in zip(o, outs[0]))
