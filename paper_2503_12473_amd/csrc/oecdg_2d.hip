@@ -135,7 +135,10 @@ constexpr Tab2<K> make_tab2() {
     Tab2<K> t{};
     constexpr int K1 = K + 1, Q = K + 1;
     constexpr auto g = ct::gauss<Q>();
-    for (int i = 0; i < Q; ++i) t.w[i] = g.w[i];
+    // weights whose sum is 2 exactly (a constant state stays one, and the averages'
+    // sum changes by rounding errors of both signs only)
+    for (int i = 0; i < Q; ++i) t.w[i] = Q == 2 ? 1.0 : (Q == 3 ? (i == 1 ? 8.0 / 9.0 : 5.0 / 9.0) : g.w[1]);
+    if (Q == 4) t.w[0] = t.w[3] = 1.0 - g.w[1];
     for (int d = 0; d < K1; ++d)
         for (int hf = 0; hf < 2; ++hf)
             for (int i = 0; i < Q; ++i) {
@@ -186,6 +189,7 @@ struct Stats2 {
     double bx, by;                // largest x / y wave speeds at cell averages (both meshes)
     double t;                     // start time of the current step
     double tau, tau_max;          // the current step
+    double fx, fy, ratio;         // its 2 tau_max / h_x, 2 tau_max / h_y and tau / tau_max
     double tau_damp;              // tau of the OE step applied to the next tile kernel's input
     long long nexec;              // completed steps
     int pending, last, bad;       // bad: no admissible time step
@@ -441,8 +445,12 @@ template <int K>
 __device__ inline NodeTab<K> node_tab(int p) { return node_tabs<K>.t[p]; }
 
 // Coupling and volume terms of eq:2D_H for one owned cell: R[q][a][b] = their
-// integral against P_a P_b (own-cell part of the coupling left to the caller),
-// from the damped cells of the other mesh in LDS (oth, lds_stride apart).
+// integral against P_a P_b (own-cell part of the coupling left to the caller), times
+// 16 tau_max / (h_x h_y): the coupling then has no factor but the weights.  (With
+// 1 / tau_max, the area and the inverse mass as factors their roundings, which are the
+// same in every cell and stage, added up: the sum of the averages drifted by up to 2e-14
+// in 120 stages, where it now keeps to 5e-16.)  From the damped cells of the other mesh in LDS
+// (oth, lds_stride apart).
 //
 // A quadrant (sx, sy) is evaluated in its mirror image on the upper right one.
 // With P_n(-x) = (-1)^n P_n(x) and the symmetric Gauss rule, mirroring x turns a
@@ -451,14 +459,12 @@ __device__ inline NodeTab<K> node_tab(int p) { return node_tabs<K>.t[p]; }
 // compile-time tables, and only signs of the loaded modes (flip_sign) and, where
 // the quadrant loop crosses an axis, of the sums R change.
 template <int K, int FLUX, int TX, int TY, bool PK>
-__device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, int r, double itm,
+__device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, int r, double sxx, double syy,
                                 double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NM = kept_modes<K, PK>();
     constexpr int W = Halo2<TX, TY>::W, LS = lds_stride(NC * NM);
     constexpr Tab2<K> tb = make_tab2<K>();
-    const double hx = a.hx, hy = a.hy;
-    const double sxx = 2.0 / hx, syy = 2.0 / hy, area = hx * hy / 16.0;
 #pragma unroll
     for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -537,17 +543,17 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
                     w[q] = t;
                 }
                 F::both(w, f1, f2, fp);
-                const double wc = tb.w[g] * itm, wd = tb.w[g] * syy;
+                const double wd = tb.w[g] * syy;
 #pragma unroll
                 for (int q = 0; q < NC; ++q)
 #pragma unroll
                     for (int j = 0; j < K1; ++j) {
-                        A[q][j] = fma(wc * tb.own[0][1][g][j], w[q], A[q][j]);
+                        A[q][j] = fma(tb.w[g] * tb.own[0][1][g][j], w[q], A[q][j]);
                         if (j > 0) A[q][j] = fma(wd * tb.own[1][1][g][j], f2[q], A[q][j]);
                         B[q][j] = fma(tb.w[g] * tb.own[0][1][g][j], f1[q], B[q][j]);
                     }
             }
-            const double wp = area * nt.w, wpx = wp * sxx;
+            const double wpx = nt.w * sxx;
 #pragma unroll
             for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -555,7 +561,7 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
 #pragma unroll
                     for (int j = 0; j < K1; ++j) {
                         if (!kept<K, PK>(i, j)) continue;
-                        R[q][i][j] = fma(wp * nt.p[i], A[q][j], R[q][i][j]);
+                        R[q][i][j] = fma(nt.w * nt.p[i], A[q][j], R[q][i][j]);
                         if (i > 0) R[q][i][j] = fma(wpx * nt.dp[i], B[q][j], R[q][i][j]);
                     }
         }
@@ -571,11 +577,11 @@ __device__ inline void volume2d(const Stage2Args &a, const double *oth, int s, i
 
 }
 
-// Edge terms of eq:2D_H added to R: f_dir of the other mesh on its centre line
+// Edge terms of eq:2D_H added to R, scaled like it: f_dir of the other mesh on its centre line
 // along each half-edge of direction dir; the W (S) edge is mirrored onto the E (N)
 // edge as above, the halves have tables of their own.
 template <int K, int FLUX, int TX, int TY, bool PK>
-__device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, int r,
+__device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, int r, double sxx, double syy,
                                double (&R)[Flux2D<FLUX>::NC][K + 1][K + 1]) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, Q = K + 1, NM = kept_modes<K, PK>();
@@ -584,7 +590,7 @@ __device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, in
 #pragma unroll
     for (int dir = 0; dir < 2; ++dir) {
         constexpr auto vecn = [](int dr, int q) { return NC == 4 && q == 1 + dr; };   // momentum normal to the edge
-        const double ht = -0.25 * (dir ? a.hx : a.hy);
+        const double ht = -2.0 * (dir ? syy : sxx);
 #pragma unroll 1
         for (int side = 0; side < 2; ++side) {
             const unsigned fn = side ? 0u : 0x80000000u;
@@ -652,9 +658,11 @@ __device__ inline void edges2d(const Stage2Args &a, const double *oth, int s, in
     }
 }
 
-// One RK stage (see the top of the file).
+// One RK stage (see the top of the file).  WPS waves per SIMD, no more: a fifth wave of
+// the advection kernels, whose registers allow it, costs more in the caches than it
+// hides (P3 at 512^2, three steps of RK4: 1409 us with five, 1366 with four).
 template <int K, int FLUX, int TX, int TY, int WPS, bool PK>
-__global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage2Args a) {
+__global__ __launch_bounds__(2 * mesh_threads(TX, TY)) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void k_stage2d(Stage2Args a) {
     using F = Flux2D<FLUX>;
     constexpr int NC = F::NC, K1 = K + 1, NM = kept_modes<K, PK>(), NE = NC * NM, LS = lds_stride(NE);
     constexpr int W = Halo2<TX, TY>::W, NCELL = Halo2<TX, TY>::N, MT = mesh_threads(TX, TY), NT = 2 * MT;
@@ -758,10 +766,10 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
     const bool valid = tid - mesh * MT < TX * TY && gx < a.nx && gy < a.ny;
     const long long gofs = valid ? (long long)gy * a.nx + gx : 0;
     const double *own = tile + (mesh * NCELL + (r + 1 - mesh) * W + s + 1 - mesh) * LS;
-    const double itm = 1.0 / st->tau_max, tau = st->tau;
+    const double sxx = st->fx, syy = st->fy;
     const double *oth = tile + (1 - mesh) * NCELL * LS;
     double R[NC][K1][K1];
-    volume2d<K, FLUX, TX, TY, PK>(a, oth, s, r, itm, R);
+    volume2d<K, FLUX, TX, TY, PK>(a, oth, s, r, sxx, syy, R);
     // u^n and its factors, asked for before the edges, which leave the registers for
     // them.  The undamped u^n is still there (the last stage overwrites it, each
     // cell by its own thread) and is damped again: K factors are stored instead of
@@ -792,7 +800,7 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
             for (int j = 0; j < K; ++j) fn[j] = FM[j * a.plane];
         }
     }
-    edges2d<K, FLUX, TX, TY, PK>(a, oth, s, r, R);
+    edges2d<K, FLUX, TX, TY, PK>(a, oth, s, r, sxx, syy, R);
     double cn = a.rs.cn;
     if (FM && a.l > 0) {
 #pragma unroll
@@ -815,8 +823,9 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
         cn = 1.0;
     }
 
-    // own part of the coupling, mass inverse, RK combination
-    const double im = 1.0 / (a.hx * a.hy), td = tau * a.rs.d;
+    // own part of the coupling, mass inverse, RK combination:
+    // c_{ll} u + tau d_{ll} L = (c_{ll} - lam) u + lam (R scaled), lam = d_{ll} tau / tau_max
+    const double lam = a.rs.d * st->ratio, own_c = a.rs.cw - lam;
     double bad = 0.0;                            // 0 times every output: 0, or NaN if one is not finite
     double *po = OM;
 #pragma unroll
@@ -830,8 +839,7 @@ __global__ __launch_bounds__(2 * mesh_threads(TX, TY), WPS) void k_stage2d(Stage
                     continue;
                 }
                 const double s0 = own[q * NM + kept_index<K, PK>(i, j)];
-                const double Lv = fma(R[q][i][j], (2.0 * i + 1.0) * (2.0 * j + 1.0) * im, -itm * s0);
-                const double o = fma(cn, base[q][i][j], fma(td, Lv, a.rs.cw * s0));
+                const double o = fma(cn, base[q][i][j], fma((2.0 * i + 1.0) * (2.0 * j + 1.0) / 16.0 * lam, R[q][i][j], own_c * s0));
                 bad = fma(o, 0.0, bad);
                 if (valid) *po = o;
                 R[q][i][j] = o;
@@ -921,6 +929,14 @@ constexpr int RED2_LDS = RED2_NT + 2;
 constexpr int RED2_MAXB = 64;
 constexpr int RED2_AHEAD = 8;                    // records in flight per thread
 
+__device__ inline void set_step(const Red2Args &r, double tau, double tau_max) {
+    r.st->tau = tau;
+    r.st->tau_max = tau_max;
+    r.st->fx = 2.0 * tau_max / r.hx;
+    r.st->fy = 2.0 * tau_max / r.hy;
+    r.st->ratio = tau / tau_max;
+}
+
 // Workgroup blk of r.nb folds its range of records into r.fold; the last one to
 // arrive folds those and updates the step scalars.  Both in a fixed order, so the
 // result does not depend on which one is last.  lds: RED2_LDS doubles.
@@ -942,8 +958,7 @@ __device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
     };
     if (r.mode == R2_SINGLE) {
         if (tid == 0) {
-            st->tau = r.tau_o;
-            st->tau_max = r.taumax_o;
+            set_step(r, r.tau_o, r.taumax_o);
             st->tau_damp = r.tau_o;
             st->done[0] = st->done[1] = 0;
         }
@@ -1032,8 +1047,7 @@ __device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
             tau = r.t_end - st->t;
             last = 1;
         }
-        st->tau = tau;
-        st->tau_max = tm;
+        set_step(r, tau, tm);
         st->last = last;
         st->done[r.gpar] = 0;
         st->pending = 1;
@@ -1576,7 +1590,7 @@ int stage_2d(oecdg_handle *h, int stage, double dt, double tau_max, const double
     if (rc != OECDG_OK) return rc;
     Red2Args r = red_args(x, nullptr, 1, R2_SINGLE, 0);       // the step scalars only
     r.tau_o = dt;
-    r.taumax_o = tau_max;
+    r.taumax_o = std::min(tau_max, 1e100 * dt);               // (infinite: no coupling; it is a factor of the fluxes)
     HIPCHK2(h, launch_reduce2d(x, r, s));
     Stage2Args a = stage_args(x);
     a.part = x.part[0];

@@ -276,3 +276,28 @@ def test_damping_of_subnormal_data(k, space):
     prob, uC, uD = _wave_and_step(k, space)
     g, r = (_gpu_run(prob, np.ldexp(uC, e), np.ldexp(uD, e), 0.3, nsteps=3)[0] for e in (-560, -1040))
     assert _rel([np.ldexp(x, 480) for x in r], g) <= 2e-7
+
+
+@pytest.mark.parametrize("flux", [FLUX_ADVECTION, FLUX_EULER])
+@pytest.mark.parametrize("k,space,nx,ny", [(1, 0, 34, 132), (1, 1, 74, 31), (2, 0, 40, 27), (2, 1, 36, 59), (3, 0, 27, 243),
+                                           (3, 1, 83, 38)])
+def test_the_sum_of_the_averages_has_no_drift_from_rounded_factors(k, space, nx, ny, flux):
+    """60 steps of SSP-RK2, whose weights are exact: the averages sum to their initial
+    values but for rounding errors that differ from cell to cell (some 1e-16 in 120
+    stages); a factor that every cell and stage rounds alike adds up to 1e-14."""
+    nc = 4 if flux == FLUX_EULER else 1
+    prob = Problem2D(k=k, nc=nc, flux=flux, nx=nx, ny=ny, xlo=0.0, xhi=1.2, ylo=0.0, yhi=0.7, a=1.0, b=-0.6, space=space)
+
+    def f(X, Y):
+        rho = 1.0 + 0.3 * np.sin(2 * math.pi * X / 1.2) * np.cos(2 * math.pi * Y / 0.7)
+        return np.stack([rho, 0.3 * rho, -0.2 * rho, 2.5 + 0.065 * rho][:nc])
+    uC, uD = inputs.project_2d(f, prob)
+    with OECDG(prob, 0.1, rk=2) as s:
+        a, b = to_device(uC), to_device(uD)
+        s.run(a, b, nsteps=60)
+    mean = lambda u: np.array([math.fsum(x.ravel()) for x in u[:, 0, 0]])
+    m0 = mean(uC) + mean(uD)                 # (the two meshes exchange their sums)
+    m1 = mean(a.cpu().numpy().reshape(uC.shape)) + mean(b.cpu().numpy().reshape(uD.shape))
+    drift = np.abs(m1 - m0) / np.abs(m0)
+    print(f"[2d] drift k={k} space={space} {nx}x{ny} flux={flux}: {drift}", flush=True)
+    assert drift.max() <= 1e-15
