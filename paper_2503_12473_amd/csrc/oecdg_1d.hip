@@ -1345,9 +1345,9 @@ static int kernel_index(int tile, bool tailwave) {
     return (ti >= 0 && tailwave && tail_mode(tile)) ? ti + 3 : ti;
 }
 
-// Kernel pointers by (kernel, degree, flux, tile).  XW: launches with the extra
-// wave (tail tiles) use kernels whose launch bounds allow it; the others keep
-// the bounds of four waves per tile of T.  WHICH 4: the folded stage kernel.
+// Kernel pointers by (kernel, degree, flux, tile).  XW: launches with a tail tile use
+// kernels in which a lane of the wave of neighbouring cells updates the tail's dual
+// cell.  WHICH 4: the folded stage kernel.
 template <int WHICH, int KM, int FLUX, int T, bool XW>
 static void *kptr() {
     if constexpr (WHICH == 0) return (void *)k_stage<KM, FLUX, T, XW>;

@@ -183,8 +183,7 @@ constexpr Tab2<K> make_tab2() {
 
 // Global scalars of the current stage (written by k_reduce2d).
 struct Stats2 {
-    double avg[2][4], sig[2][4];  // per mesh and component
-    double isig[2][4];            // recip_sigma of sigma
+    double isig[2][4];            // recip_sigma of sigma, per mesh and component
     int small;                    // whether one of them is of a subnormal sigma
     double bx, by;                // largest x / y wave speeds at cell averages (both meshes)
     double t;                     // start time of the current step
@@ -980,7 +979,7 @@ __device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
     if (r.nb > 1) {
         if (sub == 0 && row < N)
             __hip_atomic_store(&r.fold[blk * N + row], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();                     // every store of the workgroup has been issued and waited for
+        __syncthreads();                     // (the stores are the first wave's, as the arrival, which waits for them)
         unsigned *flag = (unsigned *)(lds + RED2_NT);
         if (tid == 0) {
             const unsigned n = __hip_atomic_fetch_add(r.count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -1005,8 +1004,6 @@ __device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
         const double *t = lds + mesh * NM + 3 * q;
         const double avg = t[0] / (double)r.ncell;
         const double sig = fmax(t[1] - avg, avg - t[2]);
-        st->avg[mesh][q] = avg;
-        st->sig[mesh][q] = sig;
         const double s[1] = {sig};
         double is[1];
         const bool any = __any(recip_sigma(s, is));   // (all in one wave)

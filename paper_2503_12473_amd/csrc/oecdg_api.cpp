@@ -34,7 +34,7 @@ struct oecdg_handle {
     int64_t totC = 0, totD = 0;
     int kmax = 0, flux = 0;  // flux: kernel flux id (OECDG_FLUX_*, or 3 = Euler with reflective walls)
     int rk = 3;              // RK method of every instance (rk_stage)
-    bool tailwave = false;   // some instance's last tile updates the extra dual cell (launches carry one more wave)
+    bool tailwave = false;   // the last tile's wave of neighbouring cells updates the extra dual cell
     int ncol = 0;            // partial-statistics columns (the tiles, plus one per tail)
     int maxpart = 0;         // the most columns of one instance
     int tile = 64;
@@ -196,11 +196,10 @@ int build_tiles(oecdg_handle *h) {
     const int T = h->tile;
     // nd = np + 1 with np a multiple of T leaves dual cell np beyond np / T full
     // tiles.  When that extra tile would take the workgroup count past the
-    // number of CUs, the last tile takes the cell instead, with one more wave
-    // in every workgroup of the launch (a workgroup of five waves cannot share
-    // a CU with another, so this is used only when all tiles then fit one per
-    // CU, and for single instances).  The cell's statistics keep a partial
-    // column of their own, so the results are those of the separate tile.
+    // number of CUs, the last tile takes the cell instead, in a lane of its
+    // wave of neighbouring cells (only when all tiles then fit one per CU, and
+    // for single instances).  The cell's statistics keep a partial column of
+    // their own, so the results are those of the separate tile.
     int ncu = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)

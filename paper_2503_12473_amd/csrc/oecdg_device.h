@@ -210,9 +210,6 @@ __device__ inline double lane_value(double v, int k) {
     return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// Value of the partner lane (lane ^ 1).
-__device__ inline double pair_swap(double v) { return dpp_all<0xB1>(v); }   // quad_perm [1,0,3,2]
-
 // Reduction over the 64 lanes of a wave in a fixed tree (pairs, quads, half
 // rows, rows, then rows 0+1 and 2+3, then all four); the result is in lane 63.
 // Every lane of the wave must be active.

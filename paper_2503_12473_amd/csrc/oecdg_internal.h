@@ -115,7 +115,7 @@ struct StageArgs {
     int *err;                // [0] non-finite, [1] non-physical, [2] barrier timeout, [3] step+1 of an error
     int rk, ns;              // RK method (rk_stage) and its stages per step
     RKStage rs;              // rk_stage(rk, l), set by the stage launcher (the persistent launch forms its own)
-    int tailwave;            // launches carry one more wave, for the dual cell np of tail tiles
+    int tailwave;            // the last tile's wave of neighbouring cells also updates dual cell np
     int l;                   // stage of the step (0 .. ns-1)
     int par;                 // parity of the step index n
     int first;               // 1 for step 0 (its input is the initial data: no OE)

@@ -301,3 +301,13 @@ def test_the_sum_of_the_averages_has_no_drift_from_rounded_factors(k, space, nx,
     drift = np.abs(m1 - m0) / np.abs(m0)
     print(f"[2d] drift k={k} space={space} {nx}x{ny} flux={flux}: {drift}", flush=True)
     assert drift.max() <= 1e-15
+
+
+def test_a_stage_without_coupling():
+    """tau_max = infinity: the operator's fluxes alone, as with a tau_max beyond which
+    the coupling's share of the state rounds to nothing."""
+    prob, uC, uD = _wave_and_step(2, 0)
+    with OECDG(prob, 0.3) as s:
+        g, r = (s.stage(0, 0.01, tm, to_device(uC), to_device(uD)) for tm in (math.inf, 1e60))
+    assert all(torch.isfinite(x).all() for x in g)
+    assert _rel([x.cpu().numpy().reshape(uC.shape) for x in g], [x.cpu().numpy().reshape(uC.shape) for x in r]) <= 1e-13
