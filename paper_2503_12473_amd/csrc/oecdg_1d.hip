@@ -1467,9 +1467,10 @@ hipError_t launch_final_1d(const StageArgs &a, int kmax, int flux, int tile, hip
 }
 
 // Steps of a single small instance in one launch (k_solo): scalar fluxes without
-// wall or inflow ghosts, tiles of 32.
+// wall or inflow ghosts, tiles of 32, no descriptor flags (with which a stage
+// checks the sign of the averages of a scalar too; k_solo checks no average).
 bool solo_1d(const StageArgs &a, int flux, int tile) {
-    return a.ninst == 1 && flux <= 1 && tile == 32 && !a.red && a.inst0.npart <= SOLO_TILES;
+    return a.ninst == 1 && flux <= 1 && tile == 32 && !a.red && a.inst0.npart <= SOLO_TILES && a.inst0.flags == 0;
 }
 
 hipError_t launch_solo_1d(const StageArgs &a, int k, int flux, long long n0, int count, hipStream_t s) {
