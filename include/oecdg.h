@@ -84,7 +84,8 @@ enum {
 /* Execution modes of oecdg_run (oecdg_set_option(OECDG_OPT_MODE, ...)). */
 enum {
     OECDG_MODE_AUTO = 0,        /* library choice: graphs; the steps of a captured graph in one launch
-                                 * for scalar 1D meshes of up to 512 cells (the same bits) */
+                                 * for scalar 1D meshes of up to 512 cells without descriptor flags
+                                 * (the same bits) */
     OECDG_MODE_EAGER = 1,       /* one kernel launch per RK stage */
     OECDG_MODE_GRAPH = 2,       /* the three stage kernels of several steps captured in a hipGraph */
     OECDG_MODE_PERSISTENT = 3   /* one cooperative launch, grid barrier between stages */

@@ -108,7 +108,7 @@ struct StageArgs {
     double *DC, *DD;         // optional: damped input of stages 1 and 2 (adjoint recomputation)
     double *AC, *AD;         // classical RK4: weighted sum of the damped inputs of stages 1 and 2
     double *red;             // batched launches: [ninst][NSTAT] statistics reduced by k_fold (else null), with
-                             // 1 / sigma (0 where sigma is 0) in the place of the max
+                             // 1 / sigma (recip_sigma) in the place of the max
     double *foldw;           // [ninst][FOLD_GROUPS][foldblk][3] block results of k_fold_rows
     int foldblk;             // blocks of tiles of the largest instance
     unsigned *foldn;         // [ninst][FOLD_GROUPS] arrivals (0 between launches), FOLD_PAD apart
