@@ -1023,7 +1023,7 @@ __device__ void reduce2d(const Red2Args &r, int blk, double *lds) {
         st->tau_damp = st->tau;
     }
     if (r.mode == R2_STEP) {
-        if (!(st->t < r.t_end)) {
+        if (!(st->t < r.t_end) || st->bad) {     // (after a bad step the records are older ones')
             st->done[r.gpar] = 1;
             return;
         }

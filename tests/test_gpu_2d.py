@@ -311,3 +311,21 @@ def test_a_stage_without_coupling():
         g, r = (s.stage(0, 0.01, tm, to_device(uC), to_device(uD)) for tm in (math.inf, 1e60))
     assert all(torch.isfinite(x).all() for x in g)
     assert _rel([x.cpu().numpy().reshape(uC.shape) for x in g], [x.cpu().numpy().reshape(uC.shape) for x in r]) <= 1e-13
+
+
+@pytest.mark.parametrize("rk", [1, 2, 3, 4])
+def test_a_run_without_an_admissible_step_leaves_the_state(rk):
+    """Vacuum has no wave speed, so no step: ENONFINITE, and the arrays as they were,
+    whatever statistics an earlier run has left in the handle."""
+    from paper_2503_12473_amd import _lib
+    prob, uC, uD = _quadrants(16, 0)
+    with OECDG(prob, 0.1, rk=rk) as s:
+        s.run(to_device(uC), to_device(uD), nsteps=3)
+        uC, uD = uC.copy(), uD.copy()
+        uC[:, 0, 0] = uD[:, 0, 0] = 0.0
+        a, b = to_device(uC), to_device(uD)
+        with pytest.raises(_lib.OECDGError) as e:
+            s.run(a, b, nsteps=20)
+        assert e.value.code == _lib.ENONFINITE
+        assert np.array_equal(a.cpu().numpy().reshape(uC.shape), uC)
+        assert np.array_equal(b.cpu().numpy().reshape(uD.shape), uD)
